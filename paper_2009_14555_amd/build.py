@@ -15,7 +15,7 @@ SOURCES = [os.path.join(CSRC, "dimp_kernels.hip"), os.path.join(CSRC, "dimp_patc
            os.path.join(CSRC, "dimp_velocity.hip"), os.path.join(CSRC, "dimp_sweeps3.hip"),
            os.path.join(CSRC, "dimp_sweeps_n3.hip"),
            os.path.join(CSRC, "dimp_capi.cpp")]
-HEADERS = [os.path.join(CSRC, h) for h in ("dimp_device.hpp", "dimp_stencil.hpp", "dimp_lane.hpp", "dimp_sweeps.hpp",
+HEADERS = [os.path.join(CSRC, h) for h in ("dimp_device.hpp", "dimp_stencil.hpp", "dimp_calib.hpp", "dimp_lane.hpp", "dimp_sweeps.hpp",
                                               "dimp_internal.hpp", "dimp_pack.hpp", "dimp_patches.hpp", "dimp_adjoint.hpp",
                                               "dimp_amr.hpp")] + [
     os.path.join(ROOT, "include", "dimp.h")]

@@ -153,9 +153,9 @@ __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __res
       asm volatile("" ::: "memory");  // re-read LDS; recompute rather than keep phase-1 values live
 #pragma unroll
       for (int f = 0; f < F; ++f) U[f] = sU[f * 256 + tid];
-      Thermo<2, false> T;
+      calib::Thermo T;
       double H[6], J2;
-      cons_to_prim<2, 2, false>(P, U, W, T, H, J2);
+      calib::cons_to_prim(P, U, W, T, H, J2);
       irho0 = T.irho;
       rc2 = T.rho * T.c2;
 #pragma unroll
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __res
       }
       stencil(st);
       auto normal = [&]() -> double { return youngs2(st, P.dx, DIR); };
-      c0 = phi_candidates<2, 2, false>(P, Wm[0], W[0], Wp[0], normal);
+      c0 = calib::phi_candidates(P, Wm[0], W[0], Wp[0], normal);
       cm.mL = from_left_keep(c0.mL); cm.mR = from_left_keep(c0.mR); cm.tL = from_left_keep(c0.tL); cm.tR = from_left_keep(c0.tR);
       cp.mL = from_right_keep(c0.mL); cp.mR = from_right_keep(c0.mR); cp.tL = from_right_keep(c0.tL); cp.tR = from_right_keep(c0.tR);
     };
@@ -195,10 +195,10 @@ __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __res
       Cand cm, c0, cp;
       forward_cells(W, Wm, Wp, irho0, rc2, cm, c0, cp, st);
       double WR[F];
-      edges_predict<2, 2, false, DIR>(P, Wm, W, Wp, irho0, rc2, cm, c0, cp, nu, WL, WR);
+      calib::edges_predict<DIR>(P, Wm, W, Wp, irho0, rc2, cm, c0, cp, nu, WL, WR);
 #pragma unroll
       for (int f = 0; f < F; ++f) WRm[f] = from_left_keep(WR[f]);
-      face_flux<2, 2, false, DIR>(P, WRm, WL, fa);
+      calib::face_flux<DIR>(P, WRm, WL, fa);
     }
     // ---------------------------------------------------- 2. face reverse
     double WLb[F], WRb[F];

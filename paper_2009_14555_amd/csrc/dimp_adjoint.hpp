@@ -15,13 +15,18 @@
 // to (gamma, p_inf, G0, sigma_Y).  `own` gates the parameter accumulation so
 // that every stage instance is counted by exactly one wave.
 #pragma once
-#include "dimp_stencil.hpp"
+#include "dimp_calib.hpp"
 
 namespace dimp {
 namespace adj {
 
 using L2 = Lay<2, 2, false>;
 constexpr int F2 = L2::F;  // 11
+
+// the forward stages reversed here are the calibrated step's
+using calib::EosV;
+using calib::c2_mat;
+using calib::eos_eval;
 
 enum { PB_GAM = 0, PB_IGAM, PB_PREF, PB_EREF, PB_G0, PB_Y, PB_N };
 
@@ -160,7 +165,7 @@ __device__ __forceinline__ void c2p_bwd(const Params& P, const double* U, const 
     uu += u[k] * u[k];
   }
   double H[6], J2;
-  strain<2, 2, false>(U + L::V0, H, J2);
+  calib::strain(U + L::V0, H, J2);
   EosV e[2];
 #pragma unroll
   for (int l = 0; l < 2; ++l) e[l] = eos_eval(P.mat[l], rho[l], irho[l], J2);
@@ -372,7 +377,7 @@ __device__ __forceinline__ void stress_bwd(const Params& P, const double* W, con
   }
   const double G = gnum / xi;
   double H[6], J2;
-  strain<2, 2, false>(W + L::V0, H, J2);
+  calib::strain(W + L::V0, H, J2);
   double Gb = 0.0, Hb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -413,7 +418,7 @@ __device__ __forceinline__ void edges_bwd(const Params& P, const double* Wm, con
   double s[F], WL[F], WR[F];
 #pragma unroll
   for (int f = 0; f < F; ++f) {
-    s[f] = slope<2, 2, false>(P, f, Wm[f], W0[f], Wp[f]);
+    s[f] = calib::slope(P, f, Wm[f], W0[f], Wp[f]);
     WL[f] = W0[f] - 0.5 * s[f];
     WR[f] = W0[f] + 0.5 * s[f];
   }
@@ -426,8 +431,8 @@ __device__ __forceinline__ void edges_bwd(const Params& P, const double* Wm, con
     WR[0] = th ? c0.tR : c0.mR;
   }
   double sL[3], sR[3];
-  stress_col<2, 2, false, DIR>(P, WL, sL);
-  stress_col<2, 2, false, DIR>(P, WR, sR);
+  calib::stress_col<DIR>(P, WL, sL);
+  calib::stress_col<DIR>(P, WR, sR);
   double dW[F];
 #pragma unroll
   for (int f = 0; f < F; ++f) dW[f] = WR[f] - WL[f];
@@ -575,7 +580,7 @@ __device__ __forceinline__ void side_bwd(const Params& P, const double* W, const
     irho[l] = 1.0 / rho[l];
   }
   double H[6], J2;
-  strain<2, 2, false>(W + L::V0, H, J2);
+  calib::strain(W + L::V0, H, J2);
   EosV e[2];
 #pragma unroll
   for (int l = 0; l < 2; ++l) e[l] = eos_eval(P.mat[l], rho[l], irho[l], J2);
@@ -799,8 +804,8 @@ __device__ __forceinline__ void face_bwd(const Params& P, const double* WLf, con
                                          double* WLb, double* WRb, PBar& pb, bool own) {
   using SD = Side<2, 2, false>;
   SD A, B;
-  side_state<2, 2, false, DIR>(P, WLf, A);
-  side_state<2, 2, false, DIR>(P, WRf, B);
+  calib::side_state<DIR>(P, WLf, A);
+  calib::side_state<DIR>(P, WRf, B);
   const double uL = A.u[DIR], uR = B.u[DIR];
   const double SL = fmin(uL - A.cl, uR - B.cl);
   const double SR = fmax(uL + A.cl, uR + B.cl);
@@ -811,7 +816,7 @@ __device__ __forceinline__ void face_bwd(const Params& P, const double* WLf, con
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     unum[k] = (A.sig[k] - B.sig[k]) + (mL * A.u[k] - mR * B.u[k]);
-    ust[k] = unum[k] * frcp(mL - mR);
+    ust[k] = unum[k] * calib::rcp2(mL - mR);
   }
   const double Sst = ust[DIR];
   const bool supL = SL >= 0.0, supR = SR <= 0.0;
@@ -970,7 +975,7 @@ __device__ __forceinline__ void plastic_bwd(const Params& P, const double* U, co
 #pragma unroll
   for (int l = 0; l < 2; ++l) rho[l] = m[l] / phi[l];
   double H[6], J2;
-  strain<2, 2, false>(U + L::V0, H, J2);
+  calib::strain(U + L::V0, H, J2);
   const double J = sqrt(J2);
   double xi = 0.0, num = 0.0, wsh = 0.0, Jl[2] = {0.0, 0.0}, Gl[2] = {0.0, 0.0};
   bool yl[2] = {false, false};

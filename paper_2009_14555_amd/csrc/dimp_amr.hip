@@ -152,11 +152,12 @@ __global__ __launch_bounds__(256) void k_amr_tag(TagLayout L, const double* __re
 // (edges without the predictor); times wgt, added to what is stored with acc.
 constexpr int FLUX_SEG = 6, FLUX_PER_WAVE = 10;
 
-template <int N, int RX, int DIR, bool RK>
+template <int N, int RX, int PROF, int DIR, bool RK>
 __global__ __launch_bounds__(256) void k_amr_flux(Params P, FaceSet fs, const double* __restrict__ in, double dt,
                                                   double* __restrict__ flux, double wgt, int acc) {
   constexpr int D = 2;
   constexpr int F = Lay<D, N, RX>::F;
+  assume_profile<N, RX, PROF>(P);
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (wave * FLUX_PER_WAVE >= 2 * fs.len) return;  // uniform per wave
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(256) void k_amr_flux(Params P, FaceSet fs, const do
   }
   FaceV<D, N, RX> fa;
   double irho0;
-  lane_face<D, N, RX, DIR, RK>(P, load_U, phi_t, RK ? 1.0 / P.dx[DIR] : dt / P.dx[DIR], fa, irho0, false);
+  lane_face<D, N, RX, DIR, RK>(P, load_U, phi_t, RK ? P.idx[DIR] : dt * P.idx[DIR], fa, irho0, false);
   (void)irho0;
   if (live && l == 3) {
 #pragma unroll
@@ -261,15 +262,17 @@ hipError_t launch_amr_flux(const Params& P, int rx, int dir, const FaceSet& fs, 
   const int64_t waves = (2 * fs.len + FLUX_PER_WAVE - 1) / FLUX_PER_WAVE;
   const int grid = (int)((waves + 3) / 4);
   const int a = acc ? 1 : 0;
-#define DIMP_AMR_FLUX(NV, RXV, DIRV)                                                                           \
-  do {                                                                                                         \
-    if (rk)                                                                                                    \
-      hipLaunchKernelGGL((k_amr_flux<NV, RXV, DIRV, true>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,   \
-                         wgt, a);                                                                              \
-    else                                                                                                       \
-      hipLaunchKernelGGL((k_amr_flux<NV, RXV, DIRV, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,  \
-                         wgt, a);                                                                              \
-  } while (0)
+#define DIMP_AMR_FLUX(NV, RXV, DIRV)                                                                            \
+  (void)by_profile<NV, RXV>(P, [&](auto prof) {                                                                 \
+    constexpr int PROF = decltype(prof)::value;                                                                 \
+    if (rk)                                                                                                     \
+      hipLaunchKernelGGL((k_amr_flux<NV, RXV, PROF, DIRV, true>), dim3(grid), dim3(256), 0, st, P, fs, in, dt,    \
+                         flux, wgt, a);                                                                         \
+    else                                                                                                        \
+      hipLaunchKernelGGL((k_amr_flux<NV, RXV, PROF, DIRV, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt,   \
+                         flux, wgt, a);                                                                         \
+    return hipSuccess;                                                                                          \
+  })
 #define DIMP_AMR_FLUX_RX(NV, DIRV)          \
   do {                                      \
     if (rx == 2) DIMP_AMR_FLUX(NV, 2, DIRV); \

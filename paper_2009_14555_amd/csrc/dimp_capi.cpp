@@ -152,6 +152,7 @@ dimp::MatP pack_material(const dimp_material& m) {
   q.eos = m.eos;
   q.plast = m.plast;
   q.cv = m.cv;
+  q.abar_one = q.bbar_three = 1;  // no curve with other exponents
   if (m.eos == DIMP_EOS_ROMENSKII) {
     q.Gam = m.Gamma0;
     q.inv_rho0 = 1.0 / m.rho0;
@@ -213,12 +214,33 @@ dimp_status check_material(const dimp_material& m, const char* what) {
   return DIMP_OK;
 }
 
+// the material profile of packed parameters (PROF_*; by_profile lists the
+// ones compiled for each layout)
+int material_profile(const dimp::Params& P, int nmat, bool hist) {
+  const dimp::MatP *a = &P.mat[0], *b = &P.mat[1];
+  if (nmat < 2 || nmat > dimp::MAXMAT || a->eos == dimp::EOS_ROMENSKII || a->shear) return dimp::PROF_ANY;
+  for (int l = 1; l < nmat; ++l)
+    if (!P.mat[l].abar_one || !P.mat[l].bbar_three) return dimp::PROF_ANY;
+  const bool gas_b = b->eos != dimp::EOS_ROMENSKII && !b->shear;
+  if (!hist && nmat == 2 && gas_b) return dimp::PROF_GAS_GAS;
+  if (b->eos != dimp::EOS_ROMENSKII || !b->shear) return dimp::PROF_ANY;
+  if (!hist) return dimp::PROF_GAS_SOLID;
+  if (P.rx.kind == dimp::RXK_MIX && P.rx.mat == 0) {
+    const bool usual = P.rx.gen ? P.rx.law == dimp::LAW_IG && P.rx.jwl[0] && P.rx.jwl[1]
+                                : P.rx.law == dimp::LAW_POWER && P.rx.n_is2;
+    return usual ? dimp::PROF_GAS_SOLID : dimp::PROF_ANY;
+  }
+  if (P.rx.kind == dimp::RXK_EPS && P.rx.mat == 1) return dimp::PROF_GAS_JC;
+  return dimp::PROF_ANY;
+}
+
 void rebuild_params(dimp_ctx* h) {
   dimp::Params& P = h->P;
   std::memset(&P, 0, sizeof P);
   for (int d = 0; d < 3; ++d) {
     P.n[d] = h->n[d];
     P.dx[d] = h->dx[d];
+    P.idx[d] = 1.0 / h->dx[d];
     P.bc[d] = h->bc[d];
   }
   P.ncell = h->ncell();
@@ -239,6 +261,9 @@ void rebuild_params(dimp_ctx* h) {
     P.mat[l] = pack_material(h->mats[l]);
     if (P.mat[l].shear && !(h->reactive() && h->rx.mat == l)) P.any_shear = 1;
   }
+  // the grids the adjoint takes (need_adjoint) step its arithmetic
+  P.calib = !h->patches && h->ndim == 2 && h->nmat == 2 && !h->hist() && !h->geom &&
+            h->opt.limiter == DIMP_LIMITER_VANALBADA && h->bc[0] <= DIMP_BC_PERIODIC && h->bc[1] <= DIMP_BC_PERIODIC;
   P.rx.mat = h->rx.mat;
   P.rx.kind = dimp::RXK_MIX;
   if (h->jc_mat() >= 0) {
@@ -247,16 +272,14 @@ void rebuild_params(dimp_ctx* h) {
   }
   if (h->reactive()) {
     const dimp::MatP a = pack_material(h->rx.reactant), b = pack_material(h->rx.product);
-    P.rx.Ga = a.Gam;
     P.rx.invGa = a.invGam;
     P.rx.pa = a.pref0;
     P.rx.ea = a.eref0;
-    P.rx.cva = h->rx.reactant.cv;
-    P.rx.Gb = b.Gam;
+    P.rx.iGca = 1.0 / (a.Gam * h->rx.reactant.cv);
     P.rx.invGb = b.invGam;
     P.rx.pb = b.pref0;
     P.rx.eb = b.eref0 - h->rx.Q;
-    P.rx.cvb = h->rx.product.cv;
+    P.rx.iGcb = 1.0 / (b.Gam * h->rx.product.cv);
     P.rx.k = h->rx.k;
     P.rx.n = h->rx.n;
     P.rx.n_is2 = (h->rx.n == 2.0);
@@ -295,6 +318,7 @@ void rebuild_params(dimp_ctx* h) {
     P.rx.ig_rho0 = g[15];
     P.rx.ig_punit = g[16];
   }
+  P.prof = material_profile(P, h->nmat, h->hist());
 }
 
 dimp_status need_bound(dimp_ctx* h) {

@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace dimp {
 
 // ------------------------------------------------------------ parameters
@@ -44,8 +46,9 @@ struct RxP {
   int kind, gen;  // gen: a component has density-dependent (JWL) reference curves
   int law, pad;   // LAW_POWER or LAW_IG
   int jwl[2];     // component c is JWL
-  double Ga, invGa, pa, ea, cva;  // reactant: Gamma, 1/Gamma, constant p_ref, e_ref, C_V
-  double Gb, invGb, pb, eb, cvb;  // product (e_ref already lowered by Q)
+  double invGa, pa, ea;  // reactant: 1/Gamma, constant p_ref, e_ref
+  double invGb, pb, eb;  // product (e_ref already lowered by Q)
+  double iGca, iGcb;     // 1 / (Gamma C_V)
   double k, n, inv_pref;          // LAW_POWER: -k lam (max(p,0)/pref)^n
   // JWL terms of component c: A, B, R1 rho0, R2 rho0 and 1/(R1 rho0), 1/(R2 rho0)
   double jA[2], jB[2], jR1[2], jR2[2], jiR1[2], jiR2[2];
@@ -64,13 +67,15 @@ constexpr int MAXMAT = 3;
 struct Params {
   int64_t n[3];
   int64_t ncell;
-  double dx[3];
+  double dx[3], idx[3];  // cell widths and their inverses
   int bc[3];
   int limiter, thinc, any_shear, geom;  // geom 1: cylindrical (2-D, x = r, y = z)
   double r_lo;                           // cylindrical: radius of the grid's low x face
   double beta0, delta, eps;
   double va_e2[6];  // squared van Albada epsilon per field kind
-  int nmat, pad_nmat;
+  int nmat;
+  int prof;        // material profile (PROF_*), by the materials' types
+  int calib, pad;  // the step the adjoint differentiates (dimp_calib.hpp)
   MatP mat[MAXMAT];
   RxP rx;
 };
@@ -85,6 +90,74 @@ __device__ __forceinline__ bool rx_mix(const Params& P) {
   return RX && P.rx.kind == RXK_MIX;
 }
 constexpr int BC_PERIODIC = 1, BC_REFLECTIVE = 2, BC_AXIS = 3;
+
+// Material profiles.  The kernels are compiled for any materials (PROF_ANY:
+// every closure behind uniform branches on the material's type, with the
+// general powers of the Romenskii curves) and for the combinations the
+// workloads run, with the types stated at compile time:
+//   PROF_GAS_SOLID  material 0 a gas or the reactive mixture, material 1 a
+//                   Romenskii solid (perfect plasticity or elastic), and no
+//                   Romenskii curve with exponents other than alpha-bar = 1,
+//                   beta-bar = 3 (Table 1); a third material may be either;
+//                   a mixture of two gases burns by the quadratic power law,
+//                   one of two JWL components by ignition and growth;
+//   PROF_GAS_JC     the same with a Johnson-Cook solid in the history slot;
+//   PROF_GAS_GAS    two gases.
+// The chosen instance computes the same expressions.  Without the branches a
+// sweep is a few long blocks that the scheduler can fill: the 2-D sweeps of
+// PROF_GAS_SOLID take 126-137 VGPRs against 149-151 and hardly spill scalar
+// registers (10 lane moves against 100-190).
+//   PROF_CALIB      not a statement about the materials: the stages of
+//                   dimp_calib.hpp (Params::calib, sweeps and the initial state)
+constexpr int PROF_ANY = 0, PROF_GAS_SOLID = 1, PROF_GAS_JC = 2, PROF_GAS_GAS = 3, PROF_CALIB = 4;
+
+template <int N, int RX, int PROF>
+__device__ __forceinline__ void assume_profile(const Params& P) {
+  if constexpr (PROF != PROF_ANY && PROF != PROF_CALIB) {
+    __builtin_assume(P.mat[0].eos != EOS_ROMENSKII);
+    __builtin_assume(P.mat[0].shear == 0);
+    __builtin_assume(P.mat[1].abar_one != 0);
+    __builtin_assume(P.mat[1].bbar_three != 0);
+    if constexpr (N == 3) {
+      __builtin_assume(P.mat[2].abar_one != 0);
+      __builtin_assume(P.mat[2].bbar_three != 0);
+    }
+    if constexpr (PROF == PROF_GAS_GAS) {
+      __builtin_assume(P.mat[1].eos != EOS_ROMENSKII);
+      __builtin_assume(P.mat[1].shear == 0);
+      __builtin_assume(P.any_shear == 0);
+    } else {
+      __builtin_assume(P.mat[1].eos == EOS_ROMENSKII);
+      __builtin_assume(P.mat[1].shear != 0);
+      __builtin_assume(P.any_shear != 0);
+    }
+    if constexpr (RX != 0) {
+      __builtin_assume(P.rx.kind == (PROF == PROF_GAS_JC ? RXK_EPS : RXK_MIX));
+      __builtin_assume(P.rx.mat == (PROF == PROF_GAS_JC ? 1 : 0));
+      if constexpr (RX == 1 && PROF == PROF_GAS_SOLID) {
+        __builtin_assume(P.rx.law == LAW_POWER);
+        __builtin_assume(P.rx.n_is2 != 0);
+      }
+      if constexpr (RX == 2) {
+        __builtin_assume(P.rx.law == LAW_IG);
+        __builtin_assume(P.rx.jwl[0] != 0);
+        __builtin_assume(P.rx.jwl[1] != 0);
+      }
+    }
+  }
+}
+
+// f(std::integral_constant<int, PROF>) for the profile that P states, among
+// the ones compiled for N materials and the RX layout
+template <int N, int RX, class Fn>
+static inline hipError_t by_profile(const Params& P, Fn&& f) {
+  if (P.prof == PROF_GAS_SOLID) return f(std::integral_constant<int, PROF_GAS_SOLID>{});
+  if constexpr (RX == 1)
+    if (P.prof == PROF_GAS_JC) return f(std::integral_constant<int, PROF_GAS_JC>{});
+  if constexpr (RX == 0 && N == 2)
+    if (P.prof == PROF_GAS_GAS) return f(std::integral_constant<int, PROF_GAS_GAS>{});
+  return f(std::integral_constant<int, PROF_ANY>{});
+}
 
 // ---------------------------------------------------------------- layout
 template <int D, int N, int RX>
@@ -159,15 +232,25 @@ __device__ __forceinline__ double from_right_keep(double v) {
   return __builtin_amdgcn_update_dpp(v, v, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
 }
 
-// 1/b from the hardware reciprocal refined by two Newton steps: within an ulp
-// or two of the correctly rounded quotient, at about half the instructions
-// of an IEEE division
+// 1/b from the hardware reciprocal r (about 2^-23 relative) refined by the
+// cubic step r (1 + e + e^2), e = 1 - b r: within an ulp or two of the
+// correctly rounded quotient, in one instruction fewer than two Newton steps
+// and at well under half the cost of an IEEE division
 __device__ __forceinline__ double frcp(double b) {
-  double r = __builtin_amdgcn_rcp(b);
-  double e = fma(-b, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-b, r, 1.0);
-  return fma(r, e, r);
+  const double r = __builtin_amdgcn_rcp(b);
+  const double e = fma(-b, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
+// square root from the hardware reciprocal square root y: with r = 1 - x y^2
+// the root is x y (1 + r/2 + 3 r^2/8 + ...), two terms of which reach double
+// precision.  The added 1e-300 (nothing for x > 1e-284) keeps y finite at
+// x = 0, where the root is 0; a negative x gives NaN.
+__device__ __forceinline__ double fsqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x + 1e-300);
+  const double g = x * y;
+  const double r = fma(-g, y, 1.0);
+  return fma(g, r * fma(0.375, r, 0.5), g);
 }
 
 // a[y] for a runtime index y < M, read with compile-time indices and selects
@@ -192,42 +275,43 @@ __device__ __forceinline__ double vget(const double* V, int i, int j) {
 }
 
 // ----------------------------------------------------------- closures
-struct EosV {
-  double Gam, invGam, pref, eref, dpref, deref, G;
+// Sec. 2.3 closures at phasic density rho and strain invariant J2, in the
+// volume-specific forms the mixture rules use, none of which needs 1/rho: with
+// e_ref' = p_ref / rho^2 on a Romenskii curve,
+//   rho c^2 = rho p_ref' - (1 + Gamma) p_ref + (1 + Gamma) p
+// (a gas, with constant curves: (1 + Gamma) p - p_ref); rc is that less
+// (1 + Gamma) p, re = rho e_ref.
+struct Curve {
+  double pref, re, G, rc;
 };
 
-// Sec. 2.3 closures at phasic density rho (1/rho given) and strain invariant J2
-__device__ __forceinline__ EosV eos_eval(const MatP& m, double rho, double irho, double J2) {
-  EosV e;
-  e.Gam = m.Gam;
-  e.invGam = m.invGam;
+__device__ __forceinline__ Curve curve_eval(const MatP& m, double rho, double J2) {
+  Curve c;
   if (m.eos != EOS_ROMENSKII) {
-    e.pref = m.pref0;
-    e.eref = m.eref0;
-    e.dpref = 0.0;
-    e.deref = 0.0;
-    e.G = 0.0;
-    return e;
+    c.pref = m.pref0;
+    c.re = rho * m.eref0;
+    c.G = 0.0;
+    c.rc = -m.pref0;
+    return c;
   }
   const double x = rho * m.inv_rho0;
   const double xa = m.abar_one ? x : pow(x, m.abar);
-  const double ec = m.ec_coef * (xa - 1.0) * (xa - 1.0);
-  const double pc = m.K0a * x * xa * (xa - 1.0);
-  const double dpc = m.dpc_coef * ((2.0 * m.abar + 1.0) * xa * xa - (m.abar + 1.0) * xa);
-  double G;
+  const double xm = xa - 1.0;
+  const double kx = m.K0a * (x * xa);
+  const double slope = m.abar_one ? fma(3.0, xm, 1.0) : (2.0 * m.abar + 1.0) * xa - (m.abar + 1.0);
   if (m.bbar_three) {
     const double x2 = x * x;
-    G = m.G0 * (x2 * x2);
+    c.G = m.G0 * (x2 * x2);
   } else {
-    G = m.G0 * pow(x, m.bbar + 1.0);
+    c.G = m.G0 * pow(x, m.bbar + 1.0);
   }
-  const double GJ = G * J2;
-  e.pref = pc + m.bbar * GJ;
-  e.eref = ec + GJ * irho;
-  e.dpref = dpc + m.bbar * (m.bbar + 1.0) * GJ * irho;
-  e.deref = e.pref * irho * irho;
-  e.G = G;
-  return e;
+  const double GJ = c.G * J2;
+  const double bG = m.bbar_three ? 3.0 * GJ : m.bbar * GJ;
+  c.pref = fma(kx, xm, bG);
+  c.re = fma(rho, m.ec_coef * (xm * xm), GJ);
+  const double b1 = m.bbar_three ? 4.0 * bG : (m.bbar + 1.0) * bG;
+  c.rc = fma(kx, slope, b1) - (1.0 + m.Gam) * c.pref;
+  return c;
 }
 
 // shear modulus only (no reference curves)
@@ -241,15 +325,12 @@ __device__ __forceinline__ double shear_modulus(const MatP& m, double rho) {
   return m.G0 * pow(x, m.bbar + 1.0);
 }
 
-__device__ __forceinline__ double c2_mat(const EosV& e, double rho, double irho, double p) {
-  return e.dpref - rho * e.Gam * e.deref + ((1.0 + e.Gam) * p - e.pref) * irho;
-}
-
 // Hencky strain dev H ~ dev((B - adj B)/4), B = V V^T (Sec. 3.2: Bazant
 // approximation with the cofactor standing in for the inverse of the
-// unimodular B), and J^2 = tr(H H^T).
+// unimodular B), and J^2 = tr(H H^T).  strain4 leaves 4 H: the quarter is
+// folded into what multiplies it.
 template <int D, int N, int RX>
-__device__ __forceinline__ void strain(const double* V, double H[6], double& J2) {
+__device__ __forceinline__ void strain4(const double* V, double H[6], double& J2) {
   double B[6];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -287,32 +368,34 @@ __device__ __forceinline__ void strain(const double* V, double H[6], double& J2)
     A[4] = B[2] * B[1] - B[0] * B[4];
     A[5] = B[0] * B[3] - B[1] * B[1];
   }
-  double K[6];
 #pragma unroll
-  for (int s = 0; s < 6; ++s) K[s] = 0.25 * (B[s] - A[s]);
-  const double tr = (K[0] + K[3] + K[5]) * (1.0 / 3.0);
-  H[0] = K[0] - tr;
-  H[3] = K[3] - tr;
-  H[5] = K[5] - tr;
-  H[1] = K[1];
-  H[2] = K[2];
-  H[4] = K[4];
+  for (int s = 0; s < 6; ++s) H[s] = B[s] - A[s];
+  const double tr = (H[0] + H[3] + H[5]) * (1.0 / 3.0);
+  H[0] = H[0] - tr;
+  H[3] = H[3] - tr;
+  H[5] = H[5] - tr;
   double j2 = H[0] * H[0] + H[3] * H[3] + H[5] * H[5];
   if (D >= 2) j2 += 2.0 * (H[1] * H[1]);
   if (D == 3) j2 += 2.0 * (H[2] * H[2] + H[4] * H[4]);
-  J2 = j2;
+  J2 = 0.0625 * j2;
+}
+
+template <int D, int N, int RX>
+__device__ __forceinline__ void strain(const double* V, double H[6], double& J2) {
+  strain4<D, N, RX>(V, H, J2);
+#pragma unroll
+  for (int s = 0; s < 6; ++s) H[s] = 0.25 * H[s];
 }
 
 // ------------------------------------------------------ phase densities
-// phi_l, rho_l and 1/rho_l of every material.  For two materials one
-// division serves both densities and one both inverses.
+// phi_l and rho_l of every material
 template <int N>
 struct Phases {
-  double phi[N], rho[N], irho[N];
+  double phi[N], rho[N];
 };
 
 template <int N>
-__device__ __forceinline__ void phases_from_partial(const double* phi_st, const double* m, Phases<N>& Q) {
+__device__ __forceinline__ void phase_fractions(const double* phi_st, Phases<N>& Q) {
   double sphi = 0.0;
 #pragma unroll
   for (int l = 0; l < N - 1; ++l) {
@@ -320,105 +403,135 @@ __device__ __forceinline__ void phases_from_partial(const double* phi_st, const 
     sphi += Q.phi[l];
   }
   Q.phi[N - 1] = 1.0 - sphi;
+}
+
+// from partial densities; r is their sum and ir its inverse.  For two
+// materials one reciprocal serves all three quotients.
+template <int N>
+__device__ __forceinline__ void phases_from_partial(const double* phi_st, const double* m, Phases<N>& Q, double& r,
+                                                    double& ir) {
+  phase_fractions<N>(phi_st, Q);
+  r = 0.0;
+#pragma unroll
+  for (int l = 0; l < N; ++l) r += m[l];
   if (N == 2) {
-    const double ip = frcp(Q.phi[0] * Q.phi[1]);
-    const double im = frcp(m[0] * m[1]);
+    const double pp = Q.phi[0] * Q.phi[1];
+    const double q = frcp(pp * r);
+    ir = q * pp;
+    const double ip = q * r;
     Q.rho[0] = m[0] * (Q.phi[1] * ip);
     Q.rho[1] = m[1] * (Q.phi[0] * ip);
-    Q.irho[0] = Q.phi[0] * (m[1] * im);
-    Q.irho[1] = Q.phi[1] * (m[0] * im);
   } else {
+    ir = frcp(r);
 #pragma unroll
-    for (int l = 0; l < N; ++l) {
-      Q.rho[l] = m[l] / Q.phi[l];
-      Q.irho[l] = Q.phi[l] / m[l];
-    }
+    for (int l = 0; l < N; ++l) Q.rho[l] = m[l] * frcp(Q.phi[l]);
   }
 }
 
 template <int N>
 __device__ __forceinline__ void phases_from_prim(const double* phi_st, const double* rho, Phases<N>& Q) {
-  double sphi = 0.0;
-#pragma unroll
-  for (int l = 0; l < N - 1; ++l) {
-    Q.phi[l] = phi_st[l];
-    sphi += Q.phi[l];
-  }
-  Q.phi[N - 1] = 1.0 - sphi;
+  phase_fractions<N>(phi_st, Q);
 #pragma unroll
   for (int l = 0; l < N; ++l) Q.rho[l] = rho[l];
-  if (N == 2) {
-    const double ir = frcp(rho[0] * rho[1]);
-    Q.irho[0] = rho[1] * ir;
-    Q.irho[1] = rho[0] * ir;
-  } else {
-#pragma unroll
-    for (int l = 0; l < N; ++l) Q.irho[l] = 1.0 / rho[l];
-  }
 }
 
 // ------------------------------------------------------ mixture state
-// reference curves of one reactive component at its own density: p_ref,
-// e_ref and their density derivatives
-struct RxRef {
-  double p, e, dp, de;
+// The reactive mixture's components at equal pressure and temperature: their
+// volume shares s and s1 = 1 - s of the mixture, their reference curves, and
+// what the density dependence of a JWL curve adds to rho c^2 per unit share
+// (ka, kb: Gamma^-1 rho dp_ref/drho - (the JWL part of p_ref)).
+struct Split {
+  double s, s1;
+  double pa, pb, ea, eb, ka, kb;
 };
 
+// The mixture of all materials at one state.  w_l = phi_l / Gamma_l; n0, d0:
+// the sums of phi_l (p_ref / Gamma - rho e_ref) and of w_l over the
+// non-reactive materials, so that rho e + n = p xi with the reactive terms
+// added to both.
 template <int N, int RX>
 struct Thermo {
-  EosV e[N];
+  Curve c[N];
+  double w[N];
+  double n0, d0;
   double xi, ixi;  // sum phi_l / Gamma_l (reactive: effective) and its inverse
   double rho, irho;
   double p, rhoe;
-  double Gmix, c2, cL2;
-  double rho_a, rho_b;
-  RxRef A, B;  // reactive components at rho_a, rho_b
+  double Gmix, rc2, c2, cL2;  // rc2 = rho c^2
+  Split sp;
 };
 
 // Reference curves of reactive component C (0 reactant, 1 product) at
 // density 1/irho: the constant part (a gas's p_ref and e_ref, the product's
 // e_ref lowered by Q) plus, for a JWL component (Sec. 2.3),
 // A exp(-R1 rho0/rho) + B exp(-R2 rho0/rho) and its energy
-// A/(R1 rho0) exp(-R1 rho0/rho) + B/(R2 rho0) exp(-R2 rho0/rho), whose
-// density derivative is p_ref/rho^2.
+// A/(R1 rho0) exp(-R1 rho0/rho) + B/(R2 rho0) exp(-R2 rho0/rho).  j is the JWL
+// part of p_ref and q = R1 rho0 A exp() + R2 rho0 B exp() its slope:
+// dp_ref/drho = q / rho^2, de_ref/drho = j / rho^2.
+struct RxRef {
+  double p, e, j, q;
+};
+
 template <int C>
 __device__ __forceinline__ RxRef rx_ref(const RxP& r, double irho) {
   RxRef o;
   o.p = C ? r.pb : r.pa;
   o.e = C ? r.eb : r.ea;
-  o.dp = 0.0;
-  o.de = 0.0;
+  o.j = 0.0;
+  o.q = 0.0;
   if (r.jwl[C]) {
     const double xa = exp(-r.jR1[C] * irho), xb = exp(-r.jR2[C] * irho);
     const double pa = r.jA[C] * xa, pb = r.jB[C] * xb;
-    const double i2 = irho * irho;
-    o.p = (pa + pb) + o.p;
+    o.j = pa + pb;
+    o.p = o.j + o.p;
     o.e = (pa * r.jiR1[C] + pb * r.jiR2[C]) + o.e;
-    o.dp = (r.jR1[C] * pa + r.jR2[C] * pb) * i2;
-    o.de = (pa + pb) * i2;
+    o.q = r.jR1[C] * pa + r.jR2[C] * pb;
   }
   return o;
 }
 
-__device__ __forceinline__ RxRef rx_const(double p, double e) {
-  RxRef o;
-  o.p = p;
-  o.e = e;
-  o.dp = 0.0;
-  o.de = 0.0;
+// the split of two components at densities 1/ira and 1/irb
+__device__ __forceinline__ Split rx_split_of(const RxP& r, double s, double s1, double ira, double irb,
+                                             const RxRef& A, const RxRef& B) {
+  Split o;
+  o.s = s;
+  o.s1 = s1;
+  o.pa = A.p;
+  o.pb = B.p;
+  o.ea = A.e;
+  o.eb = B.e;
+  o.ka = A.q * r.invGa * ira - A.j;
+  o.kb = B.q * r.invGb * irb - B.j;
   return o;
 }
 
-// Both components at the mixture's own density (a pure cell: no split).  A
-// component whose weight is exactly zero keeps its constant part only: its
-// terms vanish either way.
-__device__ __forceinline__ void rx_pure(const RxP& r, double lam, double ry, double& ra, double& rb, RxRef& A,
-                                        RxRef& B) {
-  ra = ry;
-  rb = ry;
-  const double iry = 1.0 / ry;
-  A = (lam > 0.0) ? rx_ref<0>(r, iry) : rx_const(r.pa, r.ea);
-  B = (lam < 1.0) ? rx_ref<1>(r, iry) : rx_const(r.pb, r.eb);
+// two components with constant curves
+__device__ __forceinline__ Split rx_gas(const RxP& r, double s, double s1) {
+  Split o;
+  o.s = s;
+  o.s1 = s1;
+  o.pa = r.pa;
+  o.pb = r.pb;
+  o.ea = r.ea;
+  o.eb = r.eb;
+  o.ka = o.kb = 0.0;
+  return o;
+}
+
+// Both components at the mixture's own density (a pure cell: no split; the
+// shares are lam and 1 - lam).  A component whose weight is exactly zero keeps
+// its constant part only: its terms vanish either way.
+__device__ __forceinline__ Split rx_pure(const RxP& r, double lam, double ry) {
+  const double iry = frcp(ry);
+  RxRef A, B;
+  A.p = r.pa;
+  A.e = r.ea;
+  B.p = r.pb;
+  B.e = r.eb;
+  A.j = A.q = B.j = B.q = 0.0;
+  if (lam > 0.0) A = rx_ref<0>(r, iry);
+  if (lam < 1.0) B = rx_ref<1>(r, iry);
+  return rx_split_of(r, lam, 1.0 - lam, iry, iry, A, B);
 }
 
 // Appendix B with density-dependent reference curves: a root in (0, 1) of
@@ -447,40 +560,45 @@ __device__ __forceinline__ void rx_pure(const RxP& r, double lam, double ry, dou
 constexpr int RX_SUBSTEPS = 8;
 
 template <bool KNOWN_P>
-__device__ __forceinline__ void rx_newton(const RxP& r, double lam, double py, double ry, double p, double num0,
-                                          double den0, double& ra, double& rb, RxRef& A, RxRef& B) {
-  const double ka = 1.0 / (lam * r.Ga * r.cva), kb = 1.0 / ((1.0 - lam) * r.Gb * r.cvb);
+__device__ __forceinline__ Split rx_newton(const RxP& r, double lam, double py, double ry, double p, double num0,
+                                           double den0) {
   const double l1 = 1.0 - lam;
+  const double iry = frcp(ry), ila = frcp(lam), il1 = frcp(l1);
+  const double ka = ila * r.iGca, kb = il1 * r.iGcb;
   const double la = lam * ry, lb = l1 * ry;
-  const double iry = 1.0 / ry;
+  // d p_ref / ds of a component is its slope q times a constant: ds/s at
+  // fixed masses is -drho/rho
+  const double da = -(iry * ila), db = iry * il1;
   double g = 0.0, dg = 1.0;
+  double s = lam, s1 = l1, ira = iry, irb = iry;
+  RxRef A, B;
   // 0 the probe ladder, 3 steps across the first bracket, 1 Newton steps in
   // the sub-bracket, 2 a final midpoint
   int mode = 0;
   auto eval = [&](double t) {
     const double t1 = 1.0 - t;
-    const double D = lam * t1 + l1 * t;
-    const double iD = 1.0 / D;
-    ra = ry * D / t1;
-    rb = ry * D / t;
-    const double s = lam * t1 * iD, s1 = l1 * t * iD;
-    A = rx_ref<0>(r, t1 * iD * iry);
-    B = rx_ref<1>(r, t * iD * iry);
-    double pp = p, den = 1.0;
+    const double iD = frcp(lam * t1 + l1 * t);
+    const double ta = t1 * iD, tb = t * iD;
+    s = lam * ta;
+    s1 = l1 * tb;
+    ira = ta * iry;
+    irb = tb * iry;
+    A = rx_ref<0>(r, ira);
+    B = rx_ref<1>(r, irb);
+    double pp = p, iden = 1.0;
     if (!KNOWN_P) {
       const double num = num0 + py * (s * A.p * r.invGa - la * A.e) + py * (s1 * B.p * r.invGb - lb * B.e);
-      den = den0 + py * (s * r.invGa + s1 * r.invGb);
-      pp = num / den;
+      iden = frcp(den0 + py * (s * r.invGa + s1 * r.invGb));
+      pp = num * iden;
     }
     g = kb * (pp - B.p) * s1 - ka * (pp - A.p) * s;
     if (mode == 1) {  // the slope, for Newton steps only: dg/dt = lam (1-lam) / D^2 df/ds
-      const double is = 1.0 / s, is1 = 1.0 / s1;
-      const double dA = -A.dp * ra * is, dB = B.dp * rb * is1;  // d p_ref / ds
+      const double dA = A.q * da, dB = B.q * db;
       double dp = 0.0;
       if (!KNOWN_P) {
-        const double dnum = py * ((A.p + s * dA) * r.invGa + la * A.de * ra * is +
-                                  (s1 * dB - B.p) * r.invGb - lb * B.de * rb * is1);
-        dp = (dnum - pp * py * (r.invGa - r.invGb)) / den;
+        const double dnum =
+            py * ((A.p + s * dA) * r.invGa + A.j + (s1 * dB - B.p) * r.invGb - B.j);
+        dp = (dnum - pp * py * (r.invGa - r.invGb)) * iden;
       }
       const double df = ka * ((dp - dA) * s + (pp - A.p)) - kb * ((dp - dB) * s1 - (pp - B.p));
       dg = df * (lam * l1) * (iD * iD);
@@ -516,10 +634,7 @@ __device__ __forceinline__ void rx_newton(const RxP& r, double lam, double py, d
       } else {
         base = t;
         tn = up ? 0.5 * (t + 1.0) : 0.5 * t;
-        if (up && !(tn < 1.0)) {  // g < 0 at every probe below 1: the pure state
-          rx_pure(r, lam, ry, ra, rb, A, B);
-          return;
-        }
+        if (up && !(tn < 1.0)) return rx_pure(r, lam, ry);  // g < 0 at every probe below 1: the pure state
         if (probes == 64) {  // g >= 0 at every probe down to 2^-64
           mode = 2;
           tn = 0.5 * t;
@@ -554,6 +669,7 @@ __device__ __forceinline__ void rx_newton(const RxP& r, double lam, double py, d
     }
     t = tn;
   }
+  return rx_split_of(r, s, s1, ira, irb, A, B);
 }
 
 // The split's root rule for two gas components (Appendix B, with the reading
@@ -605,29 +721,14 @@ __device__ __forceinline__ bool rx_pick(const double* sr, int nr, bool up, doubl
   return true;
 }
 
-// component densities of the split t (pure outside (0, 1)): with D = lam
-// (1 - t) + (1 - lam) t, rho_a = rho_y D / (1 - t), rho_b = rho_y D / t
-__device__ __forceinline__ void rx_densities(double lam, double ry, double t, double& ra, double& rb) {
-  if (!(t > 0.0 && t < 1.0)) {
-    ra = ry;
-    rb = ry;
-    return;
-  }
-  const double D = lam * (1.0 - t) + (1.0 - lam) * t;
-  ra = ry * D / (1.0 - t);
-  rb = ry * D / t;
-}
-
-// the densities of a picked share s (lam rho_y / s, (1 - lam) rho_y / (1 - s))
-// or of the end value
-__device__ __forceinline__ void rx_from_pick(bool picked, double s, double t_end, double lam, double ry, double& ra,
-                                             double& rb) {
-  if (picked) {
-    ra = lam * ry * frcp(s);
-    rb = (1.0 - lam) * ry * frcp(1.0 - s);
-  } else {
-    rx_densities(lam, ry, t_end, ra, rb);
-  }
+// the shares of a picked s, or of the end value t_end (pure at 1): s = lam
+// (1 - t) / D, 1 - s = (1 - lam) t / D, D = lam (1 - t) + (1 - lam) t
+__device__ __forceinline__ Split rx_from_pick(const RxP& r, bool picked, double s, double t_end, double lam) {
+  if (picked) return rx_gas(r, s, 1.0 - s);
+  if (!(t_end < 1.0)) return rx_gas(r, lam, 1.0 - lam);
+  const double a = lam * (1.0 - t_end), b = (1.0 - lam) * t_end;
+  const double iD = frcp(a + b);
+  return rx_gas(r, a * iD, b * iD);
 }
 
 // Reactive split from a known pressure (Appendix B, primitive branch).  For
@@ -635,38 +736,24 @@ __device__ __forceinline__ void rx_from_pick(bool picked, double s, double t_end
 // beta) t - alpha, alpha = (p - p_a)/(Gamma_a C_V,a), beta = (p - p_b)/(Gamma_b
 // C_V,b).
 template <bool GEN>
-__device__ __forceinline__ void rx_split_p(const RxP& r, double lam, double rho_y, double p, double& ra,
-                                           double& rb, RxRef& A, RxRef& B) {
-  if constexpr (GEN) {
-    if (lam >= 1.0 - 1e-12 || lam <= 1e-12)
-      rx_pure(r, lam, rho_y, ra, rb, A, B);
-    else
-      rx_newton<true>(r, lam, 0.0, rho_y, p, 0.0, 0.0, ra, rb, A, B);
-    return;
-  }
-  A = rx_const(r.pa, r.ea);
-  B = rx_const(r.pb, r.eb);
-  if (lam >= 1.0 - 1e-12 || lam <= 1e-12) {
-    ra = rho_y;
-    rb = rho_y;
-    return;
-  }
+__device__ __forceinline__ Split rx_split_p(const RxP& r, double lam, double rho_y, double p) {
+  const bool pure = lam >= 1.0 - 1e-12 || lam <= 1e-12;
+  if constexpr (GEN) return pure ? rx_pure(r, lam, rho_y) : rx_newton<true>(r, lam, 0.0, rho_y, p, 0.0, 0.0);
+  if (pure) return rx_gas(r, lam, 1.0 - lam);
   // in t the residual is linear, (alpha + beta) t - alpha with alpha = (p -
   // p_a)/(Gamma_a C_V,a), beta = (p - p_b)/(Gamma_b C_V,b): g(1/2) < 0 where
   // beta < alpha, and the root t = alpha/(alpha + beta) lies in (0, 1) on
   // that side exactly where alpha > 0 and beta > 0 (else the ladder runs to
-  // its end); the root itself from the share s = kb/(ka + kb), ka = alpha/lam,
-  // kb = beta/(1 - lam)
-  const double alpha = (p - r.pa) * frcp(r.Ga * r.cva), beta = (p - r.pb) * frcp(r.Gb * r.cvb);
+  // its end); the share of the root is s = lam beta / (lam beta + (1 - lam)
+  // alpha)
+  const double alpha = (p - r.pa) * r.iGca, beta = (p - r.pb) * r.iGcb;
   const bool up = beta < alpha;
   const bool found = alpha > 0.0 && beta > 0.0 &&
                      (up ? beta >= 0x1p-53 * (alpha + beta) : alpha >= 0x1p-64 * (alpha + beta));
-  if (found) {
-    const double ka = alpha * frcp(lam), kb = beta * frcp(1.0 - lam);
-    rx_from_pick(true, kb * frcp(ka + kb), 1.0, lam, rho_y, ra, rb);
-  } else {
-    rx_densities(lam, rho_y, up ? 1.0 : 0x1p-65, ra, rb);
-  }
+  const double a = found ? lam * beta : lam * (up ? 1.0 : 1.0 - 0x1p-65);
+  const double b = found ? (1.0 - lam) * alpha : (1.0 - lam) * (up ? 1.0 : 0x1p-65);
+  const double iD = frcp(a + b);
+  return rx_gas(r, a * iD, b * iD);
 }
 
 // Reactive split from the conserved energy (Appendix B, conservative
@@ -675,15 +762,11 @@ __device__ __forceinline__ void rx_split_p(const RxP& r, double lam, double rho_
 // curves, temperature equality is Q(s) = Q2 s^2 + Q1 s + Q0 = 0, with g < 0
 // where Q > 0; its roots (stable formula, one Newton polish each) go to the
 // rule.
-__device__ __forceinline__ void rx_solve_gas(const RxP& r, double lam, double ry, double A0, double A1, double B0,
-                                             double B1, double& ra, double& rb) {
-  if (lam >= 1.0 - 1e-12 || lam <= 1e-12) {
-    ra = ry;
-    rb = ry;
-    return;
-  }
-  const double ka = frcp(lam * r.Ga * r.cva);
-  const double kb = frcp((1.0 - lam) * r.Gb * r.cvb);
+__device__ __forceinline__ Split rx_solve_gas(const RxP& r, double lam, double A0, double A1, double B0, double B1) {
+  if (lam >= 1.0 - 1e-12 || lam <= 1e-12) return rx_gas(r, lam, 1.0 - lam);
+  // (both weights times lam (1 - lam))
+  const double ka = (1.0 - lam) * r.iGca;
+  const double kb = lam * r.iGcb;
   const double a0 = A0 - r.pa * B0, a1 = A1 - r.pa * B1;
   const double b0 = A0 - r.pb * B0, b1 = A1 - r.pb * B1;
   const double Q2 = ka * a1 + kb * b1;
@@ -692,14 +775,14 @@ __device__ __forceinline__ void rx_solve_gas(const RxP& r, double lam, double ry
   double sr[2];
   int nr = 0;
   if (Q2 == 0.0) {
-    if (Q1 != 0.0) sr[nr++] = -Q0 / Q1;
+    if (Q1 != 0.0) sr[nr++] = -Q0 * frcp(Q1);
   } else {
     const double disc = Q1 * Q1 - 4.0 * Q2 * Q0;
     if (disc >= 0.0) {
-      const double q = -0.5 * (Q1 + copysign(sqrt(disc), Q1));
+      const double q = -0.5 * (Q1 + copysign(fsqrt(disc), Q1));
       if (q != 0.0) {
-        sr[nr++] = Q0 / q;
-        sr[nr++] = q / Q2;
+        sr[nr++] = Q0 * frcp(q);
+        sr[nr++] = q * frcp(Q2);
       } else {
         sr[nr++] = 0.0;
       }
@@ -712,114 +795,101 @@ __device__ __forceinline__ void rx_solve_gas(const RxP& r, double lam, double ry
     const double qv = (Q2 * sp + Q1) * sp + Q0, dq = 2.0 * Q2 * sp + Q1;
     if (dq != 0.0) sp = sp - qv * frcp(dq);  // one Newton polish of the root taken
   }
-  rx_from_pick(picked, sp, t_end, lam, ry, ra, rb);
+  return rx_from_pick(r, picked, sp, t_end, lam);
+}
+
+// the mixture's own 1/Gamma and p_ref/Gamma - rho e_ref per unit of its volume
+__device__ __forceinline__ double rx_xi(const RxP& r, const Split& o) { return o.s * r.invGa + o.s1 * r.invGb; }
+__device__ __forceinline__ double rx_num(const RxP& r, const Split& o, double lam, double ry) {
+  return (o.s * (o.pa * r.invGa) + o.s1 * (o.pb * r.invGb)) - ry * (lam * o.ea + (1.0 - lam) * o.eb);
 }
 
 // The reactive part of the pressure function (Appendix B, conservative
 // branch) for a cell whose non-reactive part is (num0, den0): solves the
 // split and leaves the full numerator and denominator (xi) of p.
 template <bool GEN>
-__device__ __forceinline__ void rx_cons(const RxP& r, double py, double ry, double lam, double num0, double den0,
-                                        double& ra, double& rb, RxRef& A, RxRef& B, double& num, double& den) {
+__device__ __forceinline__ Split rx_cons(const RxP& r, double py, double ry, double lam, double num0, double den0,
+                                         double& num, double& den) {
+  Split o;
   if constexpr (GEN) {
     if (lam >= 1.0 - 1e-12 || lam <= 1e-12)
-      rx_pure(r, lam, ry, ra, rb, A, B);
+      o = rx_pure(r, lam, ry);
     else
-      rx_newton<false>(r, lam, py, ry, 0.0, num0, den0, ra, rb, A, B);
+      o = rx_newton<false>(r, lam, py, ry, 0.0, num0, den0);
   } else {
-    A = rx_const(r.pa, r.ea);
-    B = rx_const(r.pb, r.eb);
     const double A0 = num0 + py * (r.pb * r.invGb - ry * (lam * r.ea + (1.0 - lam) * r.eb));
     const double A1 = py * (r.pa * r.invGa - r.pb * r.invGb);
     const double B0 = den0 + py * r.invGb;
     const double B1 = py * (r.invGa - r.invGb);
-    rx_solve_gas(r, lam, ry, A0, A1, B0, B1, ra, rb);
+    o = rx_solve_gas(r, lam, A0, A1, B0, B1);
   }
-  const double wa = py * ry * lam, wb = py * ry * (1.0 - lam);
-  // the components' volume fractions in the cell, wa / ra and wb / rb
-  const double va = wa * frcp(ra), vb = wb * frcp(rb);
-  den = den0 + va * r.invGa + vb * r.invGb;
-  num = num0 + (va * (A.p * r.invGa) - wa * A.e) + (vb * (B.p * r.invGb) - wb * B.e);
+  den = den0 + py * rx_xi(r, o);
+  num = num0 + py * rx_num(r, o, lam, ry);
+  return o;
 }
 
+// closures of the non-reactive materials and their sums w, n0, d0
 template <int N, int RX>
-__device__ __forceinline__ void eos_all(const Params& P, const Phases<N>& Q, double J2, Thermo<N, RX>& T) {
+__device__ __forceinline__ void curves_all(const Params& P, const Phases<N>& Q, double J2, Thermo<N, RX>& T) {
+  T.n0 = 0.0;
+  T.d0 = 0.0;
 #pragma unroll
   for (int l = 0; l < N; ++l) {
+    T.w[l] = 0.0;
     if (rx_mix<RX>(P) && l == P.rx.mat) continue;
-    T.e[l] = eos_eval(P.mat[l], Q.rho[l], Q.irho[l], J2);
+    T.c[l] = curve_eval(P.mat[l], Q.rho[l], J2);
+    T.w[l] = Q.phi[l] * P.mat[l].invGam;
+    T.d0 += T.w[l];
+    T.n0 += T.w[l] * T.c[l].pref - Q.phi[l] * T.c[l].re;
   }
 }
 
-// pressure from the conserved energy (Appendix B pressure function; without
-// the reactive terms when RX is false).  Leaves xi and 1/xi in T.
+// pressure from the conserved energy T.rhoe (Appendix B pressure function;
+// without the reactive terms when RX is false).  Leaves xi and 1/xi in T.
 template <int N, int RX>
 __device__ __forceinline__ void pressure_from_rhoe(const Params& P, const Phases<N>& Q, double lam,
                                                    Thermo<N, RX>& T) {
-  double den = 0.0, num = T.rhoe;
-#pragma unroll
-  for (int l = 0; l < N; ++l) {
-    if (rx_mix<RX>(P) && l == P.rx.mat) continue;
-    den += Q.phi[l] * T.e[l].invGam;
-    num += Q.phi[l] * (T.e[l].pref * T.e[l].invGam - Q.rho[l] * T.e[l].eref);
-  }
+  double den = T.d0, num = T.rhoe + T.n0;
   if (rx_mix<RX>(P)) {
     const int y = P.rx.mat;
-    const double num0 = num, den0 = den;
-    rx_cons<RX == 2>(P.rx, pick<N>(Q.phi, y), pick<N>(Q.rho, y), lam, num0, den0, T.rho_a, T.rho_b, T.A, T.B, num, den);
+    T.sp = rx_cons<RX == 2>(P.rx, pick<N>(Q.phi, y), pick<N>(Q.rho, y), lam, T.rhoe + T.n0, T.d0, num, den);
   }
   T.xi = den;
   T.ixi = frcp(den);
   T.p = num * T.ixi;
 }
 
-// mixture modulus and sound speeds (Allaire form of the mixture rule; c_L^2 =
-// c^2 + 4G/(3 rho)) once p, the split and (optionally) 1/xi are known
+// rho c^2 and the mixture's shear modulus, both times xi: sum of w_l rho_l
+// c_l^2 = p (1 + xi) + sum w_l rc_l since w_l Gamma_l = phi_l and the
+// fractions sum to 1 (Allaire form of the mixture rule)
 template <int N, int RX>
-__device__ __forceinline__ void finish(const Params& P, const Phases<N>& Q, double lam, Thermo<N, RX>& T,
-                                       bool have_xi, bool have_rho = false) {
-  if (!have_rho) {
-    double r = 0.0;
-#pragma unroll
-    for (int l = 0; l < N; ++l) r += Q.phi[l] * Q.rho[l];
-    T.rho = r;
-    T.irho = frcp(r);
-  }
-  double xi = 0.0, gnum = 0.0, cnum = 0.0;
+__device__ __forceinline__ void sound_sums(const Params& P, const Phases<N>& Q, const Thermo<N, RX>& T, double& cnum,
+                                           double& gnum) {
+  cnum = fma(T.p, T.xi, T.p);
+  gnum = 0.0;
 #pragma unroll
   for (int l = 0; l < N; ++l) {
-    double cl2, gl;
     if (rx_mix<RX>(P) && l == P.rx.mat) {
-      const RxP& q = P.rx;
-      const double ry = Q.rho[l], ra = T.rho_a, rb = T.rho_b, p = T.p;
-      const double ira = frcp(ra), irb = frcp(rb);
-      gl = (lam * ry * ira) * q.invGa + ((1.0 - lam) * ry * irb) * q.invGb;
-      const double dEdp = lam * q.invGa * ira + (1.0 - lam) * q.invGb * irb;
-      // component energy derivatives at fixed pressure, the JWL curves'
-      // own slopes included
-      const double pa = (RX == 2) ? T.A.p : q.pa, pb = (RX == 2) ? T.B.p : q.pb;
-      double dEa = -(p - pa) * q.invGa * (ira * ira);
-      double dEb = -(p - pb) * q.invGb * (irb * irb);
-      if constexpr (RX == 2) {
-        dEa = dEa - T.A.dp * q.invGa * ira + T.A.de;
-        dEb = dEb - T.B.dp * q.invGb * irb + T.B.de;
-      }
-      const double dEdr = (lam * dEa * ra + (1.0 - lam) * dEb * rb) * Q.irho[l];
-      cl2 = (p * (Q.irho[l] * Q.irho[l]) - dEdr) * frcp(dEdp);
+      const Split& o = T.sp;
+      double rc = -(o.s * (o.pa * P.rx.invGa) + o.s1 * (o.pb * P.rx.invGb));
+      if constexpr (RX == 2) rc += o.s * o.ka + o.s1 * o.kb;
+      cnum += Q.phi[l] * rc;
     } else {
-      gl = T.e[l].invGam;
-      cl2 = c2_mat(T.e[l], Q.rho[l], Q.irho[l], T.p);
-      gnum += Q.phi[l] * T.e[l].G * gl;
+      cnum += T.w[l] * T.c[l].rc;
+      gnum += T.w[l] * T.c[l].G;
     }
-    xi += Q.phi[l] * gl;
-    cnum += (Q.phi[l] * Q.rho[l] * T.irho) * cl2 * gl;
   }
-  if (!have_xi) {
-    T.xi = xi;
-    T.ixi = frcp(xi);
-  }
+}
+
+// sound speeds (c_L^2 = c^2 + 4G/(3 rho)) and shear modulus once p, the split,
+// 1/xi and 1/rho are known
+template <int N, int RX>
+__device__ __forceinline__ void finish(const Params& P, const Phases<N>& Q, Thermo<N, RX>& T) {
+  double cnum, gnum;
+  sound_sums<N, RX>(P, Q, T, cnum, gnum);
   T.Gmix = gnum * T.ixi;
-  T.c2 = cnum * T.ixi;
+  T.rc2 = cnum * T.ixi;
+  T.c2 = T.rc2 * T.irho;
   T.cL2 = T.c2 + (4.0 / 3.0) * T.Gmix * T.irho;
 }
 
@@ -831,13 +901,7 @@ __device__ __forceinline__ void cons_to_prim(const Params& P, const double* U, d
                                              double H[6], double& J2) {
   using L = Lay<D, N, RX>;
   Phases<N> Q;
-  phases_from_partial<N>(U, U + L::M0, Q);
-  double r = 0.0;
-#pragma unroll
-  for (int l = 0; l < N; ++l) r += U[L::M0 + l];
-  const double inv_r = frcp(r);
-  T.rho = r;
-  T.irho = inv_r;
+  phases_from_partial<N>(U, U + L::M0, Q, T.rho, T.irho);
   double lam = 0.0, hist = 0.0;
   if (RX) {
     const double my = pick<N>(U + L::M0, P.rx.mat);
@@ -850,14 +914,14 @@ __device__ __forceinline__ void cons_to_prim(const Params& P, const double* U, d
   double uu = 0.0;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
-    W[L::MOM0 + k] = U[L::MOM0 + k] * inv_r;
+    W[L::MOM0 + k] = U[L::MOM0 + k] * T.irho;
     uu += W[L::MOM0 + k] * W[L::MOM0 + k];
   }
   strain<D, N, RX>(U + L::V0, H, J2);
-  eos_all<N, RX>(P, Q, J2, T);
-  T.rhoe = U[L::E] - 0.5 * r * uu;
+  curves_all<N, RX>(P, Q, J2, T);
+  T.rhoe = U[L::E] - 0.5 * T.rho * uu;
   pressure_from_rhoe<N, RX>(P, Q, lam, T);
-  if (FIN) finish<N, RX>(P, Q, lam, T, true, true);
+  if (FIN) finish<N, RX>(P, Q, T);
 #pragma unroll
   for (int l = 0; l < N - 1; ++l) W[l] = Q.phi[l];
 #pragma unroll
@@ -868,42 +932,33 @@ __device__ __forceinline__ void cons_to_prim(const Params& P, const double* U, d
   for (int q = 0; q < L::NV; ++q) W[L::V0 + q] = U[L::V0 + q];
 }
 
-// primitive -> thermodynamic state (energy from p)
+// primitive -> mixture state (energy from p): the closures, the split, xi,
+// rho and rho e; H holds 4 H
 template <int D, int N, int RX>
-__device__ __forceinline__ void prim_thermo(const Params& P, const double* W, Thermo<N, RX>& T, double H[6],
-                                            double& J2, bool need_energy) {
+__device__ __forceinline__ void prim_mix(const Params& P, const double* W, Phases<N>& Q, Thermo<N, RX>& T,
+                                         double H[6], double& J2) {
   using L = Lay<D, N, RX>;
-  Phases<N> Q;
   phases_from_prim<N>(W, W + L::M0, Q);
-  double lam = 0.0;
-  if (RX) lam = fmin(fmax(W[L::LAM], 0.0), 1.0);
-  strain<D, N, RX>(W + L::V0, H, J2);
-  eos_all<N, RX>(P, Q, J2, T);
+  strain4<D, N, RX>(W + L::V0, H, J2);
+  curves_all<N, RX>(P, Q, J2, T);
   T.p = W[L::E];
-  if (rx_mix<RX>(P)) rx_split_p<RX == 2>(P.rx, lam, pick<N>(Q.rho, P.rx.mat), T.p, T.rho_a, T.rho_b, T.A, T.B);
-  if (need_energy) {
-    double e = 0.0;
-#pragma unroll
-    for (int l = 0; l < N; ++l) {
-      if (rx_mix<RX>(P) && l == P.rx.mat) continue;
-      e += Q.phi[l] * ((T.p - T.e[l].pref) * T.e[l].invGam + Q.rho[l] * T.e[l].eref);
-    }
-    if (rx_mix<RX>(P)) {
-      const RxP& r = P.rx;
-      const int y = r.mat;
-      const double py = pick<N>(Q.phi, y), ry = pick<N>(Q.rho, y);
-      const double wa = py * ry * lam, wb = py * ry * (1.0 - lam);
-      if constexpr (RX == 2)
-        e += wa * ((T.p - T.A.p) * r.invGa / T.rho_a + T.A.e) + wb * ((T.p - T.B.p) * r.invGb / T.rho_b + T.B.e);
-      else
-        e += wa * ((T.p - r.pa) * r.invGa / T.rho_a + r.ea) + wb * ((T.p - r.pb) * r.invGb / T.rho_b + r.eb);
-    }
-    T.rhoe = e;
+  T.xi = T.d0;
+  double n = T.n0;
+  if (rx_mix<RX>(P)) {
+    const int y = P.rx.mat;
+    const double lam = fmin(fmax(W[L::LAM], 0.0), 1.0);
+    const double py = pick<N>(Q.phi, y), ry = pick<N>(Q.rho, y);
+    T.sp = rx_split_p<RX == 2>(P.rx, lam, ry, T.p);
+    T.xi = T.d0 + py * rx_xi(P.rx, T.sp);
+    n += py * rx_num(P.rx, T.sp, lam, ry);
   }
-  finish<N, RX>(P, Q, lam, T, false);
+  T.rhoe = fma(T.p, T.xi, -n);
+  T.rho = 0.0;
+#pragma unroll
+  for (int l = 0; l < N; ++l) T.rho += Q.phi[l] * Q.rho[l];
 }
 
-// Mixture shear modulus G = sum(phi_l G_l / Gamma_l) / xi and strain of a
+// Mixture shear modulus G = sum(phi_l G_l / Gamma_l) / xi and 4 H of a
 // primitive state: all the stress needs besides p
 template <int D, int N, int RX>
 __device__ __forceinline__ double prim_shear(const Params& P, const double* W, double H[6]) {
@@ -920,32 +975,30 @@ __device__ __forceinline__ double prim_shear(const Params& P, const double* W, d
 #pragma unroll
   for (int l = 0; l < N; ++l) {
     if (rx_mix<RX>(P) && l == P.rx.mat) {
-      const RxP& q = P.rx;
       const double lam = fmin(fmax(W[L::LAM], 0.0), 1.0);
-      const double ry = W[L::M0 + l];
-      double ra, rb;
-      RxRef A, B;
-      rx_split_p<RX == 2>(q, lam, ry, W[L::E], ra, rb, A, B);
-      xi += phi[l] * ((lam * ry / ra) * q.invGa + ((1.0 - lam) * ry / rb) * q.invGb);
+      const Split o = rx_split_p<RX == 2>(P.rx, lam, W[L::M0 + l], W[L::E]);
+      xi += phi[l] * rx_xi(P.rx, o);
     } else {
-      const double gl = P.mat[l].invGam;
-      xi += phi[l] * gl;
-      gnum += phi[l] * shear_modulus(P.mat[l], W[L::M0 + l]) * gl;
+      const double wl = phi[l] * P.mat[l].invGam;
+      xi += wl;
+      gnum += wl * shear_modulus(P.mat[l], W[L::M0 + l]);
     }
   }
   double J2;
-  strain<D, N, RX>(W + L::V0, H, J2);
+  strain4<D, N, RX>(W + L::V0, H, J2);
   return gnum * frcp(xi);
 }
 
 // ------------------------------------------------ reconstruction pieces
+// 0 for differences of opposite sign, else the smaller one: of the two terms
+// one is 0 (five instructions, where the comparisons and selects of the
+// definition take seven)
 __device__ __forceinline__ double minmod(double a, double b) {
-  if (a * b <= 0.0) return 0.0;
-  return (fabs(a) < fabs(b)) ? a : b;
+  return fmax(fmin(a, b), 0.0) + fmin(fmax(a, b), 0.0);
 }
 
 __device__ __forceinline__ double vanalbada(double a, double b, double e2) {
-  return (a * (b * b + e2) + b * (a * a + e2)) / (a * a + b * b + 2.0 * e2);
+  return (a * (b * b + e2) + b * (a * a + e2)) * frcp(a * a + b * b + 2.0 * e2);
 }
 
 template <int D, int N, int RX>
@@ -953,30 +1006,6 @@ __device__ __forceinline__ double slope(const Params& P, int f, double wm, doubl
   const double a = w0 - wm, b = wp - w0;
   if (P.limiter == 1) return vanalbada(a, b, P.va_e2[Lay<D, N, RX>::kind(f)]);
   return minmod(a, b);
-}
-
-// THINC edge values (Appendix A), evaluated in the increasing orientation and
-// swapped back for a decreasing stencil
-__device__ __forceinline__ void thinc_edges(double qm, double q0, double qp, double beta, double eps,
-                                            double delta, double mL, double mR, double& tL, double& tR) {
-  const double qmin = fmin(qm, qp);
-  const double qmax = fmax(qm, qp) - qmin;
-  const double C = (q0 - qmin + eps) / (qmax + eps);
-  tL = mL;
-  tR = mR;
-  if (!((delta < C) && (C < 1.0 - delta) && ((qp - q0) * (q0 - qm) > 0.0))) return;
-  const double Bv = exp(beta * (2.0 * C - 1.0));
-  const double tb = tanh(beta);
-  const double A = (Bv / cosh(beta) - 1.0) / tb;
-  const double lo = qmin + 0.5 * qmax * (1.0 + A);
-  const double hi = qmin + 0.5 * qmax * (1.0 + (tb + A) / (1.0 + A * tb));
-  if (qp - qm < 0.0) {
-    tL = hi;
-    tR = lo;
-  } else {
-    tL = lo;
-    tR = hi;
-  }
 }
 
 // Youngs normal |n_d| from a 3x3 (2-D) stencil phi9[a][b] (a along x, b

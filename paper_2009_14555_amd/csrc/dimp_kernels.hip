@@ -9,18 +9,24 @@
 namespace dimp {
 
 // ------------------------------------------------------ pointwise kernels
-template <int D, int N, int RX>
+template <int D, int N, int RX, int PROF>
 __global__ __launch_bounds__(256) void k_prim_to_cons(Params P, const double* __restrict__ W, double* __restrict__ U) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
+  assume_profile<N, RX, PROF>(P);
   const int64_t nc = P.ncell;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += (int64_t)gridDim.x * blockDim.x) {
     double w[F];
 #pragma unroll
     for (int f = 0; f < F; ++f) w[f] = W[f * nc + c];
-    Thermo<N, RX> T;
+    std::conditional_t<PROF == PROF_CALIB, calib::Thermo, Thermo<N, RX>> T;
     double H[6], J2;
-    prim_thermo<D, N, RX>(P, w, T, H, J2, true);
+    if constexpr (PROF == PROF_CALIB) {
+      calib::prim_thermo(P, w, T, H, J2, true);
+    } else {
+      Phases<N> Q;
+      prim_mix<D, N, RX>(P, w, Q, T, H, J2);
+    }
     double phiN = 1.0;
 #pragma unroll
     for (int l = 0; l < N - 1; ++l) {
@@ -52,10 +58,11 @@ __global__ __launch_bounds__(256) void k_prim_to_cons(Params P, const double* __
   }
 }
 
-template <int D, int N, int RX>
+template <int D, int N, int RX, int PROF>
 __global__ __launch_bounds__(256) void k_cons_to_prim(Params P, const double* __restrict__ U, double* __restrict__ W) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
+  assume_profile<N, RX, PROF>(P);
   const int64_t nc = P.ncell;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += (int64_t)gridDim.x * blockDim.x) {
     double u[F], w[F];
@@ -69,11 +76,12 @@ __global__ __launch_bounds__(256) void k_cons_to_prim(Params P, const double* __
   }
 }
 
-template <int D, int N, int RX>
+template <int D, int N, int RX, int PROF>
 __global__ __launch_bounds__(256) void k_sources(Params P, double* __restrict__ U, double dt_arg,
                                                 const double* __restrict__ dtp) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
+  assume_profile<N, RX, PROF>(P);
   const int64_t nc = P.ncell;
   const double dt = dtp ? dtp[0] : dt_arg;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += (int64_t)gridDim.x * blockDim.x) {
@@ -88,11 +96,12 @@ __global__ __launch_bounds__(256) void k_sources(Params P, double* __restrict__ 
   }
 }
 
-template <int D, int N, int RX>
+template <int D, int N, int RX, int PROF>
 __global__ __launch_bounds__(256) void k_wavespeed(Params P, const double* __restrict__ U,
                                                    unsigned long long* __restrict__ smax) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
+  assume_profile<N, RX, PROF>(P);
   const int64_t nc = P.ncell;
   double s[D];
 #pragma unroll
@@ -109,11 +118,12 @@ __global__ __launch_bounds__(256) void k_wavespeed(Params P, const double* __res
   for (int k = 0; k < D; ++k) wave_max_atomic(s[k], smax + k);
 }
 
-template <int D, int N, int RX>
+template <int D, int N, int RX, int PROF>
 __global__ __launch_bounds__(256) void k_check(Params P, const double* __restrict__ U,
                                                unsigned long long* __restrict__ nbad) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
+  assume_profile<N, RX, PROF>(P);
   const int64_t nc = P.ncell;
   unsigned long long bad = 0;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += (int64_t)gridDim.x * blockDim.x) {
@@ -243,6 +253,7 @@ hipError_t launch_sweep(const Params& P, int D, int rx, const double* in, double
                  : launch_sweep_t<DD, 2, 0>(P, in, out, dt, dtp, dir, fuse, part, S, st)
   if (P.nmat == 3) return launch_sweep_n3(P, D, rx, in, out, dt, dtp, dir, fuse, part, S, st);
   if (P.nmat != 2) return hipErrorInvalidValue;
+  if (P.calib) return launch_sweep_p<2, 2, 0, PROF_CALIB>(P, in, out, dt, dtp, dir, fuse, part, S, st);
   if (D == 1) DIMP_SWEEP_RX(1);
   if (D == 2) DIMP_SWEEP_RX(2);
   return launch_sweep3(P, rx, in, out, dt, dtp, dir, fuse, part, S, st);
@@ -293,11 +304,16 @@ int64_t reduce_smax_blocks(int64_t nslots) {
 }
 
 // pointwise kernels: D in 1..3 and two materials, or D in 1..2 and three
+#define DIMP_DISPATCH_RX(DD, NN, RXV, KERNEL, ...)                                         \
+  (void)by_profile<NN, RXV>(P, [&](auto prof) {                                              \
+    hipLaunchKernelGGL((KERNEL<DD, NN, RXV, decltype(prof)::value>), __VA_ARGS__);            \
+    return hipSuccess;                                                                       \
+  })
 #define DIMP_DISPATCH_D(DD, NN, RX, KERNEL, ...)                                          \
   do {                                                                                      \
-    if (RX == 2) hipLaunchKernelGGL((KERNEL<DD, NN, 2>), __VA_ARGS__);                      \
-    else if (RX) hipLaunchKernelGGL((KERNEL<DD, NN, 1>), __VA_ARGS__);                      \
-    else hipLaunchKernelGGL((KERNEL<DD, NN, 0>), __VA_ARGS__);                              \
+    if (RX == 2) DIMP_DISPATCH_RX(DD, NN, 2, KERNEL, __VA_ARGS__);                          \
+    else if (RX) DIMP_DISPATCH_RX(DD, NN, 1, KERNEL, __VA_ARGS__);                          \
+    else DIMP_DISPATCH_RX(DD, NN, 0, KERNEL, __VA_ARGS__);                                  \
   } while (0)
 #define DIMP_DISPATCH(D, RX, KERNEL, ...)                                                   \
   do {                                                                                      \
@@ -312,6 +328,10 @@ int64_t reduce_smax_blocks(int64_t nslots) {
 
 hipError_t launch_prim_to_cons(const Params& P, int D, int rx, const double* W, double* U, hipStream_t st) {
   const int grid = grid_for(P.ncell, 256);
+  if (P.calib) {
+    hipLaunchKernelGGL((k_prim_to_cons<2, 2, 0, PROF_CALIB>), dim3(grid), dim3(256), 0, st, P, W, U);
+    return hipGetLastError();
+  }
   DIMP_DISPATCH(D, rx, k_prim_to_cons, dim3(grid), dim3(256), 0, st, P, W, U);
   return hipGetLastError();
 }

@@ -4,49 +4,15 @@
 
 namespace dimp {
 
-// ------------------------------------------------- lane-per-cell sweep
-// The stages of one sweep for a wave whose 64 lanes hold 64 consecutive cells
-// along the sweep axis (3 halo cells on each side, lanes 3..60 are written).
-// U: the lane's conserved state; phi_t[b][c]: phi_1 of the lane's cell at
-// transverse offsets (b, c) in {-1,0,1}^2 (2-D uses c = 1 only), with the
-// offset along the sweep axis supplied by shuffles.
-// U is read twice through load_U (for the primitive state and for the
-// update) rather than kept in registers across the face computation.
-// RK = false: the split MUSCL-Hancock sweep, Un = the updated state (and, with
-// FUSE, the source steps and the wave speed s of the result).  RK = true: the
-// direction's part of the unsplit operator of Sec. 3.1, Un = D_dir(q) with
-// nu = 1/dx (edges without the predictor; FUSE is left to the caller).
-//
-// lane_face: the stages up to the flux through the face on the left of the
-// lane's cell (fa; wall: that face is a reflective wall), and the cell's
-// 1 / (sum of partial densities); it depends on the cells 3 to the left and
-// 2 to the right.  lane_sweep adds the update.
-template <int D, int N, int RX, int DIR, bool RK, class LoadU>
-__device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const double (&phi_t)[3][3], double nu,
-                                          FaceV<D, N, RX>& fa, double& irho0, bool wall) {
-  using L = Lay<D, N, RX>;
-  constexpr int F = L::F;
-  double W[F];
-  double rc2;
-  {
-    double U[F];
-    load_U(U);
-    Thermo<N, RX> T;
-    double H[6], J2;
-    cons_to_prim<D, N, RX>(P, U, W, T, H, J2);
-    irho0 = T.irho;  // 1 / sum of partial densities
-    rc2 = T.rho * T.c2;
-  }
-  double Wm[F], Wp[F];
-#pragma unroll
-  for (int f = 0; f < F; ++f) {
-    Wm[f] = from_left(W[f]);
-    Wp[f] = from_right(W[f]);
-  }
+// THINC candidates of every stored volume fraction of the lane's cell, all
+// with the normal of the first, and the BVD choice on them.
+template <int D, int N, int RX, int DIR>
+__device__ __forceinline__ void lane_bvd(const Params& P, const double* Wm, const double* W, const double* Wp,
+                                         const double (&phi_t)[3][3], double* WL, double* WR, double* jump) {
   // phi stencil along the sweep axis for the interface normal (all lanes
   // shuffle; the normal itself is only evaluated in mixed cells)
   double sm[3][3], sp[3][3];
-  if (P.thinc && D >= 2) {
+  if (D >= 2) {
 #pragma unroll
     for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -91,8 +57,7 @@ __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const
       }
     return youngs3(st, P.dx, DIR);
   };
-  // candidates of every stored volume fraction, all with the normal of the
-  // first; the neighbours' right (left) edge candidates by shifts
+  // the neighbours' right (left) edge candidates by shifts
   CandSet<N> c0, cm, cp;
 #pragma unroll
   for (int l = 0; l < N - 1; ++l) {
@@ -102,13 +67,62 @@ __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const
     cp.c[l].mL = from_right(c0.c[l].mL);
     cp.c[l].tL = from_right(c0.c[l].tL);
   }
-  double WL[F], WR[F];
-  if (RK) {
-    (void)rc2;
-    edges_muscl<D, N, RX>(P, Wm, W, Wp, cm, c0, cp, WL, WR);
-  } else {
-    edges_predict<D, N, RX, DIR>(P, Wm, W, Wp, irho0, rc2, cm, c0, cp, nu, WL, WR);
+  edges_bvd<N>(cm, c0, cp, WL, WR, jump);
+}
+
+// ------------------------------------------------- lane-per-cell sweep
+// The stages of one sweep for a wave whose 64 lanes hold 64 consecutive cells
+// along the sweep axis (3 halo cells on each side, lanes 3..60 are written).
+// U: the lane's conserved state; phi_t[b][c]: phi_1 of the lane's cell at
+// transverse offsets (b, c) in {-1,0,1}^2 (2-D uses c = 1 only), with the
+// offset along the sweep axis supplied by shuffles.
+// U is read twice through load_U (for the primitive state and for the
+// update) rather than kept in registers across the face computation.
+// RK = false: the split MUSCL-Hancock sweep, Un = the updated state (and, with
+// FUSE, the source steps and the wave speed s of the result).  RK = true: the
+// direction's part of the unsplit operator of Sec. 3.1, Un = D_dir(q) with
+// nu = 1/dx (edges without the predictor; FUSE is left to the caller).
+//
+// lane_face: the stages up to the flux through the face on the left of the
+// lane's cell (fa; wall: that face is a reflective wall), and the cell's
+// 1 / (sum of partial densities); it depends on the cells 3 to the left and
+// 2 to the right.  lane_sweep adds the update.
+template <int D, int N, int RX, int DIR, bool RK, class LoadU>
+__device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const double (&phi_t)[3][3], double nu,
+                                          FaceV<D, N, RX>& fa, double& irho0, bool wall) {
+  using L = Lay<D, N, RX>;
+  constexpr int F = L::F;
+  double W[F];
+  double rc2;
+  {
+    double U[F];
+    load_U(U);
+    Thermo<N, RX> T;
+    double H[6], J2;
+    cons_to_prim<D, N, RX>(P, U, W, T, H, J2);
+    irho0 = T.irho;  // 1 / sum of partial densities
+    rc2 = T.rc2;
   }
+  double Wm[F], Wp[F];
+#pragma unroll
+  for (int f = 0; f < F; ++f) {
+    Wm[f] = from_left(W[f]);
+    Wp[f] = from_right(W[f]);
+  }
+  double WL[F], WR[F], jump[F];
+  edges_limited<D, N, RX>(P, Wm, W, Wp, WL, WR, jump);
+  if (P.thinc) {
+    // THINC and the BVD choice where a lane of the wave holds a mixed cell
+    // (elsewhere both candidates of every fraction are the MUSCL edges)
+    bool mixed = false;
+#pragma unroll
+    for (int l = 0; l < N - 1; ++l) {
+      double num, den;
+      mixed = mixed || thinc_mixed(P, Wm[l], W[l], Wp[l], num, den);
+    }
+    if (__builtin_amdgcn_ballot_w64(mixed) != 0) lane_bvd<D, N, RX, DIR>(P, Wm, W, Wp, phi_t, WL, WR, jump);
+  }
+  if (!RK) edges_half_step<D, N, RX, DIR>(P, W, jump, irho0, rc2, nu, WL, WR);
   // face on the left of this cell: right edge of the left neighbour | my left edge
   double WRm[F];
 #pragma unroll

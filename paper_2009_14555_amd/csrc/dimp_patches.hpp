@@ -84,16 +84,17 @@ __device__ __forceinline__ int4 segment_of(const int4* __restrict__ seg, int sb,
   return sg;
 }
 
-template <int N, int RX, bool FUSE, int WPB>
+template <int N, int RX, int PROF, bool FUSE, int WPB>
 __global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX>())) void psweep_row(
     Params P, const PatchGeo* __restrict__ geo, WorkList wl, int64_t w0, int64_t nwork, const double* __restrict__ in,
     double* __restrict__ out, double dt_arg, const double* __restrict__ dtp, double* __restrict__ part) {
   constexpr int F = Lay<PD, N, RX>::F;
+  assume_profile<N, RX, PROF>(P);
   const int lane = threadIdx.x & 63;
-  const int64_t wv = xcd_block(blockIdx.x, gridDim.x) * WPB + (threadIdx.x >> 6);
+  const int64_t wv = xcd_block(blockIdx.x, gridDim.x) * WPB + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (wv >= nwork) return;  // whole waves only: a work item is one wave
   const double dt = dtp ? dtp[0] : dt_arg;
-  const double nu = dt / P.dx[0];
+  const double nu = dt * P.idx[0];
   const int64_t E = P.ncell;
   __shared__ double stash[F * 64 * WPB];
   const int sb = wl.beg[w0 + wv], se = wl.beg[w0 + wv + 1];
@@ -140,11 +141,12 @@ __global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX>())) void psweep_row(
   }
 }
 
-template <int N, int RX, bool FUSE, int CW>
+template <int N, int RX, int PROF, bool FUSE, int CW>
 __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
     Params P, const PatchGeo* __restrict__ geo, WorkList wl, int64_t w0, int64_t nwork, const double* __restrict__ in,
     double* __restrict__ out, double dt_arg, const double* __restrict__ dtp, double* __restrict__ part) {
   constexpr int F = Lay<PD, N, RX>::F;
+  assume_profile<N, RX, PROF>(P);
   constexpr int PITCH = CW + 1;
   constexpr int PP = CW + 2;
   extern __shared__ double lds[];
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
   const int64_t t = xcd_block(blockIdx.x, gridDim.x);
   if (t >= nwork) return;  // whole block: a work item is one tile
   const double dt = dtp ? dtp[0] : dt_arg;
-  const double nu = dt / P.dx[1];
+  const double nu = dt * P.idx[1];
   const int64_t E = P.ncell;
   const int tid = threadIdx.x;
   const int w = tid >> 6, lane = tid & 63;
@@ -225,8 +227,8 @@ size_t tile_lds_bytes() {
 
 // one sweep of a patch set with N materials and the RX layout (the
 // launch_patch_sweep contract)
-template <int N, int RX>
-hipError_t launch_patch_t(const Params& P, const PatchGeo* geo, WorkList wl, int64_t w0, int64_t nwork,
+template <int N, int RX, int PROF>
+hipError_t launch_patch_p(const Params& P, const PatchGeo* geo, WorkList wl, int64_t w0, int64_t nwork,
                           const double* in, double* out, double dt, const double* dtp, int dir, bool fuse,
                           double* part, int row_wpb, int cw, hipStream_t st) {
   if (nwork <= 0) return hipSuccess;
@@ -235,10 +237,10 @@ hipError_t launch_patch_t(const Params& P, const PatchGeo* geo, WorkList wl, int
     const dim3 block(64 * row_wpb);
 #define DIMP_ROW(W)                                                                                              \
   if (fuse)                                                                                                     \
-    hipLaunchKernelGGL((psweep_row<N, RX, true, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp,  \
+    hipLaunchKernelGGL((psweep_row<N, RX, PROF, true, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp,  \
                        part);                                                                                   \
   else                                                                                                          \
-    hipLaunchKernelGGL((psweep_row<N, RX, false, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp, \
+    hipLaunchKernelGGL((psweep_row<N, RX, PROF, false, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp, \
                        part);
     if (row_wpb == 1) {
       DIMP_ROW(1)
@@ -254,21 +256,32 @@ hipError_t launch_patch_t(const Params& P, const PatchGeo* geo, WorkList wl, int
   if (cw == 8) {
     const size_t lds = tile_lds_bytes<N, RX, 8>();
     if (fuse)
-      hipLaunchKernelGGL((psweep_tile<N, RX, true, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, true, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
     else
-      hipLaunchKernelGGL((psweep_tile<N, RX, false, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, false, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
   } else {
     const size_t lds = tile_lds_bytes<N, RX, 4>();
     if (fuse)
-      hipLaunchKernelGGL((psweep_tile<N, RX, true, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, true, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
     else
-      hipLaunchKernelGGL((psweep_tile<N, RX, false, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, false, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
   }
   return hipGetLastError();
+}
+
+// the instance of the materials' profile
+template <int N, int RX>
+hipError_t launch_patch_t(const Params& P, const PatchGeo* geo, WorkList wl, int64_t w0, int64_t nwork,
+                          const double* in, double* out, double dt, const double* dtp, int dir, bool fuse,
+                          double* part, int row_wpb, int cw, hipStream_t st) {
+  return by_profile<N, RX>(P, [&](auto prof) {
+    return launch_patch_p<N, RX, decltype(prof)::value>(P, geo, wl, w0, nwork, in, out, dt, dtp, dir, fuse, part,
+                                                        row_wpb, cw, st);
+  });
 }
 
 }  // namespace dimp

@@ -13,6 +13,18 @@
 namespace dimp {
 
 // ------------------------------------------------------ THINC candidates
+// mixed-cell test of Appendix A, delta < C < 1 - delta with C = (q0 - qmin +
+// eps)/(qmax + eps) multiplied through by the non-negative denominator, and a
+// monotone stencil
+__device__ __forceinline__ bool thinc_mixed(const Params& P, double qm, double q0, double qp, double& num,
+                                            double& den) {
+  const double qmin = fmin(qm, qp);
+  const double qmax = fmax(qm, qp) - qmin;
+  num = q0 - qmin + P.eps;
+  den = qmax + P.eps;
+  return (P.delta * den < num) && (num < (1.0 - P.delta) * den) && ((qp - q0) * (q0 - qm) > 0.0);
+}
+
 // MUSCL edges (mL, mR) of phi and the THINC-or-MUSCL pair (tL, tR).  The
 // interface normal (a sqrt and two divisions) and the three transcendentals
 // are only evaluated in mixed cells (Appendix A criterion); cosh and tanh of
@@ -26,12 +38,10 @@ __device__ __forceinline__ Cand phi_candidates(const Params& P, double qm, doubl
   c.tL = c.mL;
   c.tR = c.mR;
   if (!P.thinc) return c;
+  double num, den;
+  if (!thinc_mixed(P, qm, q0, qp, num, den)) return c;
   const double qmin = fmin(qm, qp);
   const double qmax = fmax(qm, qp) - qmin;
-  // mixed-cell test delta < C < 1 - delta with C = (q0 - qmin + eps)/(qmax + eps),
-  // multiplied through by the non-negative denominator
-  const double num = q0 - qmin + P.eps, den = qmax + P.eps;
-  if (!((P.delta * den < num) && (num < (1.0 - P.delta) * den) && ((qp - q0) * (q0 - qm) > 0.0))) return c;
   const double C = num / den;
   const double beta = P.beta0 * nd_of() + 0.01;
   const double eb = exp(beta);
@@ -50,33 +60,31 @@ __device__ __forceinline__ Cand phi_candidates(const Params& P, double qm, doubl
 }
 
 // total boundary variation of the candidate pair (Lp, Rp) of a cell against
-// the neighbours' candidates (Appendix A)
+// the neighbours' candidates (Appendix A): the least of the four sums of a
+// left and a right jump is the sum of the least of each
 __device__ __forceinline__ double tbv(const Cand& m, const Cand& p, double Lp, double Rp) {
-  const double v1 = fabs(m.mR - Lp) + fabs(Rp - p.mL);
-  const double v2 = fabs(m.tR - Lp) + fabs(Rp - p.tL);
-  const double v3 = fabs(m.mR - Lp) + fabs(Rp - p.tL);
-  const double v4 = fabs(m.tR - Lp) + fabs(Rp - p.mL);
-  return fmin(fmin(v1, v2), fmin(v3, v4));
+  return fmin(fabs(m.mR - Lp), fabs(m.tR - Lp)) + fmin(fabs(Rp - p.mL), fabs(Rp - p.tL));
 }
 
-// stress column sigma_{k,DIR} = 2 G dev H - p delta of a primitive state
+// stress column sigma_{k,DIR} = 2 G dev H - p delta of a primitive state;
+// shear_col leaves the part 2 G dev H
 template <int D, int N, int RX, int DIR>
-__device__ __forceinline__ void stress_col(const Params& P, const double* W, double sig[3]) {
-  using L = Lay<D, N, RX>;
+__device__ __forceinline__ void shear_col(const Params& P, const double* W, double sig[3]) {
   if (!P.any_shear) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) sig[k] = (k == DIR) ? -W[L::E] : 0.0;
+    for (int k = 0; k < 3; ++k) sig[k] = 0.0;
     return;
   }
   double H[6];
-  const double G = prim_shear<D, N, RX>(P, W, H);
+  const double G2 = 0.5 * prim_shear<D, N, RX>(P, W, H);  // H holds 4 H
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if (hnz<D>(k, DIR))
-      sig[k] = 2.0 * G * H[hs(k, DIR)] - ((k == DIR) ? W[L::E] : 0.0);
-    else
-      sig[k] = 0.0;
-  }
+  for (int k = 0; k < 3; ++k) sig[k] = hnz<D>(k, DIR) ? G2 * H[hs(k, DIR)] : 0.0;
+}
+
+template <int D, int N, int RX, int DIR>
+__device__ __forceinline__ void stress_col(const Params& P, const double* W, double sig[3]) {
+  shear_col<D, N, RX, DIR>(P, W, sig);
+  sig[DIR] -= W[Lay<D, N, RX>::E];
 }
 
 // Edges of one cell (MUSCL, with the BVD choice for phi) advanced half a
@@ -85,71 +93,80 @@ __device__ __forceinline__ void stress_col(const Params& P, const double* W, dou
 //   u_k: u_n du_k - dsigma_kn / rho     p: u_n dp + rho c^2 du_n
 //   Vbar_ij: u_n dV_ij - V_nj du_i + V_ij du_n / 3
 // (the last is DVbar/Dt = (grad u) Vbar - div(u) Vbar / 3 of Sec. 2.1).
-// MUSCL edges of every primitive component, with the BVD choice for phi
-// (C: a Cand, the candidates of the single fraction of two materials, or a
-// CandSet<N>, one per stored fraction; of the neighbours' candidates only the
-// right edges of cm and the left edges of cp are read)
-template <int D, int N, int RX, class C>
-__device__ __forceinline__ void edges_muscl(const Params& P, const double* Wm, const double* W0, const double* Wp,
-                                            const C& cm, const C& c0, const C& cp, double* WL, double* WR) {
-  using L = Lay<D, N, RX>;
-  constexpr int F = L::F;
+// MUSCL edges and slopes of every primitive component
+template <int D, int N, int RX>
+__device__ __forceinline__ void edges_limited(const Params& P, const double* Wm, const double* W0, const double* Wp,
+                                              double* WL, double* WR, double* s) {
+  constexpr int F = Lay<D, N, RX>::F;
+  // one branch for all components
+  if (P.limiter == 1) {
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+      s[f] = vanalbada(W0[f] - Wm[f], Wp[f] - W0[f], P.va_e2[Lay<D, N, RX>::kind(f)]);
+  } else {
+#pragma unroll
+    for (int f = 0; f < F; ++f) s[f] = minmod(W0[f] - Wm[f], Wp[f] - W0[f]);
+  }
 #pragma unroll
   for (int f = 0; f < F; ++f) {
-    const double s = slope<D, N, RX>(P, f, Wm[f], W0[f], Wp[f]);
-    WL[f] = W0[f] - 0.5 * s;
-    WR[f] = W0[f] + 0.5 * s;
-  }
-  if (P.thinc) {
-#pragma unroll
-    for (int l = 0; l < N - 1; ++l) {
-      const Cand &a = cand_at(cm, l), &b = cand_at(c0, l), &e = cand_at(cp, l);
-      const double tm = tbv(a, e, b.mL, b.mR);
-      const double tt = tbv(a, e, b.tL, b.tR);
-      const bool th = tt < tm;
-      WL[l] = th ? b.tL : b.mL;
-      WR[l] = th ? b.tR : b.mR;
-    }
+    WL[f] = W0[f] - 0.5 * s[f];
+    WR[f] = W0[f] + 0.5 * s[f];
   }
 }
 
-template <int D, int N, int RX, int DIR, class C>
-__device__ __forceinline__ void edges_predict(const Params& P, const double* Wm, const double* W0, const double* Wp,
-                                              double irho0, double rc2, const C& cm, const C& c0, const C& cp,
-                                              double nu, double* WL, double* WR) {
+// the BVD choice for the stored volume fractions; s receives the chosen jumps
+// (C: a Cand, the candidates of the single fraction of two materials, or a
+// CandSet<N>, one per stored fraction; of the neighbours' candidates only the
+// right edges of cm and the left edges of cp are read)
+template <int N, class C>
+__device__ __forceinline__ void edges_bvd(const C& cm, const C& c0, const C& cp, double* WL, double* WR, double* s) {
+#pragma unroll
+  for (int l = 0; l < N - 1; ++l) {
+    const Cand &a = cand_at(cm, l), &b = cand_at(c0, l), &e = cand_at(cp, l);
+    const double tm = tbv(a, e, b.mL, b.mR);
+    const double tt = tbv(a, e, b.tL, b.tR);
+    const bool th = tt < tm;
+    WL[l] = th ? b.tL : b.mL;
+    WR[l] = th ? b.tR : b.mR;
+    s[l] = WR[l] - WL[l];
+  }
+}
+
+// the half-step predictor on edges WL, WR with jumps dW = WR - WL
+template <int D, int N, int RX, int DIR>
+__device__ __forceinline__ void edges_half_step(const Params& P, const double* W0, const double* dW, double irho0,
+                                                double rc2, double nu, double* WL, double* WR) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
-  edges_muscl<D, N, RX>(P, Wm, W0, Wp, cm, c0, cp, WL, WR);
   double sL[3], sR[3];
-  stress_col<D, N, RX, DIR>(P, WL, sL);
-  stress_col<D, N, RX, DIR>(P, WR, sR);
-  double dW[F];
-#pragma unroll
-  for (int f = 0; f < F; ++f) dW[f] = WR[f] - WL[f];
-  const double un = W0[L::MOM0 + DIR];
-  const double dun = dW[L::MOM0 + DIR];
+  shear_col<D, N, RX, DIR>(P, WL, sL);
+  shear_col<D, N, RX, DIR>(P, WR, sR);
+  // the half step's length goes into the speeds
+  const double h = 0.5 * nu;
+  const double un = h * W0[L::MOM0 + DIR];
+  const double dun = h * dW[L::MOM0 + DIR];
+  const double hr = h * irho0, dun3 = dun * (1.0 / 3.0);
   double inc[F];
 #pragma unroll
-  for (int l = 0; l < N - 1; ++l) inc[l] = un * dW[l];
+  for (int f = 0; f < F; ++f) inc[f] = un * dW[f];
 #pragma unroll
-  for (int l = 0; l < N; ++l) inc[L::M0 + l] = un * dW[L::M0 + l] + W0[L::M0 + l] * dun;
-  if (RX) inc[L::LAM] = un * dW[L::LAM];
+  for (int l = 0; l < N; ++l) inc[L::M0 + l] += W0[L::M0 + l] * dun;
 #pragma unroll
-  for (int k = 0; k < D; ++k) inc[L::MOM0 + k] = un * dW[L::MOM0 + k] - (sR[k] - sL[k]) * irho0;
-  inc[L::E] = un * dW[L::E] + rc2 * dun;
+  for (int k = 0; k < D; ++k)
+    if (hnz<D>(k, DIR)) inc[L::MOM0 + k] -= (sR[k] - sL[k]) * hr;
+  inc[L::MOM0 + DIR] += dW[L::E] * hr;
+  inc[L::E] += rc2 * dun;
 #pragma unroll
   for (int q = 0; q < L::NV; ++q) {
     const int a = L::vi(q), b = L::vj(q);
-    double v = un * dW[L::V0 + q];
-    if (a < D && L::vq(DIR, b) >= 0) v -= vget<D, N, RX>(W0 + L::V0, DIR, b) * dW[L::MOM0 + (a < D ? a : 0)];
-    v += (1.0 / 3.0) * W0[L::V0 + q] * dun;
-    inc[L::V0 + q] = v;
+    if (a < D && L::vq(DIR, b) >= 0)
+      inc[L::V0 + q] -= vget<D, N, RX>(W0 + L::V0, DIR, b) * (h * dW[L::MOM0 + (a < D ? a : 0)]);
+    inc[L::V0 + q] += W0[L::V0 + q] * dun3;
   }
-  const double h = 0.5 * nu;
 #pragma unroll
   for (int f = 0; f < F; ++f) {
-    WL[f] -= h * inc[f];
-    WR[f] -= h * inc[f];
+    WL[f] -= inc[f];
+    WR[f] -= inc[f];
   }
 #pragma unroll
   for (int l = 0; l < N - 1; ++l) {
@@ -160,6 +177,16 @@ __device__ __forceinline__ void edges_predict(const Params& P, const double* Wm,
     WL[L::LAM] = fmin(fmax(WL[L::LAM], 0.0), 1.0);
     WR[L::LAM] = fmin(fmax(WR[L::LAM], 0.0), 1.0);
   }
+}
+
+template <int D, int N, int RX, int DIR, class C>
+__device__ __forceinline__ void edges_predict(const Params& P, const double* Wm, const double* W0, const double* Wp,
+                                              double irho0, double rc2, const C& cm, const C& c0, const C& cp,
+                                              double nu, double* WL, double* WR) {
+  double s[Lay<D, N, RX>::F];
+  edges_limited<D, N, RX>(P, Wm, W0, Wp, WL, WR, s);
+  if (P.thinc) edges_bvd<N>(cm, c0, cp, WL, WR, s);
+  edges_half_step<D, N, RX, DIR>(P, W0, s, irho0, rc2, nu, WL, WR);
 }
 
 // ----------------------------------------------------------- face flux
@@ -173,9 +200,10 @@ struct Side {
 template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void side_state(const Params& P, const double* W, Side<D, N, RX>& S) {
   using L = Lay<D, N, RX>;
+  Phases<N> Q;
   Thermo<N, RX> T;
   double H[6], J2;
-  prim_thermo<D, N, RX>(P, W, T, H, J2, true);
+  prim_mix<D, N, RX>(P, W, Q, T, H, J2);
   S.rho = T.rho;
   double uu = 0.0;
 #pragma unroll
@@ -184,14 +212,15 @@ __device__ __forceinline__ void side_state(const Params& P, const double* W, Sid
     uu += S.u[k] * S.u[k];
   }
   S.E = T.rhoe + 0.5 * T.rho * uu;
-  S.cl = sqrt(T.cL2);
+  // one reciprocal for 1/xi and c_L^2 = (sum of w rho c^2 + 4/3 sum of w G) / (xi rho)
+  double cnum, gnum;
+  sound_sums<N, RX>(P, Q, T, cnum, gnum);
+  const double q = frcp(T.xi * T.rho);
+  S.cl = fsqrt(fma(4.0 / 3.0, gnum, cnum) * q);
+  const double G2 = 0.5 * (gnum * (q * T.rho));  // H holds 4 H
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if (hnz<D>(k, DIR))
-      S.sig[k] = 2.0 * T.Gmix * H[hs(k, DIR)] - ((k == DIR) ? T.p : 0.0);
-    else
-      S.sig[k] = 0.0;
-  }
+  for (int k = 0; k < 3; ++k) S.sig[k] = hnz<D>(k, DIR) ? G2 * H[hs(k, DIR)] : 0.0;
+  S.sig[DIR] -= T.p;
 }
 
 template <int D, int N, int RX>
@@ -224,8 +253,12 @@ __device__ __forceinline__ void star_flux(const Params& P, const double* W, cons
   using L = Lay<D, N, RX>;
   const double un = S.u[DIR];
   const double r = a * inv;
-  const double rm1 = r - 1.0;
-  const double us_face = un + SK * rm1;
+  const double us_face = un + SK * (r - 1.0);
+  // F_K + S_K (U*_K - U_K) collected: a mass m moves with the face velocity
+  // u* = u_n + S_K (r - 1), every other term with S_K / (S_K - S*) = SK inv of
+  // its star correction; the normal row of Vbar is continuous and carries no
+  // flux (u_n V_nj - V_nj u_n = 0)
+  const double Si = SK * inv;
   double phiN = 1.0;
 #pragma unroll
   for (int l = 0; l < N - 1; ++l) {
@@ -233,43 +266,36 @@ __device__ __forceinline__ void star_flux(const Params& P, const double* W, cons
     out.F[l] = W[l] * us_face;  // phi_K u*, the same u* as in the phi source
   }
 #pragma unroll
-  for (int l = 0; l < N; ++l) {
-    const double m = (l < N - 1 ? W[l] : phiN) * W[L::M0 + l];
-    out.F[L::M0 + l] = m * un + SK * (rm1 * m);
-  }
-  if (RX) {
-    const double ml = m_lambda<D, N, RX>(P, W);
-    out.F[L::LAM] = ml * un + SK * (rm1 * ml);
-  }
-  const double rs = r * S.rho;
+  for (int l = 0; l < N; ++l) out.F[L::M0 + l] = (l < N - 1 ? W[l] : phiN) * W[L::M0 + l] * us_face;
+  if (RX) out.F[L::LAM] = m_lambda<D, N, RX>(P, W) * us_face;
+  const double du = un - SK, Sr = SK * r;
   double usK = 0.0, usS = 0.0;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
-    const double mom = S.rho * S.u[k];
-    out.F[L::MOM0 + k] = mom * un - S.sig[k] + SK * (rs * ust[k] - mom);
+    out.F[L::MOM0 + k] = S.rho * (S.u[k] * du + Sr * ust[k]) - S.sig[k];
     const double sst = S.sig[k] - mK * (ust[k] - S.u[k]);
     usK += S.u[k] * S.sig[k];
     usS += ust[k] * sst;
   }
-  const double Es = (S.E * a + (usK - usS)) * inv;
-  out.F[L::E] = S.E * un - usK + SK * (Es - S.E);
+  out.F[L::E] = (S.E * us_face - usK) + Si * (usK - usS);
 #pragma unroll
-  for (int q = 0; q < L::NV; ++q) {
-    const int i = L::vi(q), j = L::vj(q);
-    const double V = W[L::V0 + q];
-    const bool coupled = (i < D) && (L::vq(DIR, j) >= 0);
-    const double Vn = coupled ? vget<D, N, RX>(W + L::V0, DIR, j) : 0.0;
+  for (int i = 0; i < 3; ++i) {
+    if (i == DIR) continue;
+    // Vbar_ij u* - Vbar_nj (u_i + Si (u*_i - u_i))
     const int ii = i < D ? i : 0;
-    double Fx = V * un;
-    if (coupled) Fx -= Vn * S.u[ii];
-    if (i == DIR) {
-      out.F[L::V0 + q] = Fx;  // normal row continuous: U* = U
-    } else {
-      double Vs = a * V;
-      if (coupled) Vs -= Vn * (ust[ii] - S.u[ii]);
-      out.F[L::V0 + q] = Fx + SK * (Vs * inv - V);
+    const double ui = (i < D) ? S.u[ii] + Si * (ust[ii] - S.u[ii]) : 0.0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if (L::vq(i, j) < 0) continue;
+      const int q = L::vq(i, j) >= 0 ? L::vq(i, j) : 0;
+      double Fx = W[L::V0 + q] * us_face;
+      if (i < D && L::vq(DIR, j) >= 0) Fx -= vget<D, N, RX>(W + L::V0, DIR, j) * ui;
+      out.F[L::V0 + q] = Fx;
     }
   }
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if (L::vq(DIR, j) >= 0) out.F[L::V0 + (L::vq(DIR, j) >= 0 ? L::vq(DIR, j) : 0)] = 0.0;
   out.ustar = us_face;
 #pragma unroll
   for (int j = 0; j < D; ++j) out.Vn[j] = vget<D, N, RX>(W + L::V0, DIR, j);
@@ -333,6 +359,32 @@ __device__ __forceinline__ void face_flux(const Params& P, const double* WL, con
 }
 
 // ---------------------------------------------------------------- update
+// F_b - F_a less the non-conservative sources of phi and Vbar
+template <int D, int N, int RX, int DIR>
+__device__ __forceinline__ void flux_difference(const double* U, double inv_rho, const FaceV<D, N, RX>& a,
+                                                const FaceV<D, N, RX>& b, double* Dd) {
+  using L = Lay<D, N, RX>;
+  const double du = b.ustar - a.ustar;
+  const double du23 = (2.0 / 3.0) * du;
+#pragma unroll
+  for (int f = 0; f < L::V0; ++f) Dd[f] = b.F[f] - a.F[f];
+#pragma unroll
+  for (int l = 0; l < N - 1; ++l) Dd[l] -= U[l] * du;
+  double u[D], dV[D];
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    u[k] = U[L::MOM0 + k] * inv_rho;
+    dV[k] = b.Vn[k] - a.Vn[k];
+  }
+#pragma unroll
+  for (int q = 0; q < L::NV; ++q) {
+    const int i = L::vi(q), j = L::vj(q);
+    double v = (i == DIR) ? 0.0 : b.F[L::V0 + q] - a.F[L::V0 + q];  // the normal row carries no flux
+    if (i < D && j < D) v += u[i < D ? i : 0] * dV[j < D ? j : 0];
+    Dd[L::V0 + q] = v - U[L::V0 + q] * du23;
+  }
+}
+
 // U^{new} = U - nu (F_b - F_a) with phi's source phi div u and Vbar's sources
 // (2/3) Vbar div u - u_i beta_j taken with the face velocities u* and the
 // upwinded normal rows Vbar*_{n j} (cell-centre coefficients).
@@ -340,18 +392,10 @@ template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void update_cell(const double* U, double inv_rho, const FaceV<D, N, RX>& a,
                                             const FaceV<D, N, RX>& b, double nu, double* Un) {
   using L = Lay<D, N, RX>;
-  const double du = b.ustar - a.ustar;
+  double Dd[L::F];
+  flux_difference<D, N, RX, DIR>(U, inv_rho, a, b, Dd);
 #pragma unroll
-  for (int l = 0; l < N - 1; ++l) Un[l] = U[l] - nu * ((b.F[l] - a.F[l]) - U[l] * du);
-#pragma unroll
-  for (int f = N - 1; f < L::V0; ++f) Un[f] = U[f] - nu * (b.F[f] - a.F[f]);
-#pragma unroll
-  for (int q = 0; q < L::NV; ++q) {
-    const int i = L::vi(q), j = L::vj(q);
-    double src = (2.0 / 3.0) * U[L::V0 + q] * du;
-    if (i < D && j < D) src -= (U[L::MOM0 + (i < D ? i : 0)] * inv_rho) * (b.Vn[j < D ? j : 0] - a.Vn[j < D ? j : 0]);
-    Un[L::V0 + q] = U[L::V0 + q] - nu * ((b.F[L::V0 + q] - a.F[L::V0 + q]) - src);
-  }
+  for (int f = 0; f < L::F; ++f) Un[f] = U[f] - nu * Dd[f];
 }
 
 // The direction's part of the unsplit operator D(q) of Sec. 3.1: the flux
@@ -361,18 +405,9 @@ template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void div_cell(const double* U, double inv_rho, const FaceV<D, N, RX>& a,
                                          const FaceV<D, N, RX>& b, double idx, double* Dd) {
   using L = Lay<D, N, RX>;
-  const double du = b.ustar - a.ustar;
+  flux_difference<D, N, RX, DIR>(U, inv_rho, a, b, Dd);
 #pragma unroll
-  for (int l = 0; l < N - 1; ++l) Dd[l] = ((b.F[l] - a.F[l]) - U[l] * du) * idx;
-#pragma unroll
-  for (int f = N - 1; f < L::V0; ++f) Dd[f] = (b.F[f] - a.F[f]) * idx;
-#pragma unroll
-  for (int q = 0; q < L::NV; ++q) {
-    const int i = L::vi(q), j = L::vj(q);
-    double src = (2.0 / 3.0) * U[L::V0 + q] * du;
-    if (i < D && j < D) src -= (U[L::MOM0 + (i < D ? i : 0)] * inv_rho) * (b.Vn[j < D ? j : 0] - a.Vn[j < D ? j : 0]);
-    Dd[L::V0 + q] = ((b.F[L::V0 + q] - a.F[L::V0 + q]) - src) * idx;
-  }
+  for (int f = 0; f < L::F; ++f) Dd[f] *= idx;
 }
 
 // --------------------------------------------------------------- sources
@@ -403,10 +438,10 @@ struct JcCtx {
   }
 };
 
-__device__ __forceinline__ double jc_target(const MatP& m, const EosV& e, double p, double rho, double J,
+__device__ __forceinline__ double jc_target(const MatP& m, const Curve& e, double p, double rho, double J,
                                             double eps, double dt) {
   if (!(dt > 0.0) || !(J > 0.0)) return J;
-  const double theta = fmin(fmax((p - e.pref) / (rho * e.Gam * m.cv) * m.jc_inv_dT, 0.0), 1.0);
+  const double theta = fmin(fmax((p - e.pref) / (rho * m.Gam * m.cv) * m.jc_inv_dT, 0.0), 1.0);
   const double soft = 1.0 - pow(theta, m.jc_m);
   if (!(soft > 0.0)) return 0.0;  // at or above melt: no strength
   const JcCtx c{sqrt(6.0) * e.G, soft, J, eps};
@@ -457,10 +492,7 @@ __device__ __forceinline__ void plastic_cell(const Params& P, double* U, double 
   cons_to_prim<D, N, RX, false>(P, U, W, T, H, J2);
   const double J = sqrt(J2);
   double num = 0.0;
-  double phiN = 1.0;
   double J_ep = J;  // target of the Johnson-Cook material (plastic strain update)
-#pragma unroll
-  for (int l = 0; l < N - 1; ++l) phiN -= W[l];
 #pragma unroll
   for (int l = 0; l < N; ++l) {
     if (rx_mix<RX>(P) && l == P.rx.mat) continue;
@@ -468,13 +500,12 @@ __device__ __forceinline__ void plastic_cell(const Params& P, double* U, double 
     if (!m.shear) continue;
     double Jl = J;
     if (m.plast == PLAST_PERFECT) {
-      Jl = fmin(J, m.yield_s6 * frcp(T.e[l].G));
+      Jl = fmin(J, m.yield_s6 * frcp(T.c[l].G));
     } else if (RX && m.plast == PLAST_JC) {
-      Jl = jc_target(m, T.e[l], T.p, W[L::M0 + l], J, W[L::LAM], dt);
+      Jl = jc_target(m, T.c[l], T.p, W[L::M0 + l], J, W[L::LAM], dt);
       J_ep = Jl;
     }
-    const double phi_l = (l < N - 1) ? W[l] : phiN;
-    num += phi_l * T.e[l].invGam * Jl;
+    num += T.w[l] * Jl;
   }
   const double fac = (J > 0.0) ? (num * T.ixi) * frcp(J) : 0.0;
   double Hs[6];
@@ -518,9 +549,8 @@ __device__ __forceinline__ void plastic_cell(const Params& P, double* U, double 
 template <bool GEN>
 __device__ __forceinline__ double rx_pressure(const RxP& r, double phi_y, double rho_y, double lam, double num0,
                                               double den0) {
-  double ra, rb, num, den;
-  RxRef A, B;
-  rx_cons<GEN>(r, phi_y, rho_y, lam, num0, den0, ra, rb, A, B, num, den);
+  double num, den;
+  (void)rx_cons<GEN>(r, phi_y, rho_y, lam, num0, den0, num, den);
   return num * frcp(den);
 }
 
@@ -608,11 +638,8 @@ __device__ __forceinline__ void reaction_cell(const Params& P, double* U, double
     return;
   }
   Phases<N> Q;
-  phases_from_partial<N>(U, U + L::M0, Q);
-  double rt = 0.0;
-#pragma unroll
-  for (int l = 0; l < N; ++l) rt += U[L::M0 + l];
-  const double irt = frcp(rt);
+  double rt, irt;
+  phases_from_partial<N>(U, U + L::M0, Q, rt, irt);
   double u[D], uu = 0.0;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
@@ -622,15 +649,9 @@ __device__ __forceinline__ void reaction_cell(const Params& P, double* U, double
   double H[6], J2;
   strain<D, N, RX>(U + L::V0, H, J2);
   Thermo<N, RX> T;
-  eos_all<N, RX>(P, Q, J2, T);  // the non-reactive materials
+  curves_all<N, RX>(P, Q, J2, T);  // the non-reactive materials
   const double rhoe = U[L::E] - 0.5 * rt * uu;
-  double num0 = rhoe, den0 = 0.0;
-#pragma unroll
-  for (int l = 0; l < N; ++l) {
-    if (l == y) continue;
-    den0 += Q.phi[l] * T.e[l].invGam;
-    num0 += Q.phi[l] * (T.e[l].pref * T.e[l].invGam - Q.rho[l] * T.e[l].eref);
-  }
+  const double num0 = rhoe + T.n0, den0 = T.d0;
   double phi_y = 0.0, rho_y = 0.0;
 #pragma unroll
   for (int l = 0; l < N; ++l)
@@ -647,30 +668,33 @@ __device__ __forceinline__ void reaction_cell(const Params& P, double* U, double
     return -r.k * lc * xn;
   };
   const double l0 = fmin(fmax(U[L::LAM] * frcp(my), 0.0), 1.0);
-  const double k1 = rate(l0);
-  double l1 = l0;
-  // no rate at the start (an unreacted cell below the ignition threshold, a
-  // fully burnt one): every later stage evaluates the same lambda and gives
-  // 0 again, so the result is l0 exactly
-  if (k1 != 0.0) {
-    const double k2 = rate(l0 + 0.5 * dt * k1);
-    const double k3 = rate(l0 + 0.5 * dt * k2);
-    const double k4 = rate(l0 + dt * k3);
-    l1 = l0 + (dt / 6.0) * (k1 + 2.0 * k2 + 2.0 * k3 + k4);
-    l1 = fmin(fmax(l1, 0.0), 1.0);
+  // the four stages through one evaluation site (the JWL split is some 600
+  // instructions: four copies, and the other splits of a fused sweep, exceed
+  // the instruction cache)
+  double l1 = l0, k = 0.0, sum = 0.0;
+#pragma unroll 1
+  for (int st = 0; st < 4; ++st) {
+    const double c = (st == 0) ? 0.0 : (st == 3) ? 1.0 : 0.5;
+    k = rate(l0 + c * dt * k);
+    // no rate at the start (an unreacted cell below the ignition threshold, a
+    // fully burnt one): every later stage evaluates the same lambda and gives
+    // 0 again, so the result is l0 exactly
+    if (st == 0 && !(k != 0.0)) break;
+    sum += (st == 1 || st == 2) ? 2.0 * k : k;
+    if (st == 3) l1 = fmin(fmax(l0 + (dt / 6.0) * sum, 0.0), 1.0);
   }
   U[L::LAM] = my * l1;
   if (WS) {
     double num, den;
-    rx_cons<RX == 2>(r, phi_y, rho_y, l1, num0, den0, T.rho_a, T.rho_b, T.A, T.B, num, den);
+    T.sp = rx_cons<RX == 2>(r, phi_y, rho_y, l1, num0, den0, num, den);
     T.rho = rt;
     T.irho = irt;
     T.xi = den;
     T.ixi = frcp(den);
     T.p = num * T.ixi;
     T.rhoe = rhoe;
-    finish<N, RX>(P, Q, l1, T, true, true);
-    const double cl = sqrt(T.cL2);
+    finish<N, RX>(P, Q, T);
+    const double cl = fsqrt(T.cL2);
 #pragma unroll
     for (int k = 0; k < D; ++k) s[k] = fabs(u[k]) + cl;
   }
@@ -683,7 +707,7 @@ __device__ __forceinline__ void wavespeed_cell(const Params& P, const double* U,
   Thermo<N, RX> T;
   double H[6], J2;
   cons_to_prim<D, N, RX>(P, U, W, T, H, J2);
-  const double cl = sqrt(T.cL2);
+  const double cl = fsqrt(T.cL2);
 #pragma unroll
   for (int k = 0; k < D; ++k) s[k] = fabs(W[L::MOM0 + k]) + cl;
 }
@@ -702,21 +726,18 @@ __device__ __forceinline__ void epilogue_cell(const Params& P, double* U, double
   }
   using L = Lay<D, N, RX>;
   Phases<N> Q;
-  phases_from_partial<N>(U, U + L::M0, Q);
-  double r = 0.0;
-#pragma unroll
-  for (int l = 0; l < N; ++l) r += U[L::M0 + l];
-  const double inv_r = frcp(r);
+  double r, inv_r;
+  phases_from_partial<N>(U, U + L::M0, Q, r, inv_r);
   double u[D], uu = 0.0;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     u[k] = U[L::MOM0 + k] * inv_r;
     uu += u[k] * u[k];
   }
-  // plastic step (Sec. 3.2)
+  // plastic step (Sec. 3.2); H holds 4 H
   double H[6], J2;
-  strain<D, N, RX>(U + L::V0, H, J2);
-  const double J = sqrt(J2);
+  strain4<D, N, RX>(U + L::V0, H, J2);
+  const double J = fsqrt(J2);
   double xi = 0.0, num = 0.0;
 #pragma unroll
   for (int l = 0; l < N; ++l) {
@@ -728,14 +749,13 @@ __device__ __forceinline__ void epilogue_cell(const Params& P, double* U, double
     if (m.plast == PLAST_PERFECT) Jl = fmin(J, m.yield_s6 * frcp(shear_modulus(m, Q.rho[l])));
     num += wl * Jl;
   }
-  const double fac = (J > 0.0) ? (num * frcp(xi)) * frcp(J) : 0.0;
+  const double fac = (J > 0.0) ? 0.125 * (num * frcp(xi * J)) : 0.0;  // half the factor of H
   double Mm[6], Mp[6];
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
     const double id = (q == 0 || q == 3 || q == 5) ? 1.0 : 0.0;
-    const double hq = (J > 0.0) ? fac * H[q] : 0.0;
-    Mm[q] = id - 0.5 * hq;
-    Mp[q] = id + 0.5 * hq;
+    Mm[q] = id - fac * H[q];
+    Mp[q] = id + fac * H[q];
   }
   double A[6];
   A[0] = Mm[3] * Mm[5] - Mm[4] * Mm[4];
@@ -755,15 +775,15 @@ __device__ __forceinline__ void epilogue_cell(const Params& P, double* U, double
     U[L::V0 + q] = v * inv_det;
   }
   // wave speed of the relaxed state
-  strain<D, N, RX>(U + L::V0, H, J2);
+  strain4<D, N, RX>(U + L::V0, H, J2);
   Thermo<N, RX> T;
   T.rho = r;
   T.irho = inv_r;
-  eos_all<N, RX>(P, Q, J2, T);
+  curves_all<N, RX>(P, Q, J2, T);
   T.rhoe = U[L::E] - 0.5 * r * uu;
   pressure_from_rhoe<N, RX>(P, Q, 0.0, T);
-  finish<N, RX>(P, Q, 0.0, T, true, true);
-  const double cl = sqrt(T.cL2);
+  finish<N, RX>(P, Q, T);
+  const double cl = fsqrt(T.cL2);
 #pragma unroll
   for (int k = 0; k < D; ++k) s[k] = fabs(u[k]) + cl;
 }

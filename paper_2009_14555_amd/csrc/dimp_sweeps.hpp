@@ -16,6 +16,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "dimp_calib.hpp"
 #include "dimp_internal.hpp"
 #include "dimp_lane.hpp"
 
@@ -53,13 +54,14 @@ __device__ __forceinline__ double rk_b(int stage) { return stage == 1 ? 1.0 : st
 // ----------------------------------------------------------- row sweep
 // Sweep along x.  Each wave: one 64-cell segment of one row, loaded and
 // stored straight from HBM (512-byte rows per field).
-template <int D, int N, int RX, bool FUSE, int MODE = M_SPLIT, bool WALL = false>
+template <int D, int N, int RX, int PROF, bool FUSE, int MODE = M_SPLIT, bool WALL = false>
 __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, FUSE>())) void sweep_row(Params P, const double* __restrict__ in, double* __restrict__ out,
                                                   double dt_arg, const double* __restrict__ dtp,
                                                   double* __restrict__ part, const double* __restrict__ Rin,
                                                   const double* qn, int stage) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
+  assume_profile<N, RX, PROF>(P);
   const double dt = dtp ? dtp[0] : dt_arg;
   const int lane = threadIdx.x & 63;
   const int64_t nx = P.n[0], ny = P.n[1], nz = P.n[2];
@@ -71,7 +73,9 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, FUSE>())) void sweep_ro
   const int64_t per = (nblocks + 7) / 8;
   const int64_t lb = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (lb >= nblocks) return;  // uniform per block
-  const int64_t wave = lb * 4 + (threadIdx.x >> 6);
+  // one value per wave, told to the compiler so that the index arithmetic (its
+  // divisions above all) runs on the scalar unit
+  const int64_t wave = lb * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t row = wave / nseg;
   if (row >= ny * nz) return;  // uniform per wave
   const int64_t seg = wave - row * nseg;
@@ -122,10 +126,12 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, FUSE>())) void sweep_ro
   const bool wall = WALL && ((x == 0 && (P.bc[0] == BC_REFLECTIVE || P.bc[0] == BC_AXIS)) ||
                              (x == nx && P.bc[0] == BC_REFLECTIVE));
   double Un[F], s[D];
-  if (MODE == M_SPLIT) {
-    lane_sweep<D, N, RX, 0, FUSE>(P, load_U, phi_t, dt / P.dx[0], dt, writer, Un, s, wall);
+  if constexpr (PROF == PROF_CALIB) {
+    calib::lane_sweep<0, FUSE>(P, load_U, phi_t, dt / P.dx[0], dt, writer, Un, s, wall);
+  } else if (MODE == M_SPLIT) {
+    lane_sweep<D, N, RX, 0, FUSE>(P, load_U, phi_t, dt * P.idx[0], dt, writer, Un, s, wall);
   } else {
-    lane_sweep<D, N, RX, 0, false, true>(P, load_U, phi_t, 1.0 / P.dx[0], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, 0, false, true>(P, load_U, phi_t, P.idx[0], dt, writer, Un, s, wall);
     if (writer) {
       const double b = rk_b(stage);
       if (D > 1) {
@@ -180,7 +186,7 @@ struct TileGeom {
   static constexpr int lds_doubles() { return (separate<F, NPL>() ? 2 : 1) * F * 64 * CW + NPL * 64 * PP; }
 };
 
-template <int D, int N, int RX, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false>
+template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false>
 __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void sweep_tile(Params P, const double* __restrict__ in,
                                                        double* __restrict__ out, double dt_arg,
                                                        const double* __restrict__ dtp,
@@ -191,6 +197,7 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void swee
   using G = TileGeom<CW>;
   constexpr int F = L::F;
   constexpr int PP = G::PP;
+  assume_profile<N, RX, PROF>(P);
   constexpr int NPL = (D == 3) ? 3 : 1;      // phi planes along the other transverse axis
   constexpr bool SEP = G::template separate<F, NPL>();
   extern __shared__ double lds[];
@@ -270,10 +277,12 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void swee
   const bool wall = WALL && ((jl == 0 && (P.bc[DIR] == BC_REFLECTIVE || P.bc[DIR] == BC_AXIS)) ||
                              (jl == nm && P.bc[DIR] == BC_REFLECTIVE));
   double Un[F], s[D];
-  if (MODE == M_SPLIT)
-    lane_sweep<D, N, RX, DIR, FUSE>(P, load_U, phi_t, dt / P.dx[DIR], dt, writer, Un, s, wall);
+  if constexpr (PROF == PROF_CALIB)
+    calib::lane_sweep<DIR, FUSE>(P, load_U, phi_t, dt / P.dx[DIR], dt, writer, Un, s, wall);
+  else if (MODE == M_SPLIT)
+    lane_sweep<D, N, RX, DIR, FUSE>(P, load_U, phi_t, dt * P.idx[DIR], dt, writer, Un, s, wall);
   else
-    lane_sweep<D, N, RX, DIR, false, true>(P, load_U, phi_t, 1.0 / P.dx[DIR], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, DIR, false, true>(P, load_U, phi_t, P.idx[DIR], dt, writer, Un, s, wall);
   if (MODE == M_RK_FIRST && writer) {
     // q - dt D_y(q) (the input tile still holds q)
     double U[F];
@@ -326,11 +335,10 @@ static inline int grid_for(int64_t work, int block) {
   return (int)(g < 1 ? 1 : g);
 }
 
-template <int D, int N, int RX, int DIR, bool FUSE, int MODE = M_SPLIT>
+template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int MODE = M_SPLIT>
 static void launch_tile(const Params& P, const double* in, double* out, double dt, const double* dtp,
                         double* part, hipStream_t st, const double* Rin = nullptr, const double* qn = nullptr,
                         int stage = 0) {
-  const bool walls = P.bc[DIR] >= BC_REFLECTIVE;
   constexpr int CW = TILE_COLUMNS;
   using L = Lay<D, N, RX>;
   const int oa = (DIR == 1) ? 2 : 1;
@@ -338,12 +346,14 @@ static void launch_tile(const Params& P, const double* in, double* out, double d
   const int64_t nblocks = ((P.n[0] + CW - 1) / CW) * no * ((P.n[DIR] + 57) / 58);
   const int64_t grid = ((nblocks + 7) / 8) * 8;
   const size_t lds = sizeof(double) * TileGeom<CW>::template lds_doubles<L::F, (D == 3) ? 3 : 1>();
-  if (walls) {
-    hipLaunchKernelGGL((sweep_tile<D, N, RX, DIR, FUSE, CW, MODE, true>), dim3((unsigned)grid), dim3(64 * CW), lds,
-                       st, P, in, out, dt, dtp, part, nblocks, Rin, qn, stage);
-    return;
+  if constexpr (PROF != PROF_CALIB) {  // (those grids have no walls)
+    if (P.bc[DIR] >= BC_REFLECTIVE) {
+      hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE, true>), dim3((unsigned)grid), dim3(64 * CW),
+                         lds, st, P, in, out, dt, dtp, part, nblocks, Rin, qn, stage);
+      return;
+    }
   }
-  hipLaunchKernelGGL((sweep_tile<D, N, RX, DIR, FUSE, CW, MODE>), dim3((unsigned)grid), dim3(64 * CW), lds, st, P,
+  hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE>), dim3((unsigned)grid), dim3(64 * CW), lds, st, P,
                      in, out, dt, dtp, part, nblocks, Rin, qn, stage);
 }
 
@@ -354,37 +364,37 @@ static inline int row_grid(const Params& P) {
   return (int)(((nblocks + 7) / 8) * 8);
 }
 
-template <int D, int N, int RX>
-static hipError_t launch_rk_t(const Params& P, int dir, int mode, int stage, bool fuse, const double* in,
+template <int D, int N, int RX, int PROF>
+static hipError_t launch_rk_p(const Params& P, int dir, int mode, int stage, bool fuse, const double* in,
                               double* out, const double* Rin, const double* qn, double dt, const double* dtp,
                               double* part, hipStream_t st) {
   if (dir == 0) {
     if (mode != M_RK_LAST) return hipErrorInvalidValue;
     if (P.bc[0] >= BC_REFLECTIVE) {
       if (fuse)
-        hipLaunchKernelGGL((sweep_row<D, N, RX, true, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P, in,
+        hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P, in,
                            out, dt, dtp, part, Rin, qn, stage);
       else
-        hipLaunchKernelGGL((sweep_row<D, N, RX, false, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P,
+        hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P,
                            in, out, dt, dtp, part, Rin, qn, stage);
       return hipGetLastError();
     }
     if (fuse)
-      hipLaunchKernelGGL((sweep_row<D, N, RX, true, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out, dt,
+      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out, dt,
                          dtp, part, Rin, qn, stage);
     else
-      hipLaunchKernelGGL((sweep_row<D, N, RX, false, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out,
+      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out,
                          dt, dtp, part, Rin, qn, stage);
     return hipGetLastError();
   }
   if constexpr (D >= 2) {
     if (dir == 1 && mode == M_RK_FIRST) {
-      launch_tile<D, N, RX, 1, false, M_RK_FIRST>(P, in, out, dt, dtp, part, st, nullptr, qn, stage);
+      launch_tile<D, N, RX, PROF, 1, false, M_RK_FIRST>(P, in, out, dt, dtp, part, st, nullptr, qn, stage);
       return hipGetLastError();
     }
     if constexpr (D == 3) {
       if (dir == 2 && mode == M_RK_MID) {
-        launch_tile<D, N, RX, 2, false, M_RK_MID>(P, in, out, dt, dtp, part, st, Rin, qn, stage);
+        launch_tile<D, N, RX, PROF, 2, false, M_RK_MID>(P, in, out, dt, dtp, part, st, Rin, qn, stage);
         return hipGetLastError();
       }
     }
@@ -392,43 +402,64 @@ static hipError_t launch_rk_t(const Params& P, int dir, int mode, int stage, boo
   return hipErrorInvalidValue;
 }
 
-template <int D, int N, int RX>
-static hipError_t launch_sweep_t(const Params& P, const double* in, double* out, double dt, const double* dtp,
+template <int D, int N, int RX, int PROF>
+static hipError_t launch_sweep_p(const Params& P, const double* in, double* out, double dt, const double* dtp,
                                  int dir, bool fuse, double* part, int S, hipStream_t st) {
   (void)S;
   const int block = 256;
   if (dir == 0) {
     const int grid = row_grid(P);
-    if (P.bc[0] >= BC_REFLECTIVE) {
-      if (fuse)
-        hipLaunchKernelGGL((sweep_row<D, N, RX, true, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in, out,
-                           dt, dtp, part, nullptr, nullptr, 0);
-      else
-        hipLaunchKernelGGL((sweep_row<D, N, RX, false, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in, out,
-                           dt, dtp, part, nullptr, nullptr, 0);
-      return hipGetLastError();
+    if constexpr (PROF != PROF_CALIB) {  // (those grids have no walls)
+      if (P.bc[0] >= BC_REFLECTIVE) {
+        if (fuse)
+          hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in,
+                             out, dt, dtp, part, nullptr, nullptr, 0);
+        else
+          hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in,
+                             out, dt, dtp, part, nullptr, nullptr, 0);
+        return hipGetLastError();
+      }
     }
     if (fuse)
-      hipLaunchKernelGGL((sweep_row<D, N, RX, true>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
+      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
                          nullptr, nullptr, 0);
     else
-      hipLaunchKernelGGL((sweep_row<D, N, RX, false>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
+      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
                          nullptr, nullptr, 0);
     return hipGetLastError();
   }
   if constexpr (D >= 2) {
     if (dir == 1) {
-      if (fuse) launch_tile<D, N, RX, 1, true>(P, in, out, dt, dtp, part, st);
-      else launch_tile<D, N, RX, 1, false>(P, in, out, dt, dtp, part, st);
+      if (fuse) launch_tile<D, N, RX, PROF, 1, true>(P, in, out, dt, dtp, part, st);
+      else launch_tile<D, N, RX, PROF, 1, false>(P, in, out, dt, dtp, part, st);
       return hipGetLastError();
     }
     if constexpr (D == 3) {
-      if (fuse) launch_tile<D, N, RX, 2, true>(P, in, out, dt, dtp, part, st);
-      else launch_tile<D, N, RX, 2, false>(P, in, out, dt, dtp, part, st);
+      if (fuse) launch_tile<D, N, RX, PROF, 2, true>(P, in, out, dt, dtp, part, st);
+      else launch_tile<D, N, RX, PROF, 2, false>(P, in, out, dt, dtp, part, st);
       return hipGetLastError();
     }
   }
   return hipErrorInvalidValue;
+}
+
+// the instance of the materials' profile
+template <int D, int N, int RX>
+static hipError_t launch_sweep_t(const Params& P, const double* in, double* out, double dt, const double* dtp,
+                                 int dir, bool fuse, double* part, int S, hipStream_t st) {
+  return by_profile<N, RX>(P, [&](auto prof) {
+    return launch_sweep_p<D, N, RX, decltype(prof)::value>(P, in, out, dt, dtp, dir, fuse, part, S, st);
+  });
+}
+
+template <int D, int N, int RX>
+static hipError_t launch_rk_t(const Params& P, int dir, int mode, int stage, bool fuse, const double* in,
+                              double* out, const double* Rin, const double* qn, double dt, const double* dtp,
+                              double* part, hipStream_t st) {
+  return by_profile<N, RX>(P, [&](auto prof) {
+    return launch_rk_p<D, N, RX, decltype(prof)::value>(P, dir, mode, stage, fuse, in, out, Rin, qn, dt, dtp, part,
+                                                        st);
+  });
 }
 
 }  // namespace dimp
