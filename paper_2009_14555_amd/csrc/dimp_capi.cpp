@@ -546,8 +546,11 @@ dimp_status rk_launch(dimp_ctx* h, int dir, int mode, int stage, bool fuse, cons
 // cylindrical geometric source, which needs the cell's radius) and the wave
 // speed of the result, where they are not fused into the last sweep
 dimp_status unfused_sources(dimp_ctx* h, double dt, const double* dtp) {
-  HIPCHECK(dimp::launch_sources(h->P, h->ndim, h->rxk(), h->buf[h->cur], dt, dtp, h->stream), "sources");
-  HIPCHECK(dimp::launch_wavespeed(h->P, h->ndim, h->rxk(), h->buf[h->cur], h->dsmax, h->stream), "wavespeed");
+  const dimp::DtReq* rq = h->req.dt ? &h->req : nullptr;
+  HIPCHECK(dimp::launch_sources_ws(h->P, h->ndim, h->rxk(), h->buf[h->cur], dt, dtp, h->dsmax, h->dpart, h->part_cap,
+                                   h->stream, rq),
+           "sources and wave speed");
+  h->req_served = h->req_served || rq;
   return DIMP_OK;
 }
 
@@ -1438,7 +1441,9 @@ dimp_status dimp_set_step_index(dimp_handle h, int64_t step) {
 
 static dimp_status ensure_smax(dimp_handle h) {
   if (!h->smax_valid) {
-    HIPCHECK(dimp::launch_wavespeed(h->P, h->ndim, h->rxk(), h->buf[h->cur], h->dsmax, h->stream), "wavespeed");
+    HIPCHECK(dimp::launch_wavespeed(h->P, h->ndim, h->rxk(), h->buf[h->cur], h->dsmax, h->dpart, h->part_cap,
+                                    h->stream),
+             "wavespeed");
     h->smax_valid = true;
   }
   return DIMP_OK;

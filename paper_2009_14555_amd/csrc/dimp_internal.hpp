@@ -102,8 +102,14 @@ hipError_t launch_cfl_dt(const Params& P, int D, unsigned long long* smax, doubl
 hipError_t launch_prim_to_cons(const Params& P, int D, int rx, const double* W, double* U, hipStream_t st);
 hipError_t launch_cons_to_prim(const Params& P, int D, int rx, const double* U, double* W, hipStream_t st);
 hipError_t launch_sources(const Params& P, int D, int rx, double* U, double dt, const double* dtp, hipStream_t st);
-hipError_t launch_wavespeed(const Params& P, int D, int rx, const double* U, unsigned long long* smax,
-                            hipStream_t st);
+// the source steps with the wave speed of the result, and the wave speed
+// alone: block slots in part (part_cap slots, then the reduction's scratch),
+// reduced into smax
+hipError_t launch_sources_ws(const Params& P, int D, int rx, double* U, double dt, const double* dtp,
+                             unsigned long long* smax, double* part, int64_t part_cap, hipStream_t st,
+                             const DtReq* req);
+hipError_t launch_wavespeed(const Params& P, int D, int rx, const double* U, unsigned long long* smax, double* part,
+                            int64_t part_cap, hipStream_t st);
 hipError_t launch_check(const Params& P, int D, int rx, const double* U, unsigned long long* nbad, hipStream_t st);
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t st);
 // a rest state given a velocity field (D arrays): momentum rho u, energy

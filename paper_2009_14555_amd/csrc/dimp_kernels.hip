@@ -8,6 +8,21 @@
 
 namespace dimp {
 
+__device__ __forceinline__ double nanmax(double a, double b) { return (b > a || b != b) ? b : a; }
+
+// the block's maximum of s (a NaN wins) into the block's slot of part
+template <int D>
+__device__ __forceinline__ void block_max_store(const double s[D], double* part) {
+  __shared__ double red[4][3];
+#pragma unroll
+  for (int k = 0; k < D; ++k) wave_max_store(s[k], &red[threadIdx.x >> 6][k]);
+  __syncthreads();
+  if (threadIdx.x < D) {
+    const int k = threadIdx.x;
+    part[(int64_t)blockIdx.x * 3 + k] = nanmax(nanmax(red[0][k], red[1][k]), nanmax(red[2][k], red[3][k]));
+  }
+}
+
 // ------------------------------------------------------ pointwise kernels
 template <int D, int N, int RX, int PROF>
 __global__ __launch_bounds__(256) void k_prim_to_cons(Params P, const double* __restrict__ W, double* __restrict__ U) {
@@ -76,14 +91,19 @@ __global__ __launch_bounds__(256) void k_cons_to_prim(Params P, const double* __
   }
 }
 
-template <int D, int N, int RX, int PROF>
-__global__ __launch_bounds__(256) void k_sources(Params P, double* __restrict__ U, double dt_arg,
-                                                const double* __restrict__ dtp) {
+// The source steps of every cell; with WS also the wave speed of the result,
+// one slot (3 doubles) per block.
+template <int D, int N, int RX, int PROF, bool WS>
+__device__ __forceinline__ void sources_cells(const Params& P, double* __restrict__ U, double dt_arg,
+                                              const double* __restrict__ dtp, double* __restrict__ part) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
   assume_profile<N, RX, PROF>(P);
   const int64_t nc = P.ncell;
   const double dt = dtp ? dtp[0] : dt_arg;
+  double s[D];
+#pragma unroll
+  for (int k = 0; k < D; ++k) s[k] = 0.0;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc; c += (int64_t)gridDim.x * blockDim.x) {
     double u[F];
 #pragma unroll
@@ -93,12 +113,34 @@ __global__ __launch_bounds__(256) void k_sources(Params P, double* __restrict__ 
     if (D == 2 && P.geom) geom_cell<D, N, RX>(P, u, P.r_lo + ((double)(c % P.n[0]) + 0.5) * P.dx[0], dt);
 #pragma unroll
     for (int f = 0; f < F; ++f) U[f * nc + c] = u[f];
+    if (WS) {
+      double sc[D];
+      wavespeed_cell<D, N, RX>(P, u, sc);
+#pragma unroll
+      for (int k = 0; k < D; ++k) s[k] = nanmax(s[k], sc[k]);
+    }
   }
+  if (WS) block_max_store<D>(s, part);
 }
 
 template <int D, int N, int RX, int PROF>
-__global__ __launch_bounds__(256) void k_wavespeed(Params P, const double* __restrict__ U,
-                                                   unsigned long long* __restrict__ smax) {
+__global__ __launch_bounds__(256) void k_sources(Params P, double* __restrict__ U, double dt_arg,
+                                                 const double* __restrict__ dtp) {
+  sources_cells<D, N, RX, PROF, false>(P, U, dt_arg, dtp, nullptr);
+}
+
+template <int D, int N, int RX, int PROF>
+__global__ __launch_bounds__(256) void k_sources_ws(Params P, double* __restrict__ U, double dt_arg,
+                                                    const double* __restrict__ dtp, double* __restrict__ part) {
+  sources_cells<D, N, RX, PROF, true>(P, U, dt_arg, dtp, part);
+}
+
+// One slot per block, reduced afterwards (pushing every wave's maximum into
+// the three words with an atomic took 41 us on 288k cells and 124 us on 4.2M,
+// the waves colliding on the words, and 87 us on 288k cells once they computed
+// faster; with slots 4.2M cells take 72 us and the reduction 9).
+template <int D, int N, int RX, int PROF>
+__global__ __launch_bounds__(256) void k_wavespeed(Params P, const double* __restrict__ U, double* __restrict__ part) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
   assume_profile<N, RX, PROF>(P);
@@ -112,10 +154,9 @@ __global__ __launch_bounds__(256) void k_wavespeed(Params P, const double* __res
     for (int f = 0; f < F; ++f) u[f] = U[f * nc + c];
     wavespeed_cell<D, N, RX>(P, u, sc);
 #pragma unroll
-    for (int k = 0; k < D; ++k) s[k] = (sc[k] > s[k] || sc[k] != sc[k]) ? sc[k] : s[k];
+    for (int k = 0; k < D; ++k) s[k] = nanmax(s[k], sc[k]);
   }
-#pragma unroll
-  for (int k = 0; k < D; ++k) wave_max_atomic(s[k], smax + k);
+  block_max_store<D>(s, part);
 }
 
 template <int D, int N, int RX, int PROF>
@@ -205,14 +246,16 @@ __global__ void k_cfl_dt(unsigned long long* __restrict__ smax, double cfl, doub
 // a NaN wins) and, when req.dt is set, turns them into the next step's dt by
 // the k_cfl_dt rule.  (One launch whose last block, found by a ticket counter,
 // does the second stage took 24 us at 2048^2 against 9.5 us for the two:
-// 288 returning atomics on one word.)
-__device__ __forceinline__ double nanmax(double a, double b) { return (b > a || b != b) ? b : a; }
+// 288 returning atomics on one word.)  Up to REDUCE_ONE slots the second
+// stage, one block of 1024 threads, reads the slots themselves.
+constexpr int64_t REDUCE_ONE = 2048;
 
 template <bool FINAL>
-__global__ __launch_bounds__(256) void k_reduce_smax(const double* __restrict__ part, int64_t nslots, int64_t chunk,
+__global__ __launch_bounds__(FINAL ? 1024 : 256) void k_reduce_smax(const double* __restrict__ part, int64_t nslots, int64_t chunk,
                                                      int D, double* __restrict__ out,
                                                      unsigned long long* __restrict__ smax, DtReq req) {
-  __shared__ double red[3][4];
+  constexpr int NW = FINAL ? 16 : 4;
+  __shared__ double red[3][NW];
   const int64_t lo = (int64_t)blockIdx.x * chunk;
   const int64_t hi = lo + chunk < nslots ? lo + chunk : nslots;
   double m[3] = {0.0, 0.0, 0.0};
@@ -236,7 +279,9 @@ __global__ __launch_bounds__(256) void k_reduce_smax(const double* __restrict__ 
   if (threadIdx.x == 0) {
     double s[3];
     for (int k = 0; k < 3; ++k) {
-      const double v = nanmax(nanmax(red[k][0], red[k][1]), nanmax(red[k][2], red[k][3]));
+      double v = red[k][0];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) v = nanmax(v, red[k][q]);
       s[k] = (k < D) ? v : 0.0;
       smax[k] = (k < D) ? (unsigned long long)__double_as_longlong(v) : 0ull;
     }
@@ -285,12 +330,17 @@ int64_t sweep_slots(const Params& P, int D, int dir) {
 
 hipError_t launch_reduce_smax(const double* part, int64_t nslots, int D, double* scratch,
                               unsigned long long* smax, hipStream_t st, const DtReq* req) {
+  const DtReq none{};
+  if (nslots <= REDUCE_ONE) {
+    hipLaunchKernelGGL(k_reduce_smax<true>, dim3(1), dim3(1024), 0, st, part, nslots, nslots, D, nullptr, smax,
+                       req ? *req : none);
+    return hipGetLastError();
+  }
   const int64_t nb = reduce_smax_blocks(nslots);
   const int64_t chunk = (nslots + nb - 1) / nb;
-  const DtReq none{};
   hipLaunchKernelGGL(k_reduce_smax<false>, dim3((unsigned)nb), dim3(256), 0, st, part, nslots, chunk, D, scratch,
                      smax, none);
-  hipLaunchKernelGGL(k_reduce_smax<true>, dim3(1), dim3(256), 0, st, scratch, nb, nb, D, nullptr, smax,
+  hipLaunchKernelGGL(k_reduce_smax<true>, dim3(1), dim3(1024), 0, st, scratch, nb, nb, D, nullptr, smax,
                      req ? *req : none);
   return hipGetLastError();
 }
@@ -342,6 +392,12 @@ hipError_t launch_cons_to_prim(const Params& P, int D, int rx, const double* U, 
   return hipGetLastError();
 }
 
+// blocks of a pointwise kernel that leaves one wave-speed slot each
+static int64_t slot_blocks(const Params& P, int64_t part_cap) {
+  const int64_t nb = (P.ncell + 255) / 256;
+  return nb < part_cap ? nb : part_cap;
+}
+
 hipError_t launch_sources(const Params& P, int D, int rx, double* U, double dt, const double* dtp,
                           hipStream_t st) {
   const int grid = grid_for(P.ncell, 256);
@@ -349,13 +405,21 @@ hipError_t launch_sources(const Params& P, int D, int rx, double* U, double dt, 
   return hipGetLastError();
 }
 
-hipError_t launch_wavespeed(const Params& P, int D, int rx, const double* U, unsigned long long* smax,
-                            hipStream_t st) {
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, smax, 3);
-  const int64_t want = P.ncell < 256LL * 2048 ? P.ncell : 256LL * 2048;
-  const int grid = grid_for(want, 256);
-  DIMP_DISPATCH(D, rx, k_wavespeed, dim3(grid), dim3(256), 0, st, P, U, smax);
-  return hipGetLastError();
+hipError_t launch_sources_ws(const Params& P, int D, int rx, double* U, double dt, const double* dtp,
+                             unsigned long long* smax, double* part, int64_t part_cap, hipStream_t st,
+                             const DtReq* req) {
+  const int64_t nb = slot_blocks(P, part_cap);
+  DIMP_DISPATCH(D, rx, k_sources_ws, dim3((unsigned)nb), dim3(256), 0, st, P, U, dt, dtp, part);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_reduce_smax(part, nb, D, part + 3 * part_cap, smax, st, req);
+}
+
+hipError_t launch_wavespeed(const Params& P, int D, int rx, const double* U, unsigned long long* smax, double* part,
+                            int64_t part_cap, hipStream_t st) {
+  const int64_t nb = slot_blocks(P, part_cap);
+  DIMP_DISPATCH(D, rx, k_wavespeed, dim3((unsigned)nb), dim3(256), 0, st, P, U, part);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_reduce_smax(part, nb, D, part + 3 * part_cap, smax, st);
 }
 
 hipError_t launch_check(const Params& P, int D, int rx, const double* U, unsigned long long* nbad, hipStream_t st) {

@@ -789,23 +789,6 @@ __device__ __forceinline__ void epilogue_cell(const Params& P, double* U, double
 }
 
 // --------------------------------------------------- wave max reduction
-// Non-negative doubles order like their bit patterns (a NaN, positive here,
-// orders above every finite value).  The wave maximum is pushed with an
-// atomic only when it exceeds the value last seen at the destination: the
-// destination only grows, so a stale read can only cause an extra atomic.
-__device__ __forceinline__ void wave_max_atomic(double v, unsigned long long* dst) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double o = __shfl_xor(v, off, 64);
-    v = (o > v || o != o) ? o : v;
-  }
-  if ((threadIdx.x & 63) == 0) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned long long seen = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (b > seen) atomicMax(dst, b);
-  }
-}
-
 // The wave maximum of v written by lane 0 to its own slot (no atomics: one
 // slot per wave, reduced afterwards in a fixed order).
 __device__ __forceinline__ void wave_max_store(double v, double* dst) {
@@ -823,8 +806,11 @@ __device__ __forceinline__ void wave_max_store(double v, double* dst) {
 // the mirror image of cell -1 is cell 0)
 __device__ __forceinline__ int64_t bc_map(int64_t i, int64_t n, int bc) {
   if (bc == BC_PERIODIC) {
-    i %= n;
-    return i < 0 ? i + n : i;
+    // positions lie within a wave's width of the axis: a turn or two, where a
+    // 64-bit remainder is some 100 instructions at every call
+    while (i < 0) i += n;
+    while (i >= n) i -= n;
+    return i;
   }
   return i < 0 ? 0 : (i > n - 1 ? n - 1 : i);
 }
