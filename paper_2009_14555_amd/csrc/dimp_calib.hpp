@@ -656,8 +656,8 @@ __device__ __forceinline__ void epilogue_cell(const Params& P, double* U, double
 
 // The stages of one sweep for a wave holding one cell per lane (as lane_face
 // and lane_sweep of dimp_lane.hpp)
-template <int DIR, class LoadU>
-__device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const double (&phi_t)[3][3], double nu,
+template <int DIR, class LoadU, class PhiAt>
+__device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, PhiAt&& phi_at, double nu,
                                           FaceV& fa, double& irho0, bool wall) {
   double W[F];
   double rc2;
@@ -678,10 +678,11 @@ __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const
   }
   // phi stencil along the sweep axis for the interface normal (all lanes
   // shuffle; the normal itself is only evaluated in mixed cells)
-  double sm[3][3], sp[3][3];
+  double phi_t[3][3], sm[3][3], sp[3][3];
   if (P.thinc) {
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
+      phi_t[b][1] = (b == 1) ? W[0] : phi_at(b, 1);
       sm[b][1] = from_left(phi_t[b][1]);
       sp[b][1] = from_right(phi_t[b][1]);
     }
@@ -716,12 +717,12 @@ __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const
   face_flux<DIR>(P, WRm, WL, fa, wall);
 }
 
-template <int DIR, bool FUSE, class LoadU>
-__device__ __forceinline__ void lane_sweep(const Params& P, LoadU&& load_U, const double (&phi_t)[3][3], double nu,
+template <int DIR, bool FUSE, class LoadU, class PhiAt>
+__device__ __forceinline__ void lane_sweep(const Params& P, LoadU&& load_U, PhiAt&& phi_at, double nu,
                                            double dt, bool writer, double* Un, double* s, bool wall = false) {
   FaceV fa, fb;
   double irho0;
-  lane_face<DIR>(P, load_U, phi_t, nu, fa, irho0, wall);
+  lane_face<DIR>(P, load_U, phi_at, nu, fa, irho0, wall);
 #pragma unroll
   for (int f = 0; f < F; ++f) fb.F[f] = from_right(fa.F[f]);
   fb.ustar = from_right(fa.ustar);

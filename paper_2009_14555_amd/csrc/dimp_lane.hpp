@@ -6,13 +6,20 @@ namespace dimp {
 
 // THINC candidates of every stored volume fraction of the lane's cell, all
 // with the normal of the first, and the BVD choice on them.
-template <int D, int N, int RX, int DIR>
+template <int D, int N, int RX, int DIR, class PhiAt>
 __device__ __forceinline__ void lane_bvd(const Params& P, const double* Wm, const double* W, const double* Wp,
-                                         const double (&phi_t)[3][3], double* WL, double* WR, double* jump) {
-  // phi stencil along the sweep axis for the interface normal (all lanes
+                                         PhiAt&& phi_at, double* WL, double* WR, double* jump) {
+  // phi_1 around the lane's cell for the interface normal (all lanes load and
   // shuffle; the normal itself is only evaluated in mixed cells)
-  double sm[3][3], sp[3][3];
+  double phi_t[3][3], sm[3][3], sp[3][3];
   if (D >= 2) {
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (D == 2 && c != 1) continue;
+        phi_t[b][c] = (b == 1 && c == 1) ? W[0] : phi_at(b, c);
+      }
 #pragma unroll
     for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -73,9 +80,10 @@ __device__ __forceinline__ void lane_bvd(const Params& P, const double* Wm, cons
 // ------------------------------------------------- lane-per-cell sweep
 // The stages of one sweep for a wave whose 64 lanes hold 64 consecutive cells
 // along the sweep axis (3 halo cells on each side, lanes 3..60 are written).
-// U: the lane's conserved state; phi_t[b][c]: phi_1 of the lane's cell at
-// transverse offsets (b, c) in {-1,0,1}^2 (2-D uses c = 1 only), with the
-// offset along the sweep axis supplied by shuffles.
+// U: the lane's conserved state; phi_at(b, c): phi_1 of the lane's cell at
+// transverse offsets (b - 1, c - 1) in {-1,0,1}^2 (2-D uses c = 1 only),
+// called in waves that hold a mixed cell, with the offset along the sweep axis
+// supplied by shuffles.
 // U is read twice through load_U (for the primitive state and for the
 // update) rather than kept in registers across the face computation.
 // RK = false: the split MUSCL-Hancock sweep, Un = the updated state (and, with
@@ -87,8 +95,8 @@ __device__ __forceinline__ void lane_bvd(const Params& P, const double* Wm, cons
 // lane's cell (fa; wall: that face is a reflective wall), and the cell's
 // 1 / (sum of partial densities); it depends on the cells 3 to the left and
 // 2 to the right.  lane_sweep adds the update.
-template <int D, int N, int RX, int DIR, bool RK, class LoadU>
-__device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const double (&phi_t)[3][3], double nu,
+template <int D, int N, int RX, int DIR, bool RK, class LoadU, class PhiAt>
+__device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, PhiAt&& phi_at, double nu,
                                           FaceV<D, N, RX>& fa, double& irho0, bool wall) {
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
@@ -120,7 +128,7 @@ __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const
       double num, den;
       mixed = mixed || thinc_mixed(P, Wm[l], W[l], Wp[l], num, den);
     }
-    if (__builtin_amdgcn_ballot_w64(mixed) != 0) lane_bvd<D, N, RX, DIR>(P, Wm, W, Wp, phi_t, WL, WR, jump);
+    if (__builtin_amdgcn_ballot_w64(mixed) != 0) lane_bvd<D, N, RX, DIR>(P, Wm, W, Wp, phi_at, WL, WR, jump);
   }
   if (!RK) edges_half_step<D, N, RX, DIR>(P, W, jump, irho0, rc2, nu, WL, WR);
   // face on the left of this cell: right edge of the left neighbour | my left edge
@@ -130,13 +138,13 @@ __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, const
   face_flux<D, N, RX, DIR>(P, WRm, WL, fa, wall);
 }
 
-template <int D, int N, int RX, int DIR, bool FUSE, bool RK = false, class LoadU>
-__device__ __forceinline__ void lane_sweep(const Params& P, LoadU&& load_U, const double (&phi_t)[3][3], double nu,
+template <int D, int N, int RX, int DIR, bool FUSE, bool RK = false, class LoadU, class PhiAt>
+__device__ __forceinline__ void lane_sweep(const Params& P, LoadU&& load_U, PhiAt&& phi_at, double nu,
                                            double dt, bool writer, double* Un, double* s, bool wall = false) {
   constexpr int F = Lay<D, N, RX>::F;
   FaceV<D, N, RX> fa, fb;
   double irho0;
-  lane_face<D, N, RX, DIR, RK>(P, load_U, phi_t, nu, fa, irho0, wall);
+  lane_face<D, N, RX, DIR, RK>(P, load_U, phi_at, nu, fa, irho0, wall);
 #pragma unroll
   for (int f = 0; f < F; ++f) fb.F[f] = from_right(fa.F[f]);
   fb.ustar = from_right(fa.ustar);

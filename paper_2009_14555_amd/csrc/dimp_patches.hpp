@@ -121,16 +121,13 @@ __global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX>())) void psweep_row(
       for (int f = 0; f < F; ++f) U[f] = stash[f * 64 * WPB + threadIdx.x];
     }
   };
-  double phi_t[3][3];
-  if (P.thinc) {
-    // rows j-1, j+1 clamped into the patch (stored ghost values are never read)
-    phi_t[0][1] = in[j > 0 ? cell - pitch : cell];
-    phi_t[1][1] = in[cell];
-    phi_t[2][1] = in[j < g.ny - 1 ? cell + pitch : cell];
-  }
+  // rows j-1, j+1 clamped into the patch (stored ghost values are never read)
+  auto phi_at = [&](int b, int) -> double {
+    return in[b == 0 ? (j > 0 ? cell - pitch : cell) : (j < g.ny - 1 ? cell + pitch : cell)];
+  };
   const bool writer = (q >= SEG_HALO) && (q < ncl + SEG_HALO);
   double Un[F], s[PD];
-  lane_sweep<PD, N, RX, 0, FUSE>(P, load_U, phi_t, nu, dt, writer, Un, s);
+  lane_sweep<PD, N, RX, 0, FUSE>(P, load_U, phi_at, nu, dt, writer, Un, s);
   if (writer) {
 #pragma unroll
     for (int f = 0; f < F; ++f) write_with_ghosts(g, out, E, f, x, j, Un[f]);
@@ -148,10 +145,8 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
   constexpr int F = Lay<PD, N, RX>::F;
   assume_profile<N, RX, PROF>(P);
   constexpr int PITCH = CW + 1;
-  constexpr int PP = CW + 2;
   extern __shared__ double lds[];
   double* tileU = lds;
-  double* tileP = lds + F * 64 * PITCH;
   const int64_t t = xcd_block(blockIdx.x, gridDim.x);
   if (t >= nwork) return;  // whole block: a work item is one tile
   const double dt = dtp ? dtp[0] : dt_arg;
@@ -174,36 +169,25 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
 #pragma unroll
     for (int f = 0; f < F; ++f) tileU[(f * 64 + r) * PITCH + c] = in[f * E + cell];
   }
-  if (P.thinc) {
-    for (int qq = tid; qq < 64 * PP; qq += 64 * CW) {
-      const int rr = qq / PP, cc = qq % PP;
-      const int4 sg = segment_of(wl.seg, sb, se, rr);
-      const PatchGeo g = geo[sg.x];
-      const int xx = sg.y + cc - 1, jj = sg.z + rr - (sg.w & 255) - SEG_HALO;
-      const int xc = xx < 0 ? 0 : (xx > g.nx - 1 ? g.nx - 1 : xx);
-      const int jc = jj < 0 ? 0 : (jj > g.ny - 1 ? g.ny - 1 : jj);
-      tileP[rr * PP + cc] = in[g.off + (jc + PATCH_GHOST) * (int64_t)(g.nx + 2 * PATCH_GHOST) + PATCH_GHOST + xc];
-    }
-  }
   __syncthreads();
   auto load_U = [&](double* U) {
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int f = 0; f < F; ++f) U[f] = tileU[(f * 64 + lane) * PITCH + w];
   };
-  double phi_t[3][3];
-  if (P.thinc) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b) phi_t[b][1] = tileP[lane * PP + w + b];
-  }
-  bool writer;
-  {
-    const int4 sl = segment_of(wl.seg, sb, se, lane);
-    const int ql = lane - (sl.w & 255);
-    writer = (ql >= SEG_HALO) && (ql < (sl.w >> 8) + SEG_HALO) && (sl.y + w < geo[sl.x].nx);
-  }
+  const int4 sl = segment_of(wl.seg, sb, se, lane);
+  const PatchGeo gl = geo[sl.x];
+  const int ql = lane - (sl.w & 255);
+  const bool writer = (ql >= SEG_HALO) && (ql < (sl.w >> 8) + SEG_HALO) && (sl.y + w < gl.nx);
+  // columns x-1, x+1 clamped into the patch
+  auto phi_at = [&](int b, int) -> double {
+    const int xx = sl.y + w + b - 1, jj = sl.z + ql - SEG_HALO;
+    const int xc = xx < 0 ? 0 : (xx > gl.nx - 1 ? gl.nx - 1 : xx);
+    const int jc = jj < 0 ? 0 : (jj > gl.ny - 1 ? gl.ny - 1 : jj);
+    return in[gl.off + (jc + PATCH_GHOST) * (int64_t)(gl.nx + 2 * PATCH_GHOST) + PATCH_GHOST + xc];
+  };
   double Un[F], s[PD];
-  lane_sweep<PD, N, RX, 1, FUSE>(P, load_U, phi_t, nu, dt, writer, Un, s);
+  lane_sweep<PD, N, RX, 1, FUSE>(P, load_U, phi_at, nu, dt, writer, Un, s);
   __syncthreads();
   if (writer) {
 #pragma unroll
@@ -222,7 +206,7 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
 
 template <int N, int RX, int CW>
 size_t tile_lds_bytes() {
-  return sizeof(double) * (Lay<PD, N, RX>::F * 64 * (CW + 1) + 64 * (CW + 2));
+  return sizeof(double) * (Lay<PD, N, RX>::F * 64 * (CW + 1));
 }
 
 // one sweep of a patch set with N materials and the RX layout (the

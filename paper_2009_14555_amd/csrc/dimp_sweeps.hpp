@@ -25,15 +25,17 @@ namespace dimp {
 #ifndef TILE_COLUMNS
 #define TILE_COLUMNS 4
 #endif
-// waves per SIMD the sweep kernels are built for (launch bound): three in 1-D
-// and 2-D (<= 168 VGPRs, no or a few spilled dwords); the 3-D sweeps (nine
-// stretch entries, up to 17 fields) need 200-250 VGPRs and run two without
-// spilling, and so do the sweeps of a JWL mixture (its Newton split inlined)
-// and of three materials (two more fields and a second set of THINC/BVD
-// candidates: 30-90 spilled bytes a lane at three waves)
-template <int D, int N, int RX, bool FUSE>
+// waves per SIMD the sweep kernels are built for (launch bound): four where
+// the state fits 128 VGPRs, the 1-D and 2-D instances of a material profile
+// without a history slot (124-126; at five waves they spill 120 bytes a lane);
+// three (168) with a history slot (134-167) and for the general and calibrated
+// instances; the 3-D sweeps (nine stretch entries, up to 17 fields) need
+// 185-200 VGPRs and run two without spilling, and so do the sweeps of a JWL
+// mixture (its Newton split inlined) and of three materials
+template <int D, int N, int RX, int PROF, bool FUSE>
 constexpr int sweep_waves() {
-  return (D == 3 || RX == 2 || N > 2) ? 2 : 3;
+  if (D == 3 || RX == 2 || N > 2) return 2;
+  return (RX == 0 && PROF != PROF_ANY && PROF != PROF_CALIB) ? 4 : 3;
 }
 
 // Output modes of the sweep kernels.  M_SPLIT: the split sweep, out = the
@@ -55,7 +57,7 @@ __device__ __forceinline__ double rk_b(int stage) { return stage == 1 ? 1.0 : st
 // Sweep along x.  Each wave: one 64-cell segment of one row, loaded and
 // stored straight from HBM (512-byte rows per field).
 template <int D, int N, int RX, int PROF, bool FUSE, int MODE = M_SPLIT, bool WALL = false>
-__global__ __launch_bounds__(256, (sweep_waves<D, N, RX, FUSE>())) void sweep_row(Params P, const double* __restrict__ in, double* __restrict__ out,
+__global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE>())) void sweep_row(Params P, const double* __restrict__ in, double* __restrict__ out,
                                                   double dt_arg, const double* __restrict__ dtp,
                                                   double* __restrict__ part, const double* __restrict__ Rin,
                                                   const double* qn, int stage) {
@@ -105,33 +107,22 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, FUSE>())) void sweep_ro
       for (int f = 0; f < F; ++f) U[f] = stash[f * 256 + threadIdx.x];
     }
   };
-  double phi_t[3][3];
-  if (P.thinc && D >= 2) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (D == 2 && c != 1) continue;
-        if (b == 1 && c == 1) {
-          phi_t[b][c] = in[cell];
-          continue;
-        }
-        const int64_t yy = bc_map(yj + b - 1, ny, P.bc[1]);
-        const int64_t zz = (D == 3) ? bc_map(zk + c - 1, nz, P.bc[2]) : 0;
-        phi_t[b][c] = in[(zz * ny + yy) * nx + xm];
-      }
-  }
+  auto phi_at = [&](int b, int c) -> double {
+    const int64_t yy = bc_map(yj + b - 1, ny, P.bc[1]);
+    const int64_t zz = (D == 3) ? bc_map(zk + c - 1, nz, P.bc[2]) : 0;
+    return in[(zz * ny + yy) * nx + xm];
+  };
   const bool writer = (lane >= 3) && (lane < 61) && (x < nx);
   // the face on this lane's left is a reflective wall
   const bool wall = WALL && ((x == 0 && (P.bc[0] == BC_REFLECTIVE || P.bc[0] == BC_AXIS)) ||
                              (x == nx && P.bc[0] == BC_REFLECTIVE));
   double Un[F], s[D];
   if constexpr (PROF == PROF_CALIB) {
-    calib::lane_sweep<0, FUSE>(P, load_U, phi_t, dt / P.dx[0], dt, writer, Un, s, wall);
+    calib::lane_sweep<0, FUSE>(P, load_U, phi_at, dt / P.dx[0], dt, writer, Un, s, wall);
   } else if (MODE == M_SPLIT) {
-    lane_sweep<D, N, RX, 0, FUSE>(P, load_U, phi_t, dt * P.idx[0], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, 0, FUSE>(P, load_U, phi_at, dt * P.idx[0], dt, writer, Un, s, wall);
   } else {
-    lane_sweep<D, N, RX, 0, false, true>(P, load_U, phi_t, P.idx[0], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, 0, false, true>(P, load_U, phi_at, P.idx[0], dt, writer, Un, s, wall);
     if (writer) {
       const double b = rk_b(stage);
       if (D > 1) {
@@ -176,18 +167,23 @@ struct TileGeom {
   // per-wave column reads (16 lanes = 16 rows of one column)
   static constexpr int RS = 16 / CW;
   __device__ static constexpr int at(int f, int r, int c) { return (f * 64 + r) * CW + (c ^ ((r / RS) & (CW - 1))); }
-  static constexpr int PP = CW + 3;  // phi tile row: CW + 2 columns (x halo of one), padded to an odd pitch
   // the results get a tile of their own (no barrier between the last read of
   // the input tile and the first write of a result) where both fit in 64 KB
-  // of LDS; otherwise they overwrite the input tile after a barrier
-  template <int F, int NPL>
-  static constexpr bool separate() { return (2 * F * 64 * CW + NPL * 64 * PP) * 8 <= 65536; }
-  template <int F, int NPL>
-  static constexpr int lds_doubles() { return (separate<F, NPL>() ? 2 : 1) * F * 64 * CW + NPL * 64 * PP; }
+  // of LDS, in as many blocks as the CU's registers hold (WAVES per SIMD, 160
+  // KB); otherwise they overwrite the input tile after a barrier
+  template <int F, int WAVES>
+  static constexpr bool separate() {
+    constexpr int bytes = 2 * F * 64 * CW * 8;
+    return bytes <= 65536 && bytes * (4 * WAVES / CW) <= 163840;
+  }
+  template <int F, int WAVES>
+  static constexpr int lds_doubles() {
+    return (separate<F, WAVES>() ? 2 : 1) * F * 64 * CW;
+  }
 };
 
 template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false>
-__global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void sweep_tile(Params P, const double* __restrict__ in,
+__global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, PROF, FUSE>())) void sweep_tile(Params P, const double* __restrict__ in,
                                                        double* __restrict__ out, double dt_arg,
                                                        const double* __restrict__ dtp,
                                                        double* __restrict__ part, int64_t nblocks,
@@ -196,14 +192,11 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void swee
   using L = Lay<D, N, RX>;
   using G = TileGeom<CW>;
   constexpr int F = L::F;
-  constexpr int PP = G::PP;
   assume_profile<N, RX, PROF>(P);
-  constexpr int NPL = (D == 3) ? 3 : 1;      // phi planes along the other transverse axis
-  constexpr bool SEP = G::template separate<F, NPL>();
+  constexpr bool SEP = G::template separate<F, sweep_waves<D, N, RX, PROF, FUSE>()>();
   extern __shared__ double lds[];
   double* tileU = lds;                               // [F][64][CW] input state
   double* tileO = SEP ? lds + F * 64 * CW : tileU;   // [F][64][CW] results
-  double* tileP = lds + (SEP ? 2 : 1) * F * 64 * CW; // [NPL][64][PP]
   const double dt = dtp ? dtp[0] : dt_arg;
 
   // XCD-aware logical block index
@@ -240,17 +233,6 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void swee
         if (mirror_odd<D, N, RX>(f, DIR)) tileU[G::at(f, r, c)] = -tileU[G::at(f, r, c)];
     }
   }
-  if (P.thinc && D >= 2) {
-    for (int t = tid; t < 64 * (CW + 2) * NPL; t += 64 * CW) {
-      const int pl = t / (64 * (CW + 2));
-      const int rem = t - pl * 64 * (CW + 2);
-      const int r = rem / (CW + 2), c = rem % (CW + 2);
-      const int64_t xx = bc_map(x0 + c - 1, nx, P.bc[0]);
-      const int64_t jj = bc_map(j0 + r, nm, P.bc[DIR]);
-      const int64_t oo = (D == 3) ? bc_map(o + pl - 1, no, P.bc[oa]) : 0;
-      tileP[(pl * 64 + r) * PP + c] = in[xx * sx + jj * sm + oo * so];
-    }
-  }
   __syncthreads();
   const int w = tid >> 6, lane = tid & 63;
   auto load_U = [&](double* U) {
@@ -259,17 +241,12 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void swee
     for (int f = 0; f < F; ++f) U[f] = tileU[G::at(f, lane, w)];
   };
   // transverse phi offsets: b along x, c along the other axis (3-D)
-  double phi_t[3][3];
-  if (P.thinc && D >= 2) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if (D == 2 && c != 1) continue;
-        const int pl = (D == 3) ? c : 0;
-        phi_t[b][c] = tileP[(pl * 64 + lane) * PP + w + b];
-      }
-  }
+  auto phi_at = [&](int b, int c) -> double {
+    const int64_t xx = bc_map(x0 + w + b - 1, nx, P.bc[0]);
+    const int64_t jj = bc_map(j0 + lane, nm, P.bc[DIR]);
+    const int64_t oo = (D == 3) ? bc_map(o + c - 1, no, P.bc[oa]) : 0;
+    return in[xx * sx + jj * sm + oo * so];
+  };
   // lane_sweep orders the transverse offsets over the other two axes in
   // increasing axis order: for DIR = 1 that is (x, z), for DIR = 2 (x, y)
   const bool writer = (lane >= 3) && (lane < 61) && (j0 + lane < nm) && (x0 + w < nx);
@@ -278,11 +255,11 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, FUSE>())) void swee
                              (jl == nm && P.bc[DIR] == BC_REFLECTIVE));
   double Un[F], s[D];
   if constexpr (PROF == PROF_CALIB)
-    calib::lane_sweep<DIR, FUSE>(P, load_U, phi_t, dt / P.dx[DIR], dt, writer, Un, s, wall);
+    calib::lane_sweep<DIR, FUSE>(P, load_U, phi_at, dt / P.dx[DIR], dt, writer, Un, s, wall);
   else if (MODE == M_SPLIT)
-    lane_sweep<D, N, RX, DIR, FUSE>(P, load_U, phi_t, dt * P.idx[DIR], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, DIR, FUSE>(P, load_U, phi_at, dt * P.idx[DIR], dt, writer, Un, s, wall);
   else
-    lane_sweep<D, N, RX, DIR, false, true>(P, load_U, phi_t, P.idx[DIR], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, DIR, false, true>(P, load_U, phi_at, P.idx[DIR], dt, writer, Un, s, wall);
   if (MODE == M_RK_FIRST && writer) {
     // q - dt D_y(q) (the input tile still holds q)
     double U[F];
@@ -345,7 +322,7 @@ static void launch_tile(const Params& P, const double* in, double* out, double d
   const int64_t no = (D == 3) ? P.n[oa] : 1;
   const int64_t nblocks = ((P.n[0] + CW - 1) / CW) * no * ((P.n[DIR] + 57) / 58);
   const int64_t grid = ((nblocks + 7) / 8) * 8;
-  const size_t lds = sizeof(double) * TileGeom<CW>::template lds_doubles<L::F, (D == 3) ? 3 : 1>();
+  const size_t lds = sizeof(double) * TileGeom<CW>::template lds_doubles<L::F, sweep_waves<D, N, RX, PROF, FUSE>()>();
   if constexpr (PROF != PROF_CALIB) {  // (those grids have no walls)
     if (P.bc[DIR] >= BC_REFLECTIVE) {
       hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE, true>), dim3((unsigned)grid), dim3(64 * CW),
