@@ -315,8 +315,12 @@ void rebuild_params(dimp_ctx* h) {
     P.rx.igFig = g[12];
     P.rx.igFG1 = g[13];
     P.rx.igFG2 = g[14];
-    P.rx.ig_rho0 = g[15];
-    P.rx.ig_punit = g[16];
+    P.rx.ig_irho0 = 1.0 / g[15];
+    P.rx.ig_ipunit = 1.0 / g[16];
+    for (int k = 0; k < 8; ++k) {
+      const double e = g[4 + k];  // b, c, d, e, g, x, y, z
+      P.rx.ign[k] = (e == std::floor(e) && e >= 1.0 && e <= 8.0) ? (int)e : 0;
+    }
   }
   P.prof = material_profile(P, h->nmat, h->hist());
 }

@@ -56,7 +56,8 @@ struct RxP {
   // exponents b, c, d, e, g, x, y, z, threshold a, switches F_ig, F_G1,
   // F_G2, the reference density and the pressure unit
   double igI, igG1, igG2, ig_a, ig_b, ig_c, ig_d, ig_e, ig_g, ig_x, ig_y, ig_z;
-  double igFig, igFG1, igFG2, ig_rho0, ig_punit;
+  double igFig, igFG1, igFG2, ig_irho0, ig_ipunit;  // (the inverses of the reference density and unit)
+  int ign[8];  // b, c, d, e, g, x, y, z where they are small whole numbers, else 0
 };
 
 // materials the kernels are built for: two or three (the layouts are generic
@@ -251,6 +252,40 @@ __device__ __forceinline__ double fsqrt(double x) {
   const double g = x * y;
   const double r = fma(-g, y, 1.0);
   return fma(g, r * fma(0.375, r, 0.5), g);
+}
+
+// e^x for the reference curves (x <= 0 there): x = n ln2 + r, |r| <= ln2/2, the
+// Taylor series of e^r to the 13th power (truncation 4e-18), times 2^n.  20
+// instructions where the library function takes 40 with its range checks; a
+// JWL split evaluates four per trial.  It underflows to 0 (x above
+// -1e30), overflows to infinity, and keeps NaN.
+__device__ __forceinline__ double exp_curve(double x) {
+  const double n = rint(x * 0x1.71547652b82fep0);  // 1/ln2
+  double r = fma(n, -0x1.62e42fefa39efp-1, x);     // ln2
+  r = fma(n, -0x1.abc9e3b39803fp-56, r);           // ln2 less its double
+  double p = 1.0 / 6227020800.0;
+  p = fma(p, r, 1.0 / 479001600.0);
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  return __builtin_amdgcn_ldexp(p, (int)fmin(fmax(n, -2000.0), 2000.0));
+}
+
+// x^e, by products where e is the whole number n (n = 0: any e)
+__device__ __forceinline__ double pow_of(double x, double e, int n) {
+  if (n == 0) return pow(x, e);
+  double r = x;
+  for (int k = 1; k < n; ++k) r *= x;
+  return r;
 }
 
 // a[y] for a runtime index y < M, read with compile-time indices and selects
@@ -458,7 +493,7 @@ struct Thermo {
   double rho, irho;
   double p, rhoe;
   double Gmix, rc2, c2, cL2;  // rc2 = rho c^2
-  Split sp;
+  double yrc;                 // the reactive mixture's rc per unit of its volume
 };
 
 // Reference curves of reactive component C (0 reactant, 1 product) at
@@ -480,7 +515,7 @@ __device__ __forceinline__ RxRef rx_ref(const RxP& r, double irho) {
   o.j = 0.0;
   o.q = 0.0;
   if (r.jwl[C]) {
-    const double xa = exp(-r.jR1[C] * irho), xb = exp(-r.jR2[C] * irho);
+    const double xa = exp_curve(-r.jR1[C] * irho), xb = exp_curve(-r.jR2[C] * irho);
     const double pa = r.jA[C] * xa, pb = r.jB[C] * xb;
     o.j = pa + pb;
     o.p = o.j + o.p;
@@ -566,110 +601,109 @@ __device__ __forceinline__ Split rx_newton(const RxP& r, double lam, double py, 
   const double iry = frcp(ry), ila = frcp(lam), il1 = frcp(l1);
   const double ka = ila * r.iGca, kb = il1 * r.iGcb;
   const double la = lam * ry, lb = l1 * ry;
+  // g and the state at t
+  struct Eval {
+    double g, pp, iden, iD, s, s1, ira, irb;
+    RxRef A, B;
+  };
+  auto eval = [&](double t) {
+    Eval e;
+    const double t1 = 1.0 - t;
+    e.iD = frcp(lam * t1 + l1 * t);
+    const double ta = t1 * e.iD, tb = t * e.iD;
+    e.s = lam * ta;
+    e.s1 = l1 * tb;
+    e.ira = ta * iry;
+    e.irb = tb * iry;
+    e.A = rx_ref<0>(r, e.ira);
+    e.B = rx_ref<1>(r, e.irb);
+    e.pp = p;
+    e.iden = 1.0;
+    if (!KNOWN_P) {
+      const double num = num0 + py * (e.s * e.A.p * r.invGa - la * e.A.e) + py * (e.s1 * e.B.p * r.invGb - lb * e.B.e);
+      e.iden = frcp(den0 + py * (e.s * r.invGa + e.s1 * r.invGb));
+      e.pp = num * e.iden;
+    }
+    e.g = kb * (e.pp - e.B.p) * e.s1 - ka * (e.pp - e.A.p) * e.s;
+    return e;
+  };
+  // Three loops, each with its own evaluation: the first two need g's sign
+  // only, and a wave runs each for as long as its slowest lane (one loop with
+  // the stage in a variable spent two thirds of its instructions on choosing).
+  double ti = 0.5, gi = eval(0.5).g, to = 0.5, go = gi;  // the bracket's inner and outer end
+  const bool up = gi < 0.0;
+  bool found = false;
+#pragma unroll 1
+  for (int probes = 1; probes < 64; ++probes) {
+    const double tn = up ? 0.5 * (ti + 1.0) : 0.5 * ti;
+    if (up && !(tn < 1.0)) break;
+    const double g = eval(tn).g;
+    if ((g < 0.0) != up) {
+      to = tn;
+      go = g;
+      found = true;
+      break;
+    }
+    ti = tn;
+    gi = g;
+  }
+  if (!found && up) return rx_pure(r, lam, ry);  // g < 0 at every probe below 1
+  double lo = 0.0, hi = 1.0, t = 0.5 * ti;       // g >= 0 at every probe down to 2^-64: 2^-65
+  if (found) {
+    const double base = ti, w = (to - ti) / RX_SUBSTEPS;
+#pragma unroll 1
+    for (int k = 1; k < RX_SUBSTEPS; ++k) {
+      const double tn = base + double(k) * w, g = eval(tn).g;
+      if ((g < 0.0) != up) {
+        to = tn;
+        go = g;
+        break;
+      }
+      ti = tn;
+      gi = g;
+    }
+    lo = up ? ti : to;
+    hi = up ? to : ti;
+    t = ti - gi * (to - ti) * frcp(go - gi);
+    if (!(t > lo && t < hi)) t = 0.5 * (lo + hi);
+  }
   // d p_ref / ds of a component is its slope q times a constant: ds/s at
   // fixed masses is -drho/rho
   const double da = -(iry * ila), db = iry * il1;
-  double g = 0.0, dg = 1.0;
-  double s = lam, s1 = l1, ira = iry, irb = iry;
-  RxRef A, B;
-  // 0 the probe ladder, 3 steps across the first bracket, 1 Newton steps in
-  // the sub-bracket, 2 a final midpoint
-  int mode = 0;
-  auto eval = [&](double t) {
-    const double t1 = 1.0 - t;
-    const double iD = frcp(lam * t1 + l1 * t);
-    const double ta = t1 * iD, tb = t * iD;
-    s = lam * ta;
-    s1 = l1 * tb;
-    ira = ta * iry;
-    irb = tb * iry;
-    A = rx_ref<0>(r, ira);
-    B = rx_ref<1>(r, irb);
-    double pp = p, iden = 1.0;
-    if (!KNOWN_P) {
-      const double num = num0 + py * (s * A.p * r.invGa - la * A.e) + py * (s1 * B.p * r.invGb - lb * B.e);
-      iden = frcp(den0 + py * (s * r.invGa + s1 * r.invGb));
-      pp = num * iden;
-    }
-    g = kb * (pp - B.p) * s1 - ka * (pp - A.p) * s;
-    if (mode == 1) {  // the slope, for Newton steps only: dg/dt = lam (1-lam) / D^2 df/ds
-      const double dA = A.q * da, dB = B.q * db;
-      double dp = 0.0;
-      if (!KNOWN_P) {
-        const double dnum =
-            py * ((A.p + s * dA) * r.invGa + A.j + (s1 * dB - B.p) * r.invGb - B.j);
-        dp = (dnum - pp * py * (r.invGa - r.invGb)) * iden;
-      }
-      const double df = ka * ((dp - dA) * s + (pp - A.p)) - kb * ((dp - dB) * s1 - (pp - B.p));
-      dg = df * (lam * l1) * (iD * iD);
-    }
-  };
-  // one evaluation site for the four modes
-  double lo = 0.0, hi = 1.0, glo = 0.0, ghi = 0.0, t = 0.5;
-  double base = 0.5, w = 0.0;  // the first bracket's inner end; its width / RX_SUBSTEPS (signed)
-  int probes = 0, sub = 0;
-  bool up = false;
   double last = 1.0;  // size of the previous Newton step
-  for (int it = 0; it < 160; ++it) {
-    eval(t);
-    if (mode == 2) break;
-    const bool below = g < 0.0;
-    if (below) {
+  Eval e;
+#pragma unroll 1
+  for (int it = 0; it < 100; ++it) {
+    e = eval(t);
+    if (!found || e.g == 0.0) break;
+    if (e.g < 0.0)
       lo = t;
-      glo = g;
-    } else {
+    else
       hi = t;
-      ghi = g;
+    // dg/dt = lam (1-lam) / D^2 df/ds
+    const double dA = e.A.q * da, dB = e.B.q * db;
+    double dp = 0.0;
+    if (!KNOWN_P) {
+      const double dnum =
+          py * ((e.A.p + e.s * dA) * r.invGa + e.A.j + (e.s1 * dB - e.B.p) * r.invGb - e.B.j);
+      dp = (dnum - e.pp * py * (r.invGa - r.invGb)) * e.iden;
     }
-    bool newton = false;
-    double tn = 0.0;
-    if (mode == 0) {
-      ++probes;
-      if (probes == 1) up = below;
-      if (probes > 1 && below != up) {  // the first bracket: cross it from its inner end
-        mode = 3;
-        w = (t - base) / RX_SUBSTEPS;
-        sub = 1;
-        tn = base + w;
-      } else {
-        base = t;
-        tn = up ? 0.5 * (t + 1.0) : 0.5 * t;
-        if (up && !(tn < 1.0)) return rx_pure(r, lam, ry);  // g < 0 at every probe below 1: the pure state
-        if (probes == 64) {  // g >= 0 at every probe down to 2^-64
-          mode = 2;
-          tn = 0.5 * t;
-        }
-      }
-    } else if (mode == 3) {
-      if (below != up || sub == RX_SUBSTEPS - 1) {
-        newton = true;  // [lo, hi] is the sub-bracket
-      } else {
-        ++sub;
-        tn = base + double(sub) * w;
-      }
-    } else {
-      // the current state is kept once the Newton step is below the
-      // resolution the split needs (or below half an ulp of t)
-      const double step = g / dg, size = fabs(step), room = fmin(t, 1.0 - t);
-      if (g == 0.0 || (isfinite(step) && !(size > fmax(1e-14 * room, 0x1p-53 * t)))) break;
-      // the noise floor (a triple root, whose steps shrink by 2/3, lies
-      // above it only where the root itself is known to 1e-5).  Without this
-      // test about one split in 300 of a detonation front ran all 160
-      // evaluations, and the waves that hold one set the kernels' time: two
-      // steps of a 400 x 1000 rate stick took 5.5 ms, with it 1.43 ms
-      if (size > 0.5 * last && last <= 1e-7 * room) break;
-      last = size;
-      tn = t - step;
-      if (!(tn > lo && tn < hi)) tn = 0.5 * (lo + hi);  // NaN steps land here too
-    }
-    if (newton) {
-      mode = 1;
-      tn = lo - glo * (hi - lo) / (ghi - glo);
-      if (!(tn > lo && tn < hi)) tn = 0.5 * (lo + hi);
-    }
-    t = tn;
+    const double df = ka * ((dp - dA) * e.s + (e.pp - e.A.p)) - kb * ((dp - dB) * e.s1 - (e.pp - e.B.p));
+    // the current state is kept once the Newton step is below the
+    // resolution the split needs (or below half an ulp of t)
+    const double step = e.g * frcp(df * (lam * l1) * (e.iD * e.iD)), size = fabs(step), room = fmin(t, 1.0 - t);
+    if (isfinite(step) && !(size > fmax(1e-14 * room, 0x1p-53 * t))) break;
+    // the noise floor (a triple root, whose steps shrink by 2/3, lies
+    // above it only where the root itself is known to 1e-5).  Without this
+    // test about one split in 300 of a detonation front ran all 160
+    // evaluations, and the waves that hold one set the kernels' time: two
+    // steps of a 400 x 1000 rate stick took 5.5 ms, with it 1.43 ms
+    if (size > 0.5 * last && last <= 1e-7 * room) break;
+    last = size;
+    t = t - step;
+    if (!(t > lo && t < hi)) t = 0.5 * (lo + hi);  // NaN steps land here too
   }
-  return rx_split_of(r, s, s1, ira, irb, A, B);
+  return rx_split_of(r, e.s, e.s1, e.ira, e.irb, e.A, e.B);
 }
 
 // The split's root rule for two gas components (Appendix B, with the reading
@@ -798,18 +832,64 @@ __device__ __forceinline__ Split rx_solve_gas(const RxP& r, double lam, double A
   return rx_from_pick(r, picked, sp, t_end, lam);
 }
 
-// the mixture's own 1/Gamma and p_ref/Gamma - rho e_ref per unit of its volume
-__device__ __forceinline__ double rx_xi(const RxP& r, const Split& o) { return o.s * r.invGa + o.s1 * r.invGb; }
-__device__ __forceinline__ double rx_num(const RxP& r, const Split& o, double lam, double ry) {
-  return (o.s * (o.pa * r.invGa) + o.s1 * (o.pb * r.invGb)) - ry * (lam * o.ea + (1.0 - lam) * o.eb);
+// What the mixture rules take of a split, per unit of the mixture's volume:
+// 1/Gamma, p_ref/Gamma - rho e_ref, and rc (rho c^2 / Gamma less (1 + 1/Gamma)
+// p, as of a Curve times 1/Gamma)
+struct MixY {
+  double xi, num, rc;
+};
+
+template <bool GEN>
+__device__ __forceinline__ MixY rx_mixture(const RxP& r, const Split& o, double lam, double ry) {
+  MixY m;
+  m.xi = o.s * r.invGa + o.s1 * r.invGb;
+  const double pg = o.s * (o.pa * r.invGa) + o.s1 * (o.pb * r.invGb);
+  m.num = pg - ry * (lam * o.ea + (1.0 - lam) * o.eb);
+  m.rc = GEN ? (o.s * o.ka + o.s1 * o.kb) - pg : -pg;
+  return m;
+}
+
+// the mixture of two primitive states (progress, density, pressure); with JWL
+// components through one copy of the split (the instruction cache holds 64 KB:
+// a fused sweep with a copy at every use was 120 KB)
+template <int RX>
+__device__ __forceinline__ void rx_mixture_pair(const RxP& r, const double lam[2], const double ry[2],
+                                                const double p[2], MixY& a, MixY& b) {
+  if constexpr (RX == 2) {
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+      const double l = k ? lam[1] : lam[0], d = k ? ry[1] : ry[0], q = k ? p[1] : p[0];
+      const MixY m = rx_mixture<true>(r, rx_split_p<true>(r, l, d, q), l, d);
+      if (k)
+        b = m;
+      else
+        a = m;
+    }
+  } else {
+    a = rx_mixture<false>(r, rx_split_p<false>(r, lam[0], ry[0], p[0]), lam[0], ry[0]);
+    b = rx_mixture<false>(r, rx_split_p<false>(r, lam[1], ry[1], p[1]), lam[1], ry[1]);
+  }
+}
+
+// the mixtures of two primitive states W
+template <int D, int N, int RX>
+__device__ __forceinline__ void mixtures_of(const Params& P, const double* Wa, const double* Wb, MixY& a, MixY& b) {
+  using L = Lay<D, N, RX>;
+  if (!rx_mix<RX>(P)) return;
+  const int y = P.rx.mat;
+  const double lam[2] = {fmin(fmax(Wa[L::LAM], 0.0), 1.0), fmin(fmax(Wb[L::LAM], 0.0), 1.0)};
+  const double ry[2] = {pick<N>(Wa + L::M0, y), pick<N>(Wb + L::M0, y)};
+  const double p[2] = {Wa[L::E], Wb[L::E]};
+  rx_mixture_pair<RX>(P.rx, lam, ry, p, a, b);
 }
 
 // The reactive part of the pressure function (Appendix B, conservative
 // branch) for a cell whose non-reactive part is (num0, den0): solves the
-// split and leaves the full numerator and denominator (xi) of p.
+// split and leaves the full numerator and denominator (xi) of p; returns the
+// mixture's rc.
 template <bool GEN>
-__device__ __forceinline__ Split rx_cons(const RxP& r, double py, double ry, double lam, double num0, double den0,
-                                         double& num, double& den) {
+__device__ __forceinline__ double rx_cons(const RxP& r, double py, double ry, double lam, double num0, double den0,
+                                          double& num, double& den) {
   Split o;
   if constexpr (GEN) {
     if (lam >= 1.0 - 1e-12 || lam <= 1e-12)
@@ -823,9 +903,10 @@ __device__ __forceinline__ Split rx_cons(const RxP& r, double py, double ry, dou
     const double B1 = py * (r.invGa - r.invGb);
     o = rx_solve_gas(r, lam, A0, A1, B0, B1);
   }
-  den = den0 + py * rx_xi(r, o);
-  num = num0 + py * rx_num(r, o, lam, ry);
-  return o;
+  const MixY m = rx_mixture<GEN>(r, o, lam, ry);
+  den = den0 + py * m.xi;
+  num = num0 + py * m.num;
+  return m.rc;
 }
 
 // closures of the non-reactive materials and their sums w, n0, d0
@@ -852,7 +933,7 @@ __device__ __forceinline__ void pressure_from_rhoe(const Params& P, const Phases
   double den = T.d0, num = T.rhoe + T.n0;
   if (rx_mix<RX>(P)) {
     const int y = P.rx.mat;
-    T.sp = rx_cons<RX == 2>(P.rx, pick<N>(Q.phi, y), pick<N>(Q.rho, y), lam, T.rhoe + T.n0, T.d0, num, den);
+    T.yrc = rx_cons<RX == 2>(P.rx, pick<N>(Q.phi, y), pick<N>(Q.rho, y), lam, T.rhoe + T.n0, T.d0, num, den);
   }
   T.xi = den;
   T.ixi = frcp(den);
@@ -870,10 +951,7 @@ __device__ __forceinline__ void sound_sums(const Params& P, const Phases<N>& Q, 
 #pragma unroll
   for (int l = 0; l < N; ++l) {
     if (rx_mix<RX>(P) && l == P.rx.mat) {
-      const Split& o = T.sp;
-      double rc = -(o.s * (o.pa * P.rx.invGa) + o.s1 * (o.pb * P.rx.invGb));
-      if constexpr (RX == 2) rc += o.s * o.ka + o.s1 * o.kb;
-      cnum += Q.phi[l] * rc;
+      cnum += Q.phi[l] * T.yrc;
     } else {
       cnum += T.w[l] * T.c[l].rc;
       gnum += T.w[l] * T.c[l].G;
@@ -932,11 +1010,11 @@ __device__ __forceinline__ void cons_to_prim(const Params& P, const double* U, d
   for (int q = 0; q < L::NV; ++q) W[L::V0 + q] = U[L::V0 + q];
 }
 
-// primitive -> mixture state (energy from p): the closures, the split, xi,
-// rho and rho e; H holds 4 H
+// primitive -> mixture state (energy from p; my: the reactive mixture, if any):
+// the closures, xi, rho and rho e; H holds 4 H
 template <int D, int N, int RX>
-__device__ __forceinline__ void prim_mix(const Params& P, const double* W, Phases<N>& Q, Thermo<N, RX>& T,
-                                         double H[6], double& J2) {
+__device__ __forceinline__ void prim_mix(const Params& P, const double* W, const MixY& my, Phases<N>& Q,
+                                         Thermo<N, RX>& T, double H[6], double& J2) {
   using L = Lay<D, N, RX>;
   phases_from_prim<N>(W, W + L::M0, Q);
   strain4<D, N, RX>(W + L::V0, H, J2);
@@ -945,12 +1023,10 @@ __device__ __forceinline__ void prim_mix(const Params& P, const double* W, Phase
   T.xi = T.d0;
   double n = T.n0;
   if (rx_mix<RX>(P)) {
-    const int y = P.rx.mat;
-    const double lam = fmin(fmax(W[L::LAM], 0.0), 1.0);
-    const double py = pick<N>(Q.phi, y), ry = pick<N>(Q.rho, y);
-    T.sp = rx_split_p<RX == 2>(P.rx, lam, ry, T.p);
-    T.xi = T.d0 + py * rx_xi(P.rx, T.sp);
-    n += py * rx_num(P.rx, T.sp, lam, ry);
+    const double py = pick<N>(Q.phi, P.rx.mat);
+    T.xi = T.d0 + py * my.xi;
+    n += py * my.num;
+    T.yrc = my.rc;
   }
   T.rhoe = fma(T.p, T.xi, -n);
   T.rho = 0.0;
@@ -959,9 +1035,9 @@ __device__ __forceinline__ void prim_mix(const Params& P, const double* W, Phase
 }
 
 // Mixture shear modulus G = sum(phi_l G_l / Gamma_l) / xi and 4 H of a
-// primitive state: all the stress needs besides p
+// primitive state (xi_y: of the reactive mixture): all the stress needs besides p
 template <int D, int N, int RX>
-__device__ __forceinline__ double prim_shear(const Params& P, const double* W, double H[6]) {
+__device__ __forceinline__ double prim_shear(const Params& P, const double* W, double xi_y, double H[6]) {
   using L = Lay<D, N, RX>;
   double phi[N];
   double sphi = 0.0;
@@ -975,9 +1051,7 @@ __device__ __forceinline__ double prim_shear(const Params& P, const double* W, d
 #pragma unroll
   for (int l = 0; l < N; ++l) {
     if (rx_mix<RX>(P) && l == P.rx.mat) {
-      const double lam = fmin(fmax(W[L::LAM], 0.0), 1.0);
-      const Split o = rx_split_p<RX == 2>(P.rx, lam, W[L::M0 + l], W[L::E]);
-      xi += phi[l] * rx_xi(P.rx, o);
+      xi += phi[l] * xi_y;
     } else {
       const double wl = phi[l] * P.mat[l].invGam;
       xi += wl;

@@ -40,7 +40,9 @@ __global__ __launch_bounds__(256) void k_prim_to_cons(Params P, const double* __
       calib::prim_thermo(P, w, T, H, J2, true);
     } else {
       Phases<N> Q;
-      prim_mix<D, N, RX>(P, w, Q, T, H, J2);
+      MixY my{}, mw{};
+      mixtures_of<D, N, RX>(P, w, w, my, mw);
+      prim_mix<D, N, RX>(P, w, my, Q, T, H, J2);
     }
     double phiN = 1.0;
 #pragma unroll

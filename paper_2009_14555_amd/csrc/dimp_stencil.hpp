@@ -69,21 +69,23 @@ __device__ __forceinline__ double tbv(const Cand& m, const Cand& p, double Lp, d
 // stress column sigma_{k,DIR} = 2 G dev H - p delta of a primitive state;
 // shear_col leaves the part 2 G dev H
 template <int D, int N, int RX, int DIR>
-__device__ __forceinline__ void shear_col(const Params& P, const double* W, double sig[3]) {
+__device__ __forceinline__ void shear_col(const Params& P, const double* W, double xi_y, double sig[3]) {
   if (!P.any_shear) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) sig[k] = 0.0;
     return;
   }
   double H[6];
-  const double G2 = 0.5 * prim_shear<D, N, RX>(P, W, H);  // H holds 4 H
+  const double G2 = 0.5 * prim_shear<D, N, RX>(P, W, xi_y, H);  // H holds 4 H
 #pragma unroll
   for (int k = 0; k < 3; ++k) sig[k] = hnz<D>(k, DIR) ? G2 * H[hs(k, DIR)] : 0.0;
 }
 
 template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void stress_col(const Params& P, const double* W, double sig[3]) {
-  shear_col<D, N, RX, DIR>(P, W, sig);
+  MixY my{}, mw{};
+  if (P.any_shear) mixtures_of<D, N, RX>(P, W, W, my, mw);
+  shear_col<D, N, RX, DIR>(P, W, my.xi, sig);
   sig[DIR] -= W[Lay<D, N, RX>::E];
 }
 
@@ -139,8 +141,10 @@ __device__ __forceinline__ void edges_half_step(const Params& P, const double* W
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
   double sL[3], sR[3];
-  shear_col<D, N, RX, DIR>(P, WL, sL);
-  shear_col<D, N, RX, DIR>(P, WR, sR);
+  MixY mL{}, mR{};
+  if (P.any_shear) mixtures_of<D, N, RX>(P, WL, WR, mL, mR);
+  shear_col<D, N, RX, DIR>(P, WL, mL.xi, sL);
+  shear_col<D, N, RX, DIR>(P, WR, mR.xi, sR);
   // the half step's length goes into the speeds
   const double h = 0.5 * nu;
   const double un = h * W0[L::MOM0 + DIR];
@@ -198,12 +202,12 @@ struct Side {
 };
 
 template <int D, int N, int RX, int DIR>
-__device__ __forceinline__ void side_state(const Params& P, const double* W, Side<D, N, RX>& S) {
+__device__ __forceinline__ void side_state(const Params& P, const double* W, Side<D, N, RX>& S, const MixY& my = {}) {
   using L = Lay<D, N, RX>;
   Phases<N> Q;
   Thermo<N, RX> T;
   double H[6], J2;
-  prim_mix<D, N, RX>(P, W, Q, T, H, J2);
+  prim_mix<D, N, RX>(P, W, my, Q, T, H, J2);
   S.rho = T.rho;
   double uu = 0.0;
 #pragma unroll
@@ -307,8 +311,10 @@ __device__ __forceinline__ void face_flux(const Params& P, const double* WL, con
   using L = Lay<D, N, RX>;
   constexpr int F = L::F;
   Side<D, N, RX> A, B;
-  side_state<D, N, RX, DIR>(P, WL, A);
-  side_state<D, N, RX, DIR>(P, WR, B);
+  MixY ya{}, yb{};
+  mixtures_of<D, N, RX>(P, WL, WR, ya, yb);
+  side_state<D, N, RX, DIR>(P, WL, A, ya);
+  side_state<D, N, RX, DIR>(P, WR, B, yb);
   const double uL = A.u[DIR], uR = B.u[DIR];
   const double SL = fmin(uL - A.cl, uR - B.cl);
   const double SR = fmax(uL + A.cl, uR + B.cl);
@@ -543,17 +549,6 @@ __device__ __forceinline__ void plastic_cell(const Params& P, double* U, double 
   }
 }
 
-// pressure of a cell whose reactive progress is lam, with the non-reactive
-// part of the pressure function (num0, den0) already summed; rho_y is left
-// for the rate
-template <bool GEN>
-__device__ __forceinline__ double rx_pressure(const RxP& r, double phi_y, double rho_y, double lam, double num0,
-                                              double den0) {
-  double num, den;
-  (void)rx_cons<GEN>(r, phi_y, rho_y, lam, num0, den0, num, den);
-  return num * frcp(den);
-}
-
 // Three-term ignition-and-growth rate of the reacted fraction F = 1 - lam
 // (Sec. 4.2, Table 4) at the mixture's own density rho and pressure p: each
 // term carries a positive power of lam, the growth terms one of F; the
@@ -561,14 +556,20 @@ __device__ __forceinline__ double rx_pressure(const RxP& r, double phi_y, double
 __device__ __forceinline__ double ig_rate(const RxP& r, double lam, double rho, double p) {
   if (!(lam > 0.0)) return 0.0;
   const double F = 1.0 - lam;
+  const double mu = rho * r.ig_irho0 - 1.0 - r.ig_a;
+  const bool ignite = r.igFig - F > 0.0 && mu > 0.0;
+  const bool grow1 = F > 0.0 && r.igFG1 - F > 0.0, grow2 = F > 0.0 && F - r.igFG2 > 0.0;
+  if (!(ignite || grow1 || grow2)) return 0.0;
+  // a power of lam is taken once where the terms share it (Table 4: 0.667 in
+  // all three), the whole powers (1, 3, 7) by products
+  const double lb = pow_of(lam, r.ig_b, r.ign[0]);
+  const double lc = (r.ig_c == r.ig_b) ? lb : pow_of(lam, r.ig_c, r.ign[1]);
+  const double le = (r.ig_e == r.ig_b) ? lb : pow_of(lam, r.ig_e, r.ign[3]);
+  const double ph = fmax(p, 0.0) * r.ig_ipunit;
   double out = 0.0;
-  const double mu = rho / r.ig_rho0 - 1.0 - r.ig_a;
-  if (r.igFig - F > 0.0 && mu > 0.0) out = out + r.igI * pow(lam, r.ig_b) * pow(mu, r.ig_x);
-  const double ph = fmax(p, 0.0) / r.ig_punit;
-  if (F > 0.0) {
-    if (r.igFG1 - F > 0.0) out = out + r.igG1 * pow(lam, r.ig_c) * pow(F, r.ig_d) * pow(ph, r.ig_y);
-    if (F - r.igFG2 > 0.0) out = out + r.igG2 * pow(lam, r.ig_e) * pow(F, r.ig_g) * pow(ph, r.ig_z);
-  }
+  if (ignite) out = out + r.igI * lb * pow_of(mu, r.ig_x, r.ign[5]);
+  if (grow1) out = out + r.igG1 * lc * pow_of(F, r.ig_d, r.ign[2]) * pow_of(ph, r.ig_y, r.ign[6]);
+  if (grow2) out = out + r.igG2 * le * pow_of(F, r.ig_g, r.ign[4]) * pow_of(ph, r.ig_z, r.ign[7]);
   return out;
 }
 
@@ -605,13 +606,23 @@ __device__ __forceinline__ void geom_rate(const Params& P, const double* U, doub
 template <int D, int N, int RX>
 __device__ __forceinline__ void geom_cell(const Params& P, double* U, double r, double dt) {
   using L = Lay<D, N, RX>;
-  double S0[L::F], S1[L::F], U1[L::F];
-  geom_rate<D, N, RX>(P, U, r, S0);
+  double S[L::F], sum[L::F], V[L::F];
 #pragma unroll
-  for (int f = 0; f < L::F; ++f) U1[f] = U[f] + dt * S0[f];
-  geom_rate<D, N, RX>(P, U1, r, S1);
+  for (int f = 0; f < L::F; ++f) {
+    V[f] = U[f];
+    sum[f] = 0.0;
+  }
+#pragma unroll 1
+  for (int k = 0; k < 2; ++k) {  // one copy of the closures
+    geom_rate<D, N, RX>(P, V, r, S);
 #pragma unroll
-  for (int f = 0; f < L::F; ++f) U[f] = U[f] + (0.5 * dt) * (S0[f] + S1[f]);
+    for (int f = 0; f < L::F; ++f) {
+      V[f] = U[f] + dt * S[f];
+      sum[f] += S[f];
+    }
+  }
+#pragma unroll
+  for (int f = 0; f < L::F; ++f) U[f] = U[f] + (0.5 * dt) * sum[f];
 }
 
 // Reaction (Sec. 3.3): RK4 on lambda at fixed mass and total energy, the
@@ -659,44 +670,42 @@ __device__ __forceinline__ void reaction_cell(const Params& P, double* U, double
       phi_y = Q.phi[l];
       rho_y = Q.rho[l];
     }
-  auto rate = [&](double lam) {
-    const double lc = fmin(fmax(lam, 0.0), 1.0);
-    const double p = rx_pressure<RX == 2>(r, phi_y, rho_y, lc, num0, den0);
-    if (r.law == LAW_IG) return -ig_rate(r, lc, rho_y, p);
-    const double x = fmax(p, 0.0) * r.inv_pref;
-    const double xn = r.n_is2 ? x * x : pow(x, r.n);
-    return -r.k * lc * xn;
-  };
+  // the four stages, and the split of the result for its wave speed, through
+  // one evaluation site
   const double l0 = fmin(fmax(U[L::LAM] * frcp(my), 0.0), 1.0);
-  // the four stages through one evaluation site (the JWL split is some 600
-  // instructions: four copies, and the other splits of a fused sweep, exceed
-  // the instruction cache)
-  double l1 = l0, k = 0.0, sum = 0.0;
+  double lam = l0, l1 = l0, k = 0.0, sum = 0.0;
 #pragma unroll 1
-  for (int st = 0; st < 4; ++st) {
-    const double c = (st == 0) ? 0.0 : (st == 3) ? 1.0 : 0.5;
-    k = rate(l0 + c * dt * k);
+  for (int st = 0; st < (WS ? 5 : 4); ++st) {
+    const double lc = (WS && st == 4) ? l1 : fmin(fmax(lam, 0.0), 1.0);
+    double num, den;
+    T.yrc = rx_cons<RX == 2>(r, phi_y, rho_y, lc, num0, den0, num, den);
+    T.xi = den;
+    T.ixi = frcp(den);
+    T.p = num * T.ixi;
+    if (WS && st == 4) break;
+    if (r.law == LAW_IG) {
+      k = -ig_rate(r, lc, rho_y, T.p);
+    } else {
+      const double x = fmax(T.p, 0.0) * r.inv_pref;
+      k = -r.k * lc * (r.n_is2 ? x * x : pow(x, r.n));
+    }
     // no rate at the start (an unreacted cell below the ignition threshold, a
     // fully burnt one): every later stage evaluates the same lambda and gives
     // 0 again, so the result is l0 exactly
     if (st == 0 && !(k != 0.0)) break;
     sum += (st == 1 || st == 2) ? 2.0 * k : k;
+    lam = l0 + (st == 2 ? dt : 0.5 * dt) * k;
     if (st == 3) l1 = fmin(fmax(l0 + (dt / 6.0) * sum, 0.0), 1.0);
   }
   U[L::LAM] = my * l1;
   if (WS) {
-    double num, den;
-    T.sp = rx_cons<RX == 2>(r, phi_y, rho_y, l1, num0, den0, num, den);
     T.rho = rt;
     T.irho = irt;
-    T.xi = den;
-    T.ixi = frcp(den);
-    T.p = num * T.ixi;
     T.rhoe = rhoe;
     finish<N, RX>(P, Q, T);
     const double cl = fsqrt(T.cL2);
 #pragma unroll
-    for (int k = 0; k < D; ++k) s[k] = fabs(u[k]) + cl;
+    for (int d = 0; d < D; ++d) s[d] = fabs(u[d]) + cl;
   }
 }
 
