@@ -327,7 +327,8 @@ int64_t sweep_slots(const Params& P, int D, int dir) {
   if (dir == 0) return ((P.n[0] + 57) / 58) * P.n[1] * P.n[2];
   const int oa = (dir == 1) ? 2 : 1;
   const int64_t no = (D == 3) ? P.n[oa] : 1;
-  return ((P.n[0] + TILE_COLUMNS - 1) / TILE_COLUMNS) * no * ((P.n[dir] + 57) / 58) * TILE_COLUMNS;
+  constexpr int CW = 4;  // a fused tile sweep's columns (tile_columns)
+  return ((P.n[0] + CW - 1) / CW) * no * ((P.n[dir] + 57) / 58) * TILE_WAVES;
 }
 
 hipError_t launch_reduce_smax(const double* part, int64_t nslots, int D, double* scratch,

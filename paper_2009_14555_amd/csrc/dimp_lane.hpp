@@ -4,6 +4,33 @@
 
 namespace dimp {
 
+// The block that runs as the grid's b-th of nb.  The hardware deals blocks
+// round-robin to the 8 XCDs, each with its own L2; here runs of consecutive
+// blocks are dealt instead, so that neighbours share an L2, and many runs to
+// each XCD, so that a costly region (the reaction zone above all) is spread over
+// all of them.  One run for each XCD left a 400 x 1000 detonating stick at 691 us
+// for two steps, where runs of 16 blocks take 445 (4: 458, 64: 538); 256^3, with
+// 10 times the blocks, 13310 us, where runs of 64 take 12070 (16: 12140, 4:
+// 12480); 2048^2 1935, 1852 (16: 1885, 4: 1978).  So a run is as long as leaves
+// each XCD eight runs or more, up to 64 blocks.
+__device__ __forceinline__ int64_t xcd_block(uint32_t b, uint32_t nb) {
+  const int sh = nb >= 16384 ? 6 : nb >= 1024 ? 4 : nb >= 256 ? 2 : 0;  // log2 of the run
+  const uint32_t group = 8u << sh;
+  if (b >= nb - (nb & (group - 1))) return b;  // the last, incomplete deal
+  return (b & ~(group - 1)) + ((b & 7) << sh) + ((b >> 3) & ((1u << sh) - 1));
+}
+
+// A [F][64][CW] tile of doubles in LDS, rows along the sweep axis, columns x
+template <int CW>
+struct TileGeom {
+  // element (f, r, c) of a [F][64][CW] tile: the column index is XOR-swizzled
+  // by the row so that both access patterns are free of LDS bank conflicts:
+  // the coalesced copies (16 lanes = 16/CW rows x CW columns) and the
+  // per-wave column reads (16 lanes = 16 rows of one column)
+  static constexpr int RS = 16 / CW;
+  __device__ static constexpr int at(int f, int r, int c) { return (f * 64 + r) * CW + (c ^ ((r / RS) & (CW - 1))); }
+};
+
 // THINC candidates of every stored volume fraction of the lane's cell, all
 // with the normal of the first, and the BVD choice on them.
 template <int D, int N, int RX, int DIR, class PhiAt>

@@ -22,9 +22,15 @@
 
 namespace dimp {
 
-#ifndef TILE_COLUMNS
-#define TILE_COLUMNS 4
-#endif
+// A tile sweep's block has four waves and 4 or 8 columns (a wave takes its
+// columns one after the other).  Eight columns read and write 64 contiguous
+// bytes of a row instead of 32: 256^3, y 1757 -> 1549 us, z 2419 -> 2241.  With
+// the sources fused (z 3032, 3039) and on 2-D grids (2048^2: y 260, 262; fused
+// 269, 323) the second column costs what the wider rows gain or more (there
+// the LDS of eight columns holds three blocks a CU where four columns hold
+// four).
+constexpr int TILE_WAVES = 4;
+constexpr int tile_columns(int D, bool fuse) { return (D == 3 && !fuse) ? 8 : 4; }
 // waves per SIMD the sweep kernels are built for (launch bound): four where
 // the state fits 128 VGPRs, the 1-D and 2-D instances of a material profile
 // without a history slot (124-126; at five waves they spill 120 bytes a lane);
@@ -68,13 +74,9 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE>())) void sw
   const int lane = threadIdx.x & 63;
   const int64_t nx = P.n[0], ny = P.n[1], nz = P.n[2];
   const int64_t nseg = (nx + 57) / 58;
-  // XCD-aware block order: consecutive logical blocks (the same and the
-  // neighbouring rows, whose volume fractions the THINC normals read) run on
-  // one XCD and share its L2
-  const int64_t nblocks = (nseg * ny * nz + 3) / 4;
-  const int64_t per = (nblocks + 7) / 8;
-  const int64_t lb = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (lb >= nblocks) return;  // uniform per block
+  // the blocks of a run are the same and the neighbouring rows, whose volume
+  // fractions the THINC normals read
+  const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
   // one value per wave, told to the compiler so that the index arithmetic (its
   // divisions above all) runs on the scalar unit
   const int64_t wave = lb * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -156,53 +158,24 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE>())) void sw
 // Sweep along y or z.  A block of CW waves covers CW consecutive x columns
 // and 64 cells along the sweep axis; the tile is staged through LDS so that
 // HBM sees rows of CW doubles, while each wave holds one column with one cell
-// per lane and runs the same stages as the row sweep.  Block indices are
-// remapped so that neighbouring x chunks (which share L2 lines) run on the
-// same XCD at about the same time.
-template <int CW>
-struct TileGeom {
-  // element (f, r, c) of a [F][64][CW] tile: the column index is XOR-swizzled
-  // by the row so that both access patterns are free of LDS bank conflicts:
-  // the coalesced copies (16 lanes = 16/CW rows x CW columns) and the
-  // per-wave column reads (16 lanes = 16 rows of one column)
-  static constexpr int RS = 16 / CW;
-  __device__ static constexpr int at(int f, int r, int c) { return (f * 64 + r) * CW + (c ^ ((r / RS) & (CW - 1))); }
-  // the results get a tile of their own (no barrier between the last read of
-  // the input tile and the first write of a result) where both fit in 64 KB
-  // of LDS, in as many blocks as the CU's registers hold (WAVES per SIMD, 160
-  // KB); otherwise they overwrite the input tile after a barrier
-  template <int F, int WAVES>
-  static constexpr bool separate() {
-    constexpr int bytes = 2 * F * 64 * CW * 8;
-    return bytes <= 65536 && bytes * (4 * WAVES / CW) <= 163840;
-  }
-  template <int F, int WAVES>
-  static constexpr int lds_doubles() {
-    return (separate<F, WAVES>() ? 2 : 1) * F * 64 * CW;
-  }
-};
-
+// per lane and runs the same stages as the row sweep.  The blocks
+// of a run (xcd_block) are neighbouring x chunks, which share L2 lines.
 template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false>
-__global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, PROF, FUSE>())) void sweep_tile(Params P, const double* __restrict__ in,
+__global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE>())) void sweep_tile(Params P, const double* __restrict__ in,
                                                        double* __restrict__ out, double dt_arg,
                                                        const double* __restrict__ dtp,
-                                                       double* __restrict__ part, int64_t nblocks,
+                                                       double* __restrict__ part,
                                                        const double* __restrict__ Rin, const double* qn,
                                                        int stage) {
   using L = Lay<D, N, RX>;
   using G = TileGeom<CW>;
   constexpr int F = L::F;
   assume_profile<N, RX, PROF>(P);
-  constexpr bool SEP = G::template separate<F, sweep_waves<D, N, RX, PROF, FUSE>()>();
   extern __shared__ double lds[];
-  double* tileU = lds;                               // [F][64][CW] input state
-  double* tileO = SEP ? lds + F * 64 * CW : tileU;   // [F][64][CW] results
+  double* tileU = lds;  // [F][64][CW]: the input state, then the results in place
   const double dt = dtp ? dtp[0] : dt_arg;
 
-  // XCD-aware logical block index
-  const int64_t per = (nblocks + 7) / 8;
-  const int64_t lb = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (lb >= nblocks) return;  // uniform per block, before any barrier
+  const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
   const int64_t nx = P.n[0], ny = P.n[1], nz = P.n[2];
   const int64_t nm = P.n[DIR];
   const int oa = (DIR == 1) ? 2 : 1;  // the other transverse axis (3-D)
@@ -219,7 +192,7 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, PROF, FUSE>())) voi
   const int tid = threadIdx.x;
 
   // load the tile: thread t -> row r (sweep axis), column c (x)
-  for (int t = tid; t < 64 * CW; t += 64 * CW) {
+  for (int t = tid; t < 64 * CW; t += 64 * TILE_WAVES) {
     const int r = t / CW, c = t % CW;
     const int64_t xx = bc_map(x0 + c, nx, P.bc[0]);
     const int64_t jj = WALL ? bc_map_wall(j0 + r, nm, P.bc[DIR]) : bc_map(j0 + r, nm, P.bc[DIR]);
@@ -234,60 +207,68 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, PROF, FUSE>())) voi
     }
   }
   __syncthreads();
-  const int w = tid >> 6, lane = tid & 63;
-  auto load_U = [&](double* U) {
-    asm volatile("" ::: "memory");  // re-read LDS rather than keep U live in registers
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  double smax[D];
 #pragma unroll
-    for (int f = 0; f < F; ++f) U[f] = tileU[G::at(f, lane, w)];
-  };
-  // transverse phi offsets: b along x, c along the other axis (3-D)
-  auto phi_at = [&](int b, int c) -> double {
-    const int64_t xx = bc_map(x0 + w + b - 1, nx, P.bc[0]);
-    const int64_t jj = bc_map(j0 + lane, nm, P.bc[DIR]);
-    const int64_t oo = (D == 3) ? bc_map(o + c - 1, no, P.bc[oa]) : 0;
-    return in[xx * sx + jj * sm + oo * so];
-  };
-  // lane_sweep orders the transverse offsets over the other two axes in
-  // increasing axis order: for DIR = 1 that is (x, z), for DIR = 2 (x, y)
-  const bool writer = (lane >= 3) && (lane < 61) && (j0 + lane < nm) && (x0 + w < nx);
-  const int64_t jl = j0 + lane;
-  const bool wall = WALL && ((jl == 0 && (P.bc[DIR] == BC_REFLECTIVE || P.bc[DIR] == BC_AXIS)) ||
-                             (jl == nm && P.bc[DIR] == BC_REFLECTIVE));
-  double Un[F], s[D];
-  if constexpr (PROF == PROF_CALIB)
-    calib::lane_sweep<DIR, FUSE>(P, load_U, phi_at, dt / P.dx[DIR], dt, writer, Un, s, wall);
-  else if (MODE == M_SPLIT)
-    lane_sweep<D, N, RX, DIR, FUSE>(P, load_U, phi_at, dt * P.idx[DIR], dt, writer, Un, s, wall);
-  else
-    lane_sweep<D, N, RX, DIR, false, true>(P, load_U, phi_at, P.idx[DIR], dt, writer, Un, s, wall);
-  if (MODE == M_RK_FIRST && writer) {
-    // q - dt D_y(q) (the input tile still holds q)
-    double U[F];
-    load_U(U);
+  for (int k = 0; k < D; ++k) smax[k] = 0.0;
+#pragma unroll 1
+  for (int col = w; col < CW && x0 + col < nx; col += TILE_WAVES) {
+    // every lane reads and writes its own slots of the wave's column only
+    auto load_U = [&](double* U) {
+      asm volatile("" ::: "memory");  // re-read LDS rather than keep U live in registers
 #pragma unroll
-    for (int f = 0; f < F; ++f) Un[f] = U[f] - dt * Un[f];
-  }
-  if (!SEP) __syncthreads();  // everyone has read its column of the input tile
-  if (writer) {
+      for (int f = 0; f < F; ++f) U[f] = tileU[G::at(f, lane, col)];
+    };
+    // transverse phi offsets: b along x, c along the other axis (3-D)
+    auto phi_at = [&](int b, int c) -> double {
+      const int64_t xx = bc_map(x0 + col + b - 1, nx, P.bc[0]);
+      const int64_t jj = bc_map(j0 + lane, nm, P.bc[DIR]);
+      const int64_t oo = (D == 3) ? bc_map(o + c - 1, no, P.bc[oa]) : 0;
+      return in[xx * sx + jj * sm + oo * so];
+    };
+    // lane_sweep orders the transverse offsets over the other two axes in
+    // increasing axis order: for DIR = 1 that is (x, z), for DIR = 2 (x, y)
+    const bool writer = (lane >= 3) && (lane < 61) && (j0 + lane < nm);
+    const int64_t jl = j0 + lane;
+    const bool wall = WALL && ((jl == 0 && (P.bc[DIR] == BC_REFLECTIVE || P.bc[DIR] == BC_AXIS)) ||
+                               (jl == nm && P.bc[DIR] == BC_REFLECTIVE));
+    double Un[F], s[D];
+    if constexpr (PROF == PROF_CALIB)
+      calib::lane_sweep<DIR, FUSE>(P, load_U, phi_at, dt / P.dx[DIR], dt, writer, Un, s, wall);
+    else if (MODE == M_SPLIT)
+      lane_sweep<D, N, RX, DIR, FUSE>(P, load_U, phi_at, dt * P.idx[DIR], dt, writer, Un, s, wall);
+    else
+      lane_sweep<D, N, RX, DIR, false, true>(P, load_U, phi_at, P.idx[DIR], dt, writer, Un, s, wall);
+    if (MODE == M_RK_FIRST && writer) {
+      // q - dt D_y(q) (the input tile still holds q)
+      double U[F];
+      load_U(U);
 #pragma unroll
-    for (int f = 0; f < F; ++f) tileO[G::at(f, lane, w)] = Un[f];
+      for (int f = 0; f < F; ++f) Un[f] = U[f] - dt * Un[f];
+    }
+    if (writer) {
+#pragma unroll
+      for (int f = 0; f < F; ++f) tileU[G::at(f, lane, col)] = Un[f];
+    }
+#pragma unroll
+    for (int k = 0; k < D; ++k) smax[k] = (s[k] > smax[k] || s[k] != s[k]) ? s[k] : smax[k];
   }
   __syncthreads();
-  for (int t = tid; t < 64 * CW; t += 64 * CW) {
+  for (int t = tid; t < 64 * CW; t += 64 * TILE_WAVES) {
     const int r = t / CW, c = t % CW;
     const int64_t xx = x0 + c, jj = j0 + r;
     if (r >= 3 && r < 61 && xx < nx && jj < nm) {
       const int64_t cell = xx * sx + jj * sm + o * so;
       if (MODE == M_SPLIT) {
 #pragma unroll
-        for (int f = 0; f < F; ++f) out[f * nc + cell] = tileO[G::at(f, r, c)];
+        for (int f = 0; f < F; ++f) out[f * nc + cell] = tileU[G::at(f, r, c)];
       } else {
         // the stage's partial result: the tile holds D_z (mid) or
         // q - dt D_y (first)
         const double a = rk_a(stage), b = rk_b(stage);
 #pragma unroll
         for (int f = 0; f < F; ++f) {
-          const double d = tileO[G::at(f, r, c)];
+          const double d = tileU[G::at(f, r, c)];
           double v;
           if (MODE == M_RK_MID)
             v = Rin[f * nc + cell] - (b * dt) * d;
@@ -299,9 +280,9 @@ __global__ __launch_bounds__(64 * CW, (sweep_waves<D, N, RX, PROF, FUSE>())) voi
     }
   }
   if (FUSE && MODE == M_SPLIT) {
-    const int64_t slot = lb * CW + (tid >> 6);
+    const int64_t slot = lb * TILE_WAVES + w;
 #pragma unroll
-    for (int k = 0; k < D; ++k) wave_max_store(s[k], part + slot * 3 + k);
+    for (int k = 0; k < D; ++k) wave_max_store(smax[k], part + slot * 3 + k);
   }
 }
 
@@ -316,29 +297,27 @@ template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int MODE = M_SPLIT
 static void launch_tile(const Params& P, const double* in, double* out, double dt, const double* dtp,
                         double* part, hipStream_t st, const double* Rin = nullptr, const double* qn = nullptr,
                         int stage = 0) {
-  constexpr int CW = TILE_COLUMNS;
+  constexpr int CW = tile_columns(D, FUSE);
   using L = Lay<D, N, RX>;
   const int oa = (DIR == 1) ? 2 : 1;
   const int64_t no = (D == 3) ? P.n[oa] : 1;
-  const int64_t nblocks = ((P.n[0] + CW - 1) / CW) * no * ((P.n[DIR] + 57) / 58);
-  const int64_t grid = ((nblocks + 7) / 8) * 8;
-  const size_t lds = sizeof(double) * TileGeom<CW>::template lds_doubles<L::F, sweep_waves<D, N, RX, PROF, FUSE>()>();
+  const int64_t grid = ((P.n[0] + CW - 1) / CW) * no * ((P.n[DIR] + 57) / 58);
+  const size_t lds = sizeof(double) * L::F * 64 * CW;
   if constexpr (PROF != PROF_CALIB) {  // (those grids have no walls)
     if (P.bc[DIR] >= BC_REFLECTIVE) {
-      hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE, true>), dim3((unsigned)grid), dim3(64 * CW),
-                         lds, st, P, in, out, dt, dtp, part, nblocks, Rin, qn, stage);
+      hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE, true>), dim3((unsigned)grid), dim3(64 * TILE_WAVES),
+                         lds, st, P, in, out, dt, dtp, part, Rin, qn, stage);
       return;
     }
   }
-  hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE>), dim3((unsigned)grid), dim3(64 * CW), lds, st, P,
-                     in, out, dt, dtp, part, nblocks, Rin, qn, stage);
+  hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE>), dim3((unsigned)grid), dim3(64 * TILE_WAVES), lds, st, P,
+                     in, out, dt, dtp, part, Rin, qn, stage);
 }
 
 static inline int row_grid(const Params& P) {
   const int64_t nseg = (P.n[0] + 57) / 58;
   const int64_t waves = nseg * P.n[1] * P.n[2];
-  const int64_t nblocks = (waves * 64 + 255) / 256;  // four waves a block
-  return (int)(((nblocks + 7) / 8) * 8);
+  return (int)((waves + 3) / 4);  // four waves a block
 }
 
 template <int D, int N, int RX, int PROF>
