@@ -29,48 +29,46 @@ namespace dimp {
 
 constexpr int PD = 2;
 // waves per SIMD of the patch sweeps: 2 with a JWL mixture (its split holds
-// more live state) or three materials, else 3
-template <int N, int RX>
+// more live state) or three materials, 4 where the state fits 128 VGPRs (a
+// material profile without a history slot), else 3
+template <int N, int RX, int PROF>
 constexpr int patch_waves() {
-  return (RX == 2 || N > 2) ? 2 : 3;
+  if (RX == 2 || N > 2) return 2;
+  return (RX == 0 && PROF != PROF_ANY) ? 4 : 3;
 }
 
-// write a value of interior cell (i, j) and, for boundary cells, its ghost
-// images (the cell itself on the interior rows/columns it borders)
-__device__ __forceinline__ void put_row(double* o, int64_t r, int i, int nx, double v) {
-  o[r + i] = v;
-  if (i == 0) {
-    o[r - 1] = v;
-    o[r - 2] = v;
-  }
-  if (i == nx - 1) {
-    o[r + nx] = v;
-    o[r + nx + 1] = v;
-  }
+// where a thread writes its cell: {element (low, high word), row pitch, sides
+// of the patch it borders: 1 x low, 2 x high, 4 y low, 8 y high; -1 nothing to
+// write}; parked in LDS while the sweep runs (in registers it pushed them past
+// 128: 48 spilled bytes a lane)
+__device__ __forceinline__ int4 patch_pos(const PatchGeo& g, int i, int j, bool live) {
+  const int pitch = g.nx + 2 * PATCH_GHOST;
+  const int64_t o = g.off + (int64_t)(j + PATCH_GHOST) * pitch + PATCH_GHOST + i;
+  const int edge = (i == 0 ? 1 : 0) | (i == g.nx - 1 ? 2 : 0) | (j == 0 ? 4 : 0) | (j == g.ny - 1 ? 8 : 0);
+  return make_int4((int)(uint32_t)o, (int)(o >> 32), pitch, live ? edge : -1);
 }
 
-__device__ __forceinline__ void write_with_ghosts(const PatchGeo& g, double* out, int64_t E, int f, int i, int j,
-                                                  double v) {
-  const int64_t pitch = g.nx + 2 * PATCH_GHOST;
-  double* o = out + f * E + g.off + PATCH_GHOST;
-  put_row(o, (j + PATCH_GHOST) * pitch, i, g.nx, v);
-  if (j == 0) {
-    put_row(o, (PATCH_GHOST - 1) * pitch, i, g.nx, v);
-    put_row(o, (PATCH_GHOST - 2) * pitch, i, g.nx, v);
-  }
-  if (j == g.ny - 1) {
-    put_row(o, (g.ny + PATCH_GHOST) * pitch, i, g.nx, v);
-    put_row(o, (g.ny + PATCH_GHOST + 1) * pitch, i, g.nx, v);
-  }
-}
-
-// XCD-aware block order: the hardware deals consecutive blocks round-robin
-// to the 8 XCDs; remapping gives each XCD a contiguous run of tasks, so
-// neighbouring rows/tiles of one patch share that XCD's L2.
-__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb) {
-  const int64_t per = nb >> 3;
-  const int64_t xcd = b & 7, k = b >> 3;
-  return (b < (per << 3)) ? xcd * per + k : b;
+// write the cell at pos, v(f) its fields, and, on a side, its ghost images; the
+// conditions are taken once for all fields
+template <int F, class V>
+__device__ __forceinline__ void write_with_ghosts(const int4& pos, double* out, int64_t E, V&& v) {
+  const int edge = pos.w;
+  if (edge < 0) return;
+  double* o = out + (((int64_t)pos.y << 32) | (uint32_t)pos.x);
+#pragma unroll
+  for (int f = 0; f < F; ++f) o[f * E] = v(f);
+  if (edge == 0) return;
+  const int di0 = (edge & 1) ? -PATCH_GHOST : 0, di1 = (edge & 2) ? PATCH_GHOST : 0;
+  const int dj0 = (edge & 4) ? -PATCH_GHOST : 0, dj1 = (edge & 8) ? PATCH_GHOST : 0;
+#pragma unroll 1
+  for (int dj = dj0; dj <= dj1; ++dj)
+#pragma unroll 1
+    for (int di = di0; di <= di1; ++di) {
+      if (di == 0 && dj == 0) continue;
+      double* q = o + (int64_t)dj * pos.z + di;
+#pragma unroll
+      for (int f = 0; f < F; ++f) q[f * E] = v(f);
+    }
 }
 
 // segment of lane (or tile row) r among segments [sb, se): the last one
@@ -85,7 +83,7 @@ __device__ __forceinline__ int4 segment_of(const int4* __restrict__ seg, int sb,
 }
 
 template <int N, int RX, int PROF, bool FUSE, int WPB>
-__global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX>())) void psweep_row(
+__global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX, PROF>())) void psweep_row(
     Params P, const PatchGeo* __restrict__ geo, WorkList wl, int64_t w0, int64_t nwork, const double* __restrict__ in,
     double* __restrict__ out, double dt_arg, const double* __restrict__ dtp, double* __restrict__ part) {
   constexpr int F = Lay<PD, N, RX>::F;
@@ -126,12 +124,12 @@ __global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX>())) void psweep_row(
     return in[b == 0 ? (j > 0 ? cell - pitch : cell) : (j < g.ny - 1 ? cell + pitch : cell)];
   };
   const bool writer = (q >= SEG_HALO) && (q < ncl + SEG_HALO);
+  __shared__ int4 pos[64 * WPB];
+  pos[threadIdx.x] = patch_pos(g, x, j, writer);
   double Un[F], s[PD];
   lane_sweep<PD, N, RX, 0, FUSE>(P, load_U, phi_at, nu, dt, writer, Un, s);
-  if (writer) {
-#pragma unroll
-    for (int f = 0; f < F; ++f) write_with_ghosts(g, out, E, f, x, j, Un[f]);
-  }
+  asm volatile("" ::: "memory");
+  write_with_ghosts<F>(pos[threadIdx.x], out, E, [&](int f) { return Un[f]; });
   if (FUSE) {
 #pragma unroll
     for (int k = 0; k < PD; ++k) wave_max_store(s[k], part + (w0 + wv) * 3 + k);
@@ -139,21 +137,20 @@ __global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX>())) void psweep_row(
 }
 
 template <int N, int RX, int PROF, bool FUSE, int CW>
-__global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
+__global__ __launch_bounds__(64 * CW, (patch_waves<N, RX, PROF>())) void psweep_tile(
     Params P, const PatchGeo* __restrict__ geo, WorkList wl, int64_t w0, int64_t nwork, const double* __restrict__ in,
     double* __restrict__ out, double dt_arg, const double* __restrict__ dtp, double* __restrict__ part) {
   constexpr int F = Lay<PD, N, RX>::F;
   assume_profile<N, RX, PROF>(P);
-  constexpr int PITCH = CW + 1;
-  extern __shared__ double lds[];
-  double* tileU = lds;
+  using G = TileGeom<CW>;
+  extern __shared__ double tileU[];  // the input state, then the results in place
   const int64_t t = xcd_block(blockIdx.x, gridDim.x);
   if (t >= nwork) return;  // whole block: a work item is one tile
   const double dt = dtp ? dtp[0] : dt_arg;
   const double nu = dt * P.idx[1];
   const int64_t E = P.ncell;
   const int tid = threadIdx.x;
-  const int w = tid >> 6, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int sb = wl.beg[w0 + t], se = wl.beg[w0 + t + 1];
   // this thread's tile element (row r, column c) for the load and the store
   const int r = tid / CW, c = tid % CW;
@@ -167,13 +164,15 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
     const int jc = jr < 0 ? 0 : (jr > gr.ny - 1 ? gr.ny - 1 : jr);
     const int64_t cell = gr.off + (jc + PATCH_GHOST) * pr + PATCH_GHOST + xc;
 #pragma unroll
-    for (int f = 0; f < F; ++f) tileU[(f * 64 + r) * PITCH + c] = in[f * E + cell];
+    for (int f = 0; f < F; ++f) tileU[G::at(f, r, c)] = in[f * E + cell];
   }
+  __shared__ int4 pos[64 * CW];
+  pos[tid] = patch_pos(gr, xr, jr, qr >= SEG_HALO && qr < (sr.w >> 8) + SEG_HALO && xr < gr.nx);
   __syncthreads();
   auto load_U = [&](double* U) {
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int f = 0; f < F; ++f) U[f] = tileU[(f * 64 + lane) * PITCH + w];
+    for (int f = 0; f < F; ++f) U[f] = tileU[G::at(f, lane, w)];  // (the lane's own slots)
   };
   const int4 sl = segment_of(wl.seg, sb, se, lane);
   const PatchGeo gl = geo[sl.x];
@@ -188,16 +187,12 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
   };
   double Un[F], s[PD];
   lane_sweep<PD, N, RX, 1, FUSE>(P, load_U, phi_at, nu, dt, writer, Un, s);
-  __syncthreads();
   if (writer) {
 #pragma unroll
-    for (int f = 0; f < F; ++f) tileU[(f * 64 + lane) * PITCH + w] = Un[f];
+    for (int f = 0; f < F; ++f) tileU[G::at(f, lane, w)] = Un[f];
   }
   __syncthreads();
-  if (qr >= SEG_HALO && qr < (sr.w >> 8) + SEG_HALO && xr < gr.nx) {
-#pragma unroll
-    for (int f = 0; f < F; ++f) write_with_ghosts(gr, out, E, f, xr, jr, tileU[(f * 64 + r) * PITCH + c]);
-  }
+  write_with_ghosts<F>(pos[tid], out, E, [&](int f) { return tileU[G::at(f, tid / CW, tid % CW)]; });
   if (FUSE) {
 #pragma unroll
     for (int k = 0; k < PD; ++k) wave_max_store(s[k], part + ((w0 + t) * CW + w) * 3 + k);
@@ -206,7 +201,7 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX>())) void psweep_tile(
 
 template <int N, int RX, int CW>
 size_t tile_lds_bytes() {
-  return sizeof(double) * (Lay<PD, N, RX>::F * 64 * (CW + 1));
+  return sizeof(double) * Lay<PD, N, RX>::F * 64 * CW;
 }
 
 // one sweep of a patch set with N materials and the RX layout (the
