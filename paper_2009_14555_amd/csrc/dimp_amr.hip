@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void k_amr_flux(Params P, FaceSet fs, const do
   auto phi_at = [&](int b, int) -> double { return in[at(a, tr + b - 1)]; };
   FaceV<D, N, RX> fa;
   double irho0;
-  lane_face<D, N, RX, DIR, RK>(P, load_U, phi_at, RK ? P.idx[DIR] : dt * P.idx[DIR], fa, irho0, false);
+  lane_face<D, N, RX, DIR, RK, PROF>(P, load_U, phi_at, RK ? P.idx[DIR] : dt * P.idx[DIR], fa, irho0, false);
   (void)irho0;
   if (live && l == 3) {
 #pragma unroll

@@ -148,6 +148,24 @@ __device__ __forceinline__ void assume_profile(const Params& P) {
   }
 }
 
+// The parameters, read anew from the kernel's arguments (P must be the kernel's
+// first; PROF < 0: P itself).  The compiler reads what a kernel uses of them
+// once, at its start, and parks what exceeds the 100 scalar registers in vector
+// lanes: a fused sweep of a JWL mixture had 1640-3100 lane reads among its 11800
+// instructions and a three-material one 1389-1761, and the parked values took
+// 15-30 vector registers.  Read anew at each stage (half step, flux, sources)
+// they come through the scalar cache: 530-760 and 33-51 lane reads left, 165
+// vector registers instead of 180-193; 256^3 12160 -> 11880 us.
+template <int N, int RX, int PROF>
+__device__ __forceinline__ const Params& fresh(const Params& P) {
+  if constexpr (PROF < 0) return P;
+  auto* p = (const __attribute__((address_space(4))) Params*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  const Params& q = *(const Params*)p;
+  assume_profile<N, RX, PROF>(q);
+  return q;
+}
+
 // f(std::integral_constant<int, PROF>) for the profile that P states, among
 // the ones compiled for N materials and the RX layout
 template <int N, int RX, class Fn>

@@ -122,7 +122,7 @@ __device__ __forceinline__ void lane_bvd(const Params& P, const double* Wm, cons
 // lane's cell (fa; wall: that face is a reflective wall), and the cell's
 // 1 / (sum of partial densities); it depends on the cells 3 to the left and
 // 2 to the right.  lane_sweep adds the update.
-template <int D, int N, int RX, int DIR, bool RK, class LoadU, class PhiAt>
+template <int D, int N, int RX, int DIR, bool RK, int PROF = -1, class LoadU, class PhiAt>
 __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, PhiAt&& phi_at, double nu,
                                           FaceV<D, N, RX>& fa, double& irho0, bool wall) {
   using L = Lay<D, N, RX>;
@@ -157,21 +157,21 @@ __device__ __forceinline__ void lane_face(const Params& P, LoadU&& load_U, PhiAt
     }
     if (__builtin_amdgcn_ballot_w64(mixed) != 0) lane_bvd<D, N, RX, DIR>(P, Wm, W, Wp, phi_at, WL, WR, jump);
   }
-  if (!RK) edges_half_step<D, N, RX, DIR>(P, W, jump, irho0, rc2, nu, WL, WR);
+  if (!RK) edges_half_step<D, N, RX, DIR>(fresh<N, RX, PROF>(P), W, jump, irho0, rc2, nu, WL, WR);
   // face on the left of this cell: right edge of the left neighbour | my left edge
   double WRm[F];
 #pragma unroll
   for (int f = 0; f < F; ++f) WRm[f] = from_left(WR[f]);
-  face_flux<D, N, RX, DIR>(P, WRm, WL, fa, wall);
+  face_flux<D, N, RX, DIR>(fresh<N, RX, PROF>(P), WRm, WL, fa, wall);
 }
 
-template <int D, int N, int RX, int DIR, bool FUSE, bool RK = false, class LoadU, class PhiAt>
+template <int D, int N, int RX, int DIR, bool FUSE, bool RK = false, int PROF = -1, class LoadU, class PhiAt>
 __device__ __forceinline__ void lane_sweep(const Params& P, LoadU&& load_U, PhiAt&& phi_at, double nu,
                                            double dt, bool writer, double* Un, double* s, bool wall = false) {
   constexpr int F = Lay<D, N, RX>::F;
   FaceV<D, N, RX> fa, fb;
   double irho0;
-  lane_face<D, N, RX, DIR, RK>(P, load_U, phi_at, nu, fa, irho0, wall);
+  lane_face<D, N, RX, DIR, RK, PROF>(P, load_U, phi_at, nu, fa, irho0, wall);
 #pragma unroll
   for (int f = 0; f < F; ++f) fb.F[f] = from_right(fa.F[f]);
   fb.ustar = from_right(fa.ustar);
@@ -187,7 +187,7 @@ __device__ __forceinline__ void lane_sweep(const Params& P, LoadU&& load_U, PhiA
   }
 #pragma unroll
   for (int k = 0; k < D; ++k) s[k] = 0.0;
-  if (FUSE && !RK && writer) epilogue_cell<D, N, RX>(P, Un, dt, s);
+  if (FUSE && !RK && writer) epilogue_cell<D, N, RX, PROF>(fresh<N, RX, PROF>(P), Un, dt, s);
 }
 
 }  // namespace dimp

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX, PROF>())) void psweep
   __shared__ int4 pos[64 * WPB];
   pos[threadIdx.x] = patch_pos(g, x, j, writer);
   double Un[F], s[PD];
-  lane_sweep<PD, N, RX, 0, FUSE>(P, load_U, phi_at, nu, dt, writer, Un, s);
+  lane_sweep<PD, N, RX, 0, FUSE, false, PROF>(P, load_U, phi_at, nu, dt, writer, Un, s);
   asm volatile("" ::: "memory");
   write_with_ghosts<F>(pos[threadIdx.x], out, E, [&](int f) { return Un[f]; });
   if (FUSE) {
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX, PROF>())) void psweep_
     return in[gl.off + (jc + PATCH_GHOST) * (int64_t)(gl.nx + 2 * PATCH_GHOST) + PATCH_GHOST + xc];
   };
   double Un[F], s[PD];
-  lane_sweep<PD, N, RX, 1, FUSE>(P, load_U, phi_at, nu, dt, writer, Un, s);
+  lane_sweep<PD, N, RX, 1, FUSE, false, PROF>(P, load_U, phi_at, nu, dt, writer, Un, s);
   if (writer) {
 #pragma unroll
     for (int f = 0; f < F; ++f) tileU[G::at(f, lane, w)] = Un[f];

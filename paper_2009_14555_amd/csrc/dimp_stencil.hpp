@@ -726,11 +726,11 @@ __device__ __forceinline__ void wavespeed_cell(const Params& P, const double* U,
 // reactive mixture the plastic weights phi_l/Gamma_l need no pressure, so the
 // phase densities and velocity are computed once and only the strain-
 // dependent closures are evaluated again for the wave speed.
-template <int D, int N, int RX>
+template <int D, int N, int RX, int PROF = -1>
 __device__ __forceinline__ void epilogue_cell(const Params& P, double* U, double dt, double s[D]) {
   if (RX) {
     plastic_cell<D, N, RX>(P, U, dt);
-    reaction_cell<D, N, RX, true>(P, U, dt, s);
+    reaction_cell<D, N, RX, true>(fresh<N, RX, PROF>(P), U, dt, s);
     return;
   }
   using L = Lay<D, N, RX>;

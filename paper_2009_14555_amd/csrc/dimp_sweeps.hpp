@@ -32,16 +32,16 @@ namespace dimp {
 constexpr int TILE_WAVES = 4;
 constexpr int tile_columns(int D, bool fuse) { return (D == 3 && !fuse) ? 8 : 4; }
 // waves per SIMD the sweep kernels are built for (launch bound): four where
-// the state fits 128 VGPRs, the 1-D and 2-D instances of a material profile
-// without a history slot (124-126; at five waves they spill 120 bytes a lane);
-// three (168) with a history slot (134-167) and for the general and calibrated
-// instances; the 3-D sweeps (nine stretch entries, up to 17 fields) need
-// 185-200 VGPRs and run two without spilling, and so do the sweeps of a JWL
-// mixture (its Newton split inlined) and of three materials
+// the state fits 128 VGPRs, the 1-D and 2-D instances of a two-material profile
+// without a history slot (122-126; at five waves they spill 120 bytes a lane);
+// three (168) with a history slot, for three materials and for the general and
+// calibrated instances (134-167); the 3-D sweeps (nine stretch entries, up to
+// 17 fields) need 176-182 VGPRs and run two without spilling, and so do the
+// fused sweeps of a JWL mixture (207) and of three reacting materials
 template <int D, int N, int RX, int PROF, bool FUSE>
 constexpr int sweep_waves() {
-  if (D == 3 || RX == 2 || N > 2) return 2;
-  return (RX == 0 && PROF != PROF_ANY && PROF != PROF_CALIB) ? 4 : 3;
+  if (D == 3 || (FUSE && (RX == 2 || (RX && N > 2)))) return 2;
+  return (N == 2 && RX == 0 && PROF != PROF_ANY && PROF != PROF_CALIB) ? 4 : 3;
 }
 
 // Output modes of the sweep kernels.  M_SPLIT: the split sweep, out = the
@@ -122,9 +122,9 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE>())) void sw
   if constexpr (PROF == PROF_CALIB) {
     calib::lane_sweep<0, FUSE>(P, load_U, phi_at, dt / P.dx[0], dt, writer, Un, s, wall);
   } else if (MODE == M_SPLIT) {
-    lane_sweep<D, N, RX, 0, FUSE>(P, load_U, phi_at, dt * P.idx[0], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, 0, FUSE, false, PROF>(P, load_U, phi_at, dt * P.idx[0], dt, writer, Un, s, wall);
   } else {
-    lane_sweep<D, N, RX, 0, false, true>(P, load_U, phi_at, P.idx[0], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, 0, false, true, PROF>(P, load_U, phi_at, P.idx[0], dt, writer, Un, s, wall);
     if (writer) {
       const double b = rk_b(stage);
       if (D > 1) {
@@ -236,9 +236,9 @@ __global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE>
     if constexpr (PROF == PROF_CALIB)
       calib::lane_sweep<DIR, FUSE>(P, load_U, phi_at, dt / P.dx[DIR], dt, writer, Un, s, wall);
     else if (MODE == M_SPLIT)
-      lane_sweep<D, N, RX, DIR, FUSE>(P, load_U, phi_at, dt * P.idx[DIR], dt, writer, Un, s, wall);
+      lane_sweep<D, N, RX, DIR, FUSE, false, PROF>(P, load_U, phi_at, dt * P.idx[DIR], dt, writer, Un, s, wall);
     else
-      lane_sweep<D, N, RX, DIR, false, true>(P, load_U, phi_at, P.idx[DIR], dt, writer, Un, s, wall);
+      lane_sweep<D, N, RX, DIR, false, true, PROF>(P, load_U, phi_at, P.idx[DIR], dt, writer, Un, s, wall);
     if (MODE == M_RK_FIRST && writer) {
       // q - dt D_y(q) (the input tile still holds q)
       double U[F];
