@@ -56,21 +56,59 @@ __device__ __forceinline__ EosB eosb_zero() {
 }
 
 // ---------------------------------------------------------------- closures
+// GS below: the materials are a gas first and a solid with exponents 1 and 3
+// second (the profile PROF_GAS_SOLID).  It is stated to the reverse stages only:
+// the forward stages that they repeat must round as the forward kernels do, and
+// the compiler fuses products differently where it knows more.
+
+// x^a, x^(a-1), x^b, x^(b+1)
+template <bool GS>
+__device__ __forceinline__ void powers(const MatP& m, double x, double& xa, double& xa1, double& xb, double& xb1) {
+  if (GS || m.abar_one) {
+    xa = x;
+    xa1 = 1.0;
+  } else {
+    xa = pow(x, m.abar);
+    xa1 = pow(x, m.abar - 1.0);
+  }
+  if (GS || m.bbar_three) {
+    const double x2 = x * x;
+    xb = x2 * x;
+    xb1 = x2 * x2;
+  } else {
+    xb = pow(x, m.bbar);
+    xb1 = pow(x, m.bbar + 1.0);
+  }
+}
+
+// the closure in a reverse stage
+template <bool GS>
+__device__ __forceinline__ EosV eos_of(const MatP& mat, int l, double rho, double irho, double J2) {
+  if constexpr (GS) {
+    MatP m = mat;
+    m.eos = l == 0 ? EOS_STIFFENED : EOS_ROMENSKII;
+    m.abar_one = m.bbar_three = 1;
+    return eos_eval(m, rho, irho, J2);
+  }
+  return eos_eval(mat, rho, irho, J2);
+}
+
 // adjoint of eos_eval at (rho, irho, J2): rho, irho and J2 are independent
 // inputs of the closure (as in the forward, which is handed both densities)
+template <bool GS>
 __device__ __forceinline__ void eos_bwd(const MatP& m, int l, double rho, double irho, double J2, const EosB& b,
                                         double& rb, double& ib, double& jb, PBar& pb, bool own) {
   pacc(pb.v[l][PB_GAM], own, b.Gam);
   pacc(pb.v[l][PB_IGAM], own, b.invGam);
-  if (m.eos != EOS_ROMENSKII) {
+  if (GS ? l == 0 : m.eos != EOS_ROMENSKII) {
     pacc(pb.v[l][PB_PREF], own, b.pref);
     pacc(pb.v[l][PB_EREF], own, b.eref);
     return;
   }
   const double a = m.abar, bb = m.bbar;
   const double x = rho * m.inv_rho0;
-  const double xa = pow(x, a);
-  const double xb1 = pow(x, bb + 1.0);
+  double xa, xa1, xb, xb1;  // x^a, x^(a-1), x^b, x^(b+1)
+  powers<GS>(m, x, xa, xa1, xb, xb1);
   const double G = m.G0 * xb1;
   const double GJ = G * J2;
   const double pc = m.K0a * x * xa * (xa - 1.0);
@@ -85,22 +123,25 @@ __device__ __forceinline__ void eos_bwd(const MatP& m, int l, double rho, double
   const double Gb = b.G + GJb * J2;
   jb += GJb * G;
   pacc(pb.v[l][PB_G0], own, Gb * xb1);
-  double xbar = Gb * m.G0 * (bb + 1.0) * pow(x, bb);
+  double xbar = Gb * m.G0 * (bb + 1.0) * xb;
   xbar += pcb * m.K0a * xa * (xa - 1.0);
   double xab = pcb * m.K0a * x * (2.0 * xa - 1.0);
   xab += ecb * m.ec_coef * 2.0 * (xa - 1.0);
   xab += dpcb * m.dpc_coef * (2.0 * (2.0 * a + 1.0) * xa - (a + 1.0));
-  xbar += xab * a * pow(x, a - 1.0);
+  xbar += xab * a * xa1;
   rb += xbar * m.inv_rho0;
 }
 
 // adjoint of shear_modulus(m, rho) = G0 x^(b+1)
+template <bool GS>
 __device__ __forceinline__ void shear_bwd(const MatP& m, int l, double rho, double Gb, double& rb, PBar& pb,
                                           bool own) {
-  if (!m.shear) return;
+  if (GS ? l == 0 : !m.shear) return;
   const double x = rho * m.inv_rho0;
-  pacc(pb.v[l][PB_G0], own, Gb * pow(x, m.bbar + 1.0));
-  rb += Gb * m.G0 * (m.bbar + 1.0) * pow(x, m.bbar) * m.inv_rho0;
+  double xa, xa1, xb, xb1;
+  powers<GS>(m, x, xa, xa1, xb, xb1);
+  pacc(pb.v[l][PB_G0], own, Gb * xb1);
+  rb += Gb * m.G0 * (m.bbar + 1.0) * xb * m.inv_rho0;
 }
 
 // adjoint of c2_mat(e, rho, irho, p)
@@ -145,19 +186,22 @@ __device__ __forceinline__ void strain_bwd(const double* V, const double* Hb_in,
 // --------------------------------------------------- conserved -> primitive
 // Outputs of the forward used downstream in a sweep: W (all 11), irho0 =
 // 1/(m0+m1) and rc2 = rho c^2.  Ub accumulates.
+template <bool GS = false>
 __device__ __forceinline__ void c2p_bwd(const Params& P, const double* U, const double* Wb, double irb_out,
                                         double rc2b, double* Ub, PBar& pb, bool own) {
   using L = L2;
   const double phi[2] = {U[0], 1.0 - U[0]};
   const double m[2] = {U[L::M0], U[L::M0 + 1]};
-  double rho[2], irho[2];
+  double rho[2], irho[2], iphi[2], im[2];
 #pragma unroll
   for (int l = 0; l < 2; ++l) {
-    rho[l] = m[l] / phi[l];
-    irho[l] = phi[l] / m[l];
+    iphi[l] = frcp(phi[l]);
+    im[l] = frcp(m[l]);
+    rho[l] = m[l] * iphi[l];
+    irho[l] = phi[l] * im[l];
   }
   const double r = m[0] + m[1];
-  const double ir = 1.0 / r;
+  const double ir = frcp(r);
   double u[2], uu = 0.0;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -168,7 +212,7 @@ __device__ __forceinline__ void c2p_bwd(const Params& P, const double* U, const 
   calib::strain(U + L::V0, H, J2);
   EosV e[2];
 #pragma unroll
-  for (int l = 0; l < 2; ++l) e[l] = eos_eval(P.mat[l], rho[l], irho[l], J2);
+  for (int l = 0; l < 2; ++l) e[l] = eos_of<GS>(P.mat[l], l, rho[l], irho[l], J2);
   const double rhoe = U[L::E] - 0.5 * r * uu;
   double xi = 0.0, num = rhoe;
 #pragma unroll
@@ -176,7 +220,7 @@ __device__ __forceinline__ void c2p_bwd(const Params& P, const double* U, const 
     xi += phi[l] * e[l].invGam;
     num += phi[l] * (e[l].pref * e[l].invGam - rho[l] * e[l].eref);
   }
-  const double ixi = 1.0 / xi;
+  const double ixi = frcp(xi);
   const double p = num * ixi;
   double cl2[2], cnum = 0.0;
 #pragma unroll
@@ -231,7 +275,7 @@ __device__ __forceinline__ void c2p_bwd(const Params& P, const double* U, const 
   for (int k = 0; k < 2; ++k) ub[k] -= rhoeb * r * u[k];
   double J2b = 0.0;
 #pragma unroll
-  for (int l = 0; l < 2; ++l) eos_bwd(P.mat[l], l, rho[l], irho[l], J2, eb[l], rhob[l], irhob[l], J2b, pb, own);
+  for (int l = 0; l < 2; ++l) eos_bwd<GS>(P.mat[l], l, rho[l], irho[l], J2, eb[l], rhob[l], irhob[l], J2b, pb, own);
   double Hb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   double Vb[5] = {Wb[L::V0], Wb[L::V0 + 1], Wb[L::V0 + 2], Wb[L::V0 + 3], Wb[L::V0 + 4]};
   strain_bwd(U + L::V0, Hb, J2b, Vb);
@@ -247,8 +291,8 @@ __device__ __forceinline__ void c2p_bwd(const Params& P, const double* U, const 
   double mb[2] = {rb, rb};
 #pragma unroll
   for (int l = 0; l < 2; ++l) {
-    mb[l] += rhob[l] / phi[l] - irhob[l] * irho[l] / m[l];
-    phib[l] += -rhob[l] * rho[l] / phi[l] + irhob[l] / m[l];
+    mb[l] += rhob[l] * iphi[l] - irhob[l] * irho[l] * im[l];
+    phib[l] += -rhob[l] * rho[l] * iphi[l] + irhob[l] * im[l];
   }
   Ub[0] += phib[0] - phib[1];
   Ub[L::M0] += mb[0];
@@ -260,7 +304,7 @@ __device__ __forceinline__ void c2p_bwd(const Params& P, const double* U, const 
 __device__ __forceinline__ void vanalbada_bwd(double a, double b, double e2, double sb, double& ab, double& bb) {
   const double Nn = a * (b * b + e2) + b * (a * a + e2);
   const double Dd = a * a + b * b + 2.0 * e2;
-  const double iD = 1.0 / Dd;
+  const double iD = frcp(Dd);
   const double dNa = b * b + e2 + 2.0 * a * b, dNb = a * a + e2 + 2.0 * a * b;
   ab += sb * (dNa * Dd - Nn * 2.0 * a) * iD * iD;
   bb += sb * (dNb * Dd - Nn * 2.0 * b) * iD * iD;
@@ -322,20 +366,21 @@ __device__ __forceinline__ void cand_bwd(const Params& P, double qm, double q0, 
       double qminb = lob + hib;
       double qmaxb = 0.5 * (1.0 + A) * lob + 0.5 * (1.0 + g) * hib;
       const double gb = 0.5 * qmax * hib;
-      double Ab = 0.5 * qmax * lob + gb * (1.0 - tb * tb) / (den2 * den2);
-      double tbb = gb * (1.0 - A * A) / (den2 * den2);
+      const double iden2 = frcp(den2 * den2), itb = frcp(tb), ich = frcp(ch), iden = frcp(den);
+      double Ab = 0.5 * qmax * lob + gb * (1.0 - tb * tb) * iden2;
+      double tbb = gb * (1.0 - A * A) * iden2;
       // A = (Bv/ch - 1)/tb
-      const double Bvb = Ab / (ch * tb);
-      const double chb = -Ab * Bv / (ch * ch * tb);
-      tbb += -Ab * A / tb;
+      const double Bvb = Ab * itb * ich;
+      const double chb = -Bvb * Bv * ich;
+      tbb += -Ab * A * itb;
       // Bv = exp(beta (2C - 1))
       double betab = Bvb * Bv * (2.0 * C - 1.0);
       const double Cb = Bvb * Bv * 2.0 * beta;
       betab += chb * sh + tbb * (1.0 - tb * tb);
       // C = num / den
-      q0b += Cb / den;
-      qminb += -Cb / den;
-      qmaxb += -Cb * C / den;
+      q0b += Cb * iden;
+      qminb += -Cb * iden;
+      qmaxb += -Cb * C * iden;
       youngs2_bwd(st, P.dx, DIR, betab * P.beta0, stb);
       // qmax = max(qm, qp) - qmin, qmin = min(qm, qp)
       if (qm <= qp) {
@@ -361,7 +406,7 @@ __device__ __forceinline__ void cand_bwd(const Params& P, double qm, double q0, 
 
 // ---------------------------------------------------------------- stress
 // adjoint of stress_col<2,2,false,DIR>(W) for a primitive state W
-template <int DIR>
+template <int DIR, bool GS = false>
 __device__ __forceinline__ void stress_bwd(const Params& P, const double* W, const double sigb[3], double* Wb,
                                            PBar& pb, bool own) {
   using L = L2;
@@ -375,7 +420,7 @@ __device__ __forceinline__ void stress_bwd(const Params& P, const double* W, con
     xi += phi[l] * P.mat[l].invGam;
     gnum += phi[l] * Gl[l] * P.mat[l].invGam;
   }
-  const double G = gnum / xi;
+  const double ixi = frcp(xi), G = gnum * ixi;
   double H[6], J2;
   calib::strain(W + L::V0, H, J2);
   double Gb = 0.0, Hb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -384,8 +429,8 @@ __device__ __forceinline__ void stress_bwd(const Params& P, const double* W, con
     Gb += 2.0 * sigb[k] * H[hs(k, DIR)];
     Hb[hs(k, DIR)] += 2.0 * G * sigb[k];
   }
-  const double gnumb = Gb / xi;
-  const double xib = -Gb * G / xi;
+  const double gnumb = Gb * ixi;
+  const double xib = -Gb * G * ixi;
   double phib[2] = {0.0, 0.0};
 #pragma unroll
   for (int l = 0; l < 2; ++l) {
@@ -393,7 +438,7 @@ __device__ __forceinline__ void stress_bwd(const Params& P, const double* W, con
     phib[l] += gnumb * Gl[l] * g + xib * g;
     pacc(pb.v[l][PB_IGAM], own, (gnumb * phi[l] * Gl[l] + xib * phi[l]));
     double rb = 0.0;
-    shear_bwd(P.mat[l], l, W[L::M0 + l], gnumb * phi[l] * g, rb, pb, own);
+    shear_bwd<GS>(P.mat[l], l, W[L::M0 + l], gnumb * phi[l] * g, rb, pb, own);
     Wb[L::M0 + l] += rb;
   }
   Wb[0] += phib[0] - phib[1];
@@ -407,7 +452,7 @@ __device__ __forceinline__ void stress_bwd(const Params& P, const double* W, con
 // Adjoint of edges_predict<2,2,false,DIR>: WLb, WRb are the bars of the
 // returned edges.  Accumulates the bars of Wm, W0, Wp, irho0, rc2 and of the
 // cell's own candidates (mL, mR, tL, tR).
-template <int DIR>
+template <int DIR, bool GS = false>
 __device__ __forceinline__ void edges_bwd(const Params& P, const double* Wm, const double* W0, const double* Wp,
                                           double irho0, double rc2, const Cand& cm, const Cand& c0, const Cand& cp,
                                           double nu, const double* WLb_in, const double* WRb_in, double* Wmb,
@@ -522,8 +567,28 @@ __device__ __forceinline__ void edges_bwd(const Params& P, const double* Wm, con
     WRb[f] += dWb[f];
     WLb[f] -= dWb[f];
   }
-  stress_bwd<DIR>(P, WL, sLb, WLb, pb, own);
-  stress_bwd<DIR>(P, WR, sRb, WRb, pb, own);
+  if (P.any_shear) {
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {  // one copy for both edges
+      double W[F], Wb[F], sb[3];
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        W[f] = k ? WR[f] : WL[f];
+        Wb[f] = 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) sb[q] = k ? sRb[q] : sLb[q];
+      stress_bwd<DIR, GS>(P, W, sb, Wb, pb, own);
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        WLb[f] += k ? 0.0 : Wb[f];
+        WRb[f] += k ? Wb[f] : 0.0;
+      }
+    }
+  } else {
+    WLb[L::E] -= sLb[DIR];
+    WRb[L::E] -= sRb[DIR];
+  }
   // edges from slopes (phi: from the BVD choice)
   double sbar[F];
 #pragma unroll
@@ -568,7 +633,7 @@ __device__ __forceinline__ SideB sideb_zero() {
 }
 
 // adjoint of side_state<2,2,false,DIR>(W)
-template <int DIR>
+template <int DIR, bool GS = false>
 __device__ __forceinline__ void side_bwd(const Params& P, const double* W, const SideB& Sb, double* Wb, PBar& pb,
                                          bool own) {
   using L = L2;
@@ -577,13 +642,13 @@ __device__ __forceinline__ void side_bwd(const Params& P, const double* W, const
 #pragma unroll
   for (int l = 0; l < 2; ++l) {
     rho[l] = W[L::M0 + l];
-    irho[l] = 1.0 / rho[l];
+    irho[l] = frcp(rho[l]);
   }
   double H[6], J2;
   calib::strain(W + L::V0, H, J2);
   EosV e[2];
 #pragma unroll
-  for (int l = 0; l < 2; ++l) e[l] = eos_eval(P.mat[l], rho[l], irho[l], J2);
+  for (int l = 0; l < 2; ++l) e[l] = eos_of<GS>(P.mat[l], l, rho[l], irho[l], J2);
   const double p = W[L::E];
   double rhoe = 0.0, rhom = 0.0, xi = 0.0, gnum = 0.0;
 #pragma unroll
@@ -593,7 +658,7 @@ __device__ __forceinline__ void side_bwd(const Params& P, const double* W, const
     xi += phi[l] * e[l].invGam;
     gnum += phi[l] * e[l].G * e[l].invGam;
   }
-  const double irhom = 1.0 / rhom, ixi = 1.0 / xi;
+  const double irhom = frcp(rhom), ixi = frcp(xi);
   double cl2[2], cnum = 0.0;
 #pragma unroll
   for (int l = 0; l < 2; ++l) {
@@ -602,7 +667,7 @@ __device__ __forceinline__ void side_bwd(const Params& P, const double* W, const
   }
   const double Gmix = gnum * ixi, c2 = cnum * ixi;
   const double cL2 = c2 + (4.0 / 3.0) * Gmix * irhom;
-  const double cl = sqrt(cL2);
+  const double icl = frcp(fsqrt(cL2));
   const double u[2] = {W[L::MOM0], W[L::MOM0 + 1]};
   const double uu = u[0] * u[0] + u[1] * u[1];
   // ---- reverse
@@ -611,7 +676,7 @@ __device__ __forceinline__ void side_bwd(const Params& P, const double* W, const
   double pbar = 0.0;
   double Hb[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   EosB eb[2] = {eosb_zero(), eosb_zero()};
-  const double cL2b = Sb.cl * 0.5 / cl;
+  const double cL2b = Sb.cl * 0.5 * icl;
   double Gmixb = 0.0;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -661,7 +726,7 @@ __device__ __forceinline__ void side_bwd(const Params& P, const double* W, const
   double J2b = 0.0;
 #pragma unroll
   for (int l = 0; l < 2; ++l) {
-    eos_bwd(P.mat[l], l, rho[l], irho[l], J2, eb[l], rhob[l], irhob[l], J2b, pb, own);
+    eos_bwd<GS>(P.mat[l], l, rho[l], irho[l], J2, eb[l], rhob[l], irhob[l], J2b, pb, own);
     rhob[l] -= irhob[l] * irho[l] * irho[l];
   }
   double Vb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
@@ -799,7 +864,7 @@ __device__ __forceinline__ void star_bwd(const double* W, const Side<2, 2, false
 
 // Adjoint of face_flux<2,2,false,DIR>(WLf, WRf): accumulates the bars of the
 // left and right states.
-template <int DIR>
+template <int DIR, bool GS = false>
 __device__ __forceinline__ void face_bwd(const Params& P, const double* WLf, const double* WRf, const FaceB& Ob,
                                          double* WLb, double* WRb, PBar& pb, bool own) {
   using SD = Side<2, 2, false>;
@@ -811,7 +876,7 @@ __device__ __forceinline__ void face_bwd(const Params& P, const double* WLf, con
   const double SR = fmax(uL + A.cl, uR + B.cl);
   const double mL = A.rho * (SL - uL);
   const double mR = B.rho * (SR - uR);
-  const double iden = 1.0 / (mL - mR);
+  const double iden = frcp(mL - mR);
   double ust[2], unum[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
@@ -825,54 +890,67 @@ __device__ __forceinline__ void face_bwd(const Params& P, const double* WLf, con
   const bool tie = !sup && (Sst == 0.0);
   SideB Ab = sideb_zero(), Bb = sideb_zero();
   double SLb = 0.0, SRb = 0.0, mLb = 0.0, mRb = 0.0, ustb[2] = {0.0, 0.0};
-  if (!tie) {
-    const SD& SK = left ? A : B;
-    const double* WK = left ? WLf : WRf;
-    double* WKb = left ? WLb : WRb;
-    SideB& SKbar = left ? Ab : Bb;
-    const double S_K = left ? SL : SR;
-    const double m_K = left ? mL : mR;
-    const double a = sup ? 1.0 : S_K - SK.u[DIR];
-    const double inv = sup ? 1.0 : 1.0 / (S_K - Sst);
-    double SKb = 0.0, abar = 0.0, invb = 0.0, mKb = 0.0;
-    star_bwd<DIR>(WK, SK, sup ? 0.0 : S_K, a, inv, ust, m_K, Ob, WKb, SKbar, SKb, abar, invb, ustb, mKb);
-    if (!sup) {
-      // a = S_K - u_K,n ; inv = 1/(S_K - S*)
-      double S_Kb = SKb + abar - invb * inv * inv;
-      SKbar.u[DIR] -= abar;
-      ustb[DIR] += invb * inv * inv;
-      if (left) {
-        SLb += S_Kb;
-        mLb += mKb;
-      } else {
-        SRb += S_Kb;
-        mRb += mKb;
-      }
-    }
-  } else {
-    FaceB half;
+  // the star state's side, through one copy; where a lane of the wave ties, a
+  // second pass takes the tie's left side (each with half the weight)
+  const int passes = __builtin_amdgcn_ballot_w64(tie) != 0 ? 2 : 1;
+#pragma unroll 1
+  for (int k = 0; k < passes; ++k) {
+    if (k && !tie) continue;
+    const bool lf = k ? true : left;
+    const double wgt = tie ? 0.5 : 1.0;
+    double WK[F2], WKb[F2];
+    SD S;
+    FaceB O;
+    S.rho = lf ? A.rho : B.rho;
+    S.E = lf ? A.E : B.E;
+    S.cl = 0.0;
+    S.u[0] = lf ? A.u[0] : B.u[0];
+    S.u[1] = lf ? A.u[1] : B.u[1];
 #pragma unroll
-    for (int f = 0; f < F2; ++f) half.F[f] = 0.5 * Ob.F[f];
-    half.ustar = 0.5 * Ob.ustar;
-    half.Vn[0] = 0.5 * Ob.Vn[0];
-    half.Vn[1] = 0.5 * Ob.Vn[1];
-    {
-      const double a = SR - B.u[DIR], inv = 1.0 / (SR - Sst);
-      double SKb = 0.0, abar = 0.0, invb = 0.0, mKb = 0.0;
-      star_bwd<DIR>(WRf, B, SR, a, inv, ust, mR, half, WRb, Bb, SKb, abar, invb, ustb, mKb);
-      SRb += SKb + abar - invb * inv * inv;
-      Bb.u[DIR] -= abar;
-      ustb[DIR] += invb * inv * inv;
-      mRb += mKb;
+    for (int q = 0; q < 3; ++q) S.sig[q] = lf ? A.sig[q] : B.sig[q];
+#pragma unroll
+    for (int f = 0; f < F2; ++f) {
+      WK[f] = lf ? WLf[f] : WRf[f];
+      WKb[f] = 0.0;
+      O.F[f] = wgt * Ob.F[f];
     }
-    {
-      const double a = SL - A.u[DIR], inv = 1.0 / (SL - Sst);
-      double SKb = 0.0, abar = 0.0, invb = 0.0, mKb = 0.0;
-      star_bwd<DIR>(WLf, A, SL, a, inv, ust, mL, half, WLb, Ab, SKb, abar, invb, ustb, mKb);
-      SLb += SKb + abar - invb * inv * inv;
-      Ab.u[DIR] -= abar;
+    O.ustar = wgt * Ob.ustar;
+    O.Vn[0] = wgt * Ob.Vn[0];
+    O.Vn[1] = wgt * Ob.Vn[1];
+    const double S_K = lf ? SL : SR;
+    const double a = sup ? 1.0 : S_K - S.u[DIR];
+    const double inv = sup ? 1.0 : frcp(S_K - Sst);
+    SideB Kb = sideb_zero();
+    double SKb = 0.0, abar = 0.0, invb = 0.0, mKb = 0.0;
+    star_bwd<DIR>(WK, S, sup ? 0.0 : S_K, a, inv, ust, lf ? mL : mR, O, WKb, Kb, SKb, abar, invb, ustb, mKb);
+    // a = S_K - u_K,n ; inv = 1/(S_K - S*)
+    if (!sup) {
+      Kb.u[DIR] -= abar;
       ustb[DIR] += invb * inv * inv;
-      mLb += mKb;
+    }
+    const double S_Kb = sup ? 0.0 : SKb + abar - invb * inv * inv, m_Kb = sup ? 0.0 : mKb;
+    SLb += lf ? S_Kb : 0.0;
+    SRb += lf ? 0.0 : S_Kb;
+    mLb += lf ? m_Kb : 0.0;
+    mRb += lf ? 0.0 : m_Kb;
+    Ab.rho += lf ? Kb.rho : 0.0;
+    Bb.rho += lf ? 0.0 : Kb.rho;
+    Ab.E += lf ? Kb.E : 0.0;
+    Bb.E += lf ? 0.0 : Kb.E;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      Ab.u[j] += lf ? Kb.u[j] : 0.0;
+      Bb.u[j] += lf ? 0.0 : Kb.u[j];
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      Ab.sig[q] += lf ? Kb.sig[q] : 0.0;
+      Bb.sig[q] += lf ? 0.0 : Kb.sig[q];
+    }
+#pragma unroll
+    for (int f = 0; f < F2; ++f) {
+      WLb[f] += lf ? WKb[f] : 0.0;
+      WRb[f] += lf ? 0.0 : WKb[f];
     }
   }
   // ust_k = unum_k / (mL - mR)
@@ -911,8 +989,29 @@ __device__ __forceinline__ void face_bwd(const Params& P, const double* WLf, con
     Bb.u[DIR] += SRb;
     Bb.cl += SRb;
   }
-  side_bwd<DIR>(P, WLf, Ab, WLb, pb, own);
-  side_bwd<DIR>(P, WRf, Bb, WRb, pb, own);
+#pragma unroll 1
+  for (int k = 0; k < 2; ++k) {  // one copy for both sides
+    double W[F2], Wb[F2];
+    SideB Sb;
+    Sb.rho = k ? Bb.rho : Ab.rho;
+    Sb.E = k ? Bb.E : Ab.E;
+    Sb.cl = k ? Bb.cl : Ab.cl;
+    Sb.u[0] = k ? Bb.u[0] : Ab.u[0];
+    Sb.u[1] = k ? Bb.u[1] : Ab.u[1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) Sb.sig[q] = k ? Bb.sig[q] : Ab.sig[q];
+#pragma unroll
+    for (int f = 0; f < F2; ++f) {
+      W[f] = k ? WRf[f] : WLf[f];
+      Wb[f] = 0.0;
+    }
+    side_bwd<DIR, GS>(P, W, Sb, Wb, pb, own);
+#pragma unroll
+    for (int f = 0; f < F2; ++f) {
+      WLb[f] += k ? 0.0 : Wb[f];
+      WRb[f] += k ? Wb[f] : 0.0;
+    }
+  }
 }
 
 // ------------------------------------------------------------------ update
@@ -1107,7 +1206,7 @@ __device__ __forceinline__ void plastic_bwd(const Params& P, const double* U, co
         // Jl = Y6 / G_l
         pacc(pb.v[l][PB_Y], own, Jlb / Gl[l]);
         const double Gb = -Jlb * Jl[l] / Gl[l];
-        shear_bwd(mt, l, rho[l], Gb, rhob[l], pb, own);
+        shear_bwd<false>(mt, l, rho[l], Gb, rhob[l], pb, own);
       } else {
         Jb += Jlb;
       }
