@@ -24,23 +24,28 @@ namespace dimp {
 
 // A tile sweep's block has four waves and 4 or 8 columns (a wave takes its
 // columns one after the other).  Eight columns read and write 64 contiguous
-// bytes of a row instead of 32: 256^3, y 1757 -> 1549 us, z 2419 -> 2241.  With
-// the sources fused (z 3032, 3039) and on 2-D grids (2048^2: y 260, 262; fused
-// 269, 323) the second column costs what the wider rows gain or more (there
-// the LDS of eight columns holds three blocks a CU where four columns hold
-// four).
+// bytes of a row instead of 32: 256^3, y 1757 -> 1549 us, z 2419 -> 2241 (with
+// eight waves, and with 16 columns, slower by a third and more: the LDS of 17
+// fields holds one such block a CU).  With the sources fused (z 3032, 3039) and
+// on 2-D grids (2048^2: y 232, 249; fused 257, 260) the second column costs what
+// the wider rows gain or more; eight columns by eight waves there take 216 us
+// at 2048^2 but 7% longer a step at 601 x 480 and at 96 x 75, half as many blocks.
 constexpr int TILE_WAVES = 4;
 constexpr int tile_columns(int D, bool fuse) { return (D == 3 && !fuse) ? 8 : 4; }
+
 // waves per SIMD the sweep kernels are built for (launch bound): four where
 // the state fits 128 VGPRs, the 1-D and 2-D instances of a two-material profile
 // without a history slot (122-126; at five waves they spill 120 bytes a lane);
 // three (168) with a history slot, for three materials and for the general and
 // calibrated instances (134-167); the 3-D sweeps (nine stretch entries, up to
 // 17 fields) need 176-182 VGPRs and run two without spilling, and so do the
-// fused sweeps of a JWL mixture (207) and of three reacting materials
-template <int D, int N, int RX, int PROF, bool FUSE>
+// fused sweeps of a JWL mixture (207) and of three reacting materials; the fused
+// x sweep of a gas mixture spills 60 bytes at three waves and is the faster for
+// it (256^3: 2225 -> 2085 us; z fused 2430 -> 2920, x 1231 -> 1456)
+template <int D, int N, int RX, int PROF, bool FUSE, bool TILE>
 constexpr int sweep_waves() {
-  if (D == 3 || (FUSE && (RX == 2 || (RX && N > 2)))) return 2;
+  if (D == 3) return (FUSE && !TILE && RX == 1 && PROF != PROF_ANY) ? 3 : 2;
+  if (FUSE && (RX == 2 || (RX && N > 2))) return 2;
   return (N == 2 && RX == 0 && PROF != PROF_ANY && PROF != PROF_CALIB) ? 4 : 3;
 }
 
@@ -63,7 +68,7 @@ __device__ __forceinline__ double rk_b(int stage) { return stage == 1 ? 1.0 : st
 // Sweep along x.  Each wave: one 64-cell segment of one row, loaded and
 // stored straight from HBM (512-byte rows per field).
 template <int D, int N, int RX, int PROF, bool FUSE, int MODE = M_SPLIT, bool WALL = false>
-__global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE>())) void sweep_row(Params P, const double* __restrict__ in, double* __restrict__ out,
+__global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE, false>())) void sweep_row(Params P, const double* __restrict__ in, double* __restrict__ out,
                                                   double dt_arg, const double* __restrict__ dtp,
                                                   double* __restrict__ part, const double* __restrict__ Rin,
                                                   const double* qn, int stage) {
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE>())) void sw
 // per lane and runs the same stages as the row sweep.  The blocks
 // of a run (xcd_block) are neighbouring x chunks, which share L2 lines.
 template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false>
-__global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE>())) void sweep_tile(Params P, const double* __restrict__ in,
+__global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE, true>())) void sweep_tile(Params P, const double* __restrict__ in,
                                                        double* __restrict__ out, double dt_arg,
                                                        const double* __restrict__ dtp,
                                                        double* __restrict__ part,
