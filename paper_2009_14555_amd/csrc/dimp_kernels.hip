@@ -8,8 +8,6 @@
 
 namespace dimp {
 
-__device__ __forceinline__ double nanmax(double a, double b) { return (b > a || b != b) ? b : a; }
-
 // the block's maximum of s (a NaN wins) into the block's slot of part
 template <int D>
 __device__ __forceinline__ void block_max_store(const double s[D], double* part) {
@@ -249,46 +247,44 @@ __global__ void k_cfl_dt(unsigned long long* __restrict__ smax, double cfl, doub
 // the k_cfl_dt rule.  (One launch whose last block, found by a ticket counter,
 // does the second stage took 24 us at 2048^2 against 9.5 us for the two:
 // 288 returning atomics on one word.)  Up to REDUCE_ONE slots the second
-// stage, one block of 1024 threads, reads the slots themselves.
+// stage reads the slots themselves.  Its block is one wave up to 256 slots, four
+// up to 1024, else sixteen: a block's start and its barrier cost more than a few
+// loads a lane (18 slots of a 1000-cell tube: 16 waves 3.9 us, one 1.7).
 constexpr int64_t REDUCE_ONE = 2048;
 
-template <bool FINAL>
-__global__ __launch_bounds__(FINAL ? 1024 : 256) void k_reduce_smax(const double* __restrict__ part, int64_t nslots, int64_t chunk,
-                                                     int D, double* __restrict__ out,
-                                                     unsigned long long* __restrict__ smax, DtReq req) {
-  constexpr int NW = FINAL ? 16 : 4;
-  __shared__ double red[3][NW];
+template <int D, int T, bool FINAL>
+__global__ __launch_bounds__(T) void k_reduce_smax(const double* __restrict__ part, int64_t nslots, int64_t chunk,
+                                                   double* __restrict__ out, unsigned long long* __restrict__ smax,
+                                                   DtReq req) {
+  constexpr int NW = T / 64;
   const int64_t lo = (int64_t)blockIdx.x * chunk;
   const int64_t hi = lo + chunk < nslots ? lo + chunk : nslots;
   double m[3] = {0.0, 0.0, 0.0};
-  for (int64_t t = lo + threadIdx.x; t < hi; t += blockDim.x)
-    for (int k = 0; k < D; ++k) m[k] = nanmax(m[k], part[t * 3 + k]);
-  for (int k = 0; k < 3; ++k) {
+  for (int64_t t = lo + threadIdx.x; t < hi; t += T)
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m[k] = nanmax(m[k], __shfl_xor(m[k], off, 64));
+    for (int k = 0; k < D; ++k) m[k] = nanmax(m[k], part[t * 3 + k]);
+#pragma unroll
+  for (int k = 0; k < D; ++k) m[k] = wave_max(m[k]);
+  if (NW > 1) {
+    __shared__ double red[3][NW];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane == 63)
+#pragma unroll
+      for (int k = 0; k < D; ++k) red[k][w] = m[k];
+    __syncthreads();
+    if (w) return;
+#pragma unroll
+    for (int k = 0; k < D; ++k) m[k] = wave_max(lane < NW ? red[k][lane] : 0.0);
   }
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int k = 0; k < 3; ++k) red[k][w] = m[k];
-  __syncthreads();
+  if (threadIdx.x != 63) return;
   if (!FINAL) {
-    if (threadIdx.x < 3) {
-      const int k = threadIdx.x;
-      out[(int64_t)blockIdx.x * 3 + k] = nanmax(nanmax(red[k][0], red[k][1]), nanmax(red[k][2], red[k][3]));
-    }
+#pragma unroll
+    for (int k = 0; k < D; ++k) out[(int64_t)blockIdx.x * 3 + k] = m[k];
     return;
   }
-  if (threadIdx.x == 0) {
-    double s[3];
-    for (int k = 0; k < 3; ++k) {
-      double v = red[k][0];
 #pragma unroll
-      for (int q = 1; q < NW; ++q) v = nanmax(v, red[k][q]);
-      s[k] = (k < D) ? v : 0.0;
-      smax[k] = (k < D) ? (unsigned long long)__double_as_longlong(v) : 0ull;
-    }
-    if (req.dt) cfl_dt_from(s, smax, req.cfl, req.dx0, req.dx1, req.dx2, D, req.dt, req.log, req.idx);
-  }
+  for (int k = 0; k < 3; ++k) smax[k] = (unsigned long long)__double_as_longlong(m[k]);
+  if (req.dt) cfl_dt_from(m, smax, req.cfl, req.dx0, req.dx1, req.dx2, D, req.dt, req.log, req.idx);
 }
 
 // ---------------------------------------------------------------- launch
@@ -331,20 +327,37 @@ int64_t sweep_slots(const Params& P, int D, int dir) {
   return ((P.n[0] + CW - 1) / CW) * no * ((P.n[dir] + 57) / 58) * TILE_WAVES;
 }
 
-hipError_t launch_reduce_smax(const double* part, int64_t nslots, int D, double* scratch,
-                              unsigned long long* smax, hipStream_t st, const DtReq* req) {
-  const DtReq none{};
-  if (nslots <= REDUCE_ONE) {
-    hipLaunchKernelGGL(k_reduce_smax<true>, dim3(1), dim3(1024), 0, st, part, nslots, nslots, D, nullptr, smax,
-                       req ? *req : none);
-    return hipGetLastError();
-  }
+template <int D>
+static void reduce_smax(const double* part, int64_t nslots, double* scratch, unsigned long long* smax, hipStream_t st,
+                        const DtReq& req) {
+  auto last = [&](auto kernel, int T, const double* p, int64_t n) {
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(T), 0, st, p, n, n, nullptr, smax, req);
+  };
+  auto final_stage = [&](const double* p, int64_t n) {
+    if (n <= 256)
+      last(k_reduce_smax<D, 64, true>, 64, p, n);
+    else if (n <= 1024)
+      last(k_reduce_smax<D, 256, true>, 256, p, n);
+    else
+      last(k_reduce_smax<D, 1024, true>, 1024, p, n);
+  };
+  if (nslots <= REDUCE_ONE) return final_stage(part, nslots);
   const int64_t nb = reduce_smax_blocks(nslots);
   const int64_t chunk = (nslots + nb - 1) / nb;
-  hipLaunchKernelGGL(k_reduce_smax<false>, dim3((unsigned)nb), dim3(256), 0, st, part, nslots, chunk, D, scratch,
-                     smax, none);
-  hipLaunchKernelGGL(k_reduce_smax<true>, dim3(1), dim3(1024), 0, st, scratch, nb, nb, D, nullptr, smax,
-                     req ? *req : none);
+  hipLaunchKernelGGL((k_reduce_smax<D, 256, false>), dim3((unsigned)nb), dim3(256), 0, st, part, nslots, chunk,
+                     scratch, smax, DtReq{});
+  final_stage(scratch, nb);
+}
+
+hipError_t launch_reduce_smax(const double* part, int64_t nslots, int D, double* scratch,
+                              unsigned long long* smax, hipStream_t st, const DtReq* req) {
+  const DtReq q = req ? *req : DtReq{};
+  if (D == 1)
+    reduce_smax<1>(part, nslots, scratch, smax, st, q);
+  else if (D == 2)
+    reduce_smax<2>(part, nslots, scratch, smax, st, q);
+  else
+    reduce_smax<3>(part, nslots, scratch, smax, st, q);
   return hipGetLastError();
 }
 

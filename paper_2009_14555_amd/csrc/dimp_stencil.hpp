@@ -798,15 +798,39 @@ __device__ __forceinline__ void epilogue_cell(const Params& P, double* U, double
 }
 
 // --------------------------------------------------- wave max reduction
-// The wave maximum of v written by lane 0 to its own slot (no atomics: one
-// slot per wave, reduced afterwards in a fixed order).
+// Wave speeds are non-negative or NaN, so they order as their bit patterns do,
+// a NaN above all numbers.
+__device__ __forceinline__ double nanmax(double a, double b) {
+  return (unsigned long long)__double_as_longlong(b) > (unsigned long long)__double_as_longlong(a) ? b : a;
+}
+
+// v of the lane that the data-parallel move CTRL names (rows outside MASK and
+// lanes without a source keep their own)
+template <int CTRL, int MASK>
+__device__ __forceinline__ double dpp_from(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, MASK, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, MASK, 0xf, false));
+}
+
+// the maximum over lanes 0..63, in lane 63: within the rows of 16 lanes by shifts
+// of 1, 2, 4, 8, then from row to row (moves in registers; shuffles through
+// the LDS took about 100 cycles each)
+__device__ __forceinline__ double wave_max(double v) {
+  v = nanmax(v, dpp_from<0x111, 0xf>(v));
+  v = nanmax(v, dpp_from<0x112, 0xf>(v));
+  v = nanmax(v, dpp_from<0x114, 0xf>(v));
+  v = nanmax(v, dpp_from<0x118, 0xf>(v));
+  v = nanmax(v, dpp_from<0x142, 0xa>(v));  // row 0's last lane to row 1, row 2's to row 3
+  v = nanmax(v, dpp_from<0x143, 0xc>(v));  // lane 31 to rows 2 and 3
+  return v;
+}
+
+// The wave maximum of v written to its own slot (no atomics: one slot per
+// wave, reduced afterwards in a fixed order).
 __device__ __forceinline__ void wave_max_store(double v, double* dst) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double o = __shfl_xor(v, off, 64);
-    v = (o > v || o != o) ? o : v;
-  }
-  if ((threadIdx.x & 63) == 0) *dst = v;
+  v = wave_max(v);
+  if ((threadIdx.x & 63) == 63) *dst = v;
 }
 
 // ------------------------------------------------------------- indexing
