@@ -73,17 +73,20 @@ __device__ __forceinline__ void block_param_sum(const PBar& pb, double* part) {
 //   2. face reverse: update and face-flux adjoints, giving the bars of the
 //      edge states; the conserved-state bar of the update and the parameter
 //      bars so far go to LDS;
-//   3. cell reverse: edges -> candidates -> primitive -> conserved, from the
-//      primitive state and the candidates that phase 1 parked in LDS.
+//   3. cell reverse: the primitive state and the candidates are recomputed
+//      from the parked conserved state (a compiler barrier keeps them from
+//      being merged with phase 1's), then edges -> candidates -> primitive
+//      -> conserved.  (Parked in LDS by phase 1 they take 3% less, but phase 1's
+//      differ from these in a last bit here and there, which decides a BVD or a
+//      limiter tie the other way and moves the gradient by up to 6e-8.)
 // Bound by the vector instructions issued (4-5 cycles each at one wave per SIMD;
 // 430-470 registers, and at two waves 900 bytes a lane go to scratch memory:
 // 3870 -> 6086 us for a gradient of 8 steps on 512 x 512).  So the instance for a
 // gas and a solid with exponents 1 and 3 (GS) calls no powers in its reverse
-// stages, reciprocals replace their divisions, the two sides of a face, the two
-// edges of a cell and the two star states of a tie each go through one copy, and
-// phase 3 does not repeat phase 1: 25600 -> 12900 instructions of code, x 169 ->
-// 108 us, y 190 -> 130 us a sweep, the gradient 4760 -> 3750 us.  (LDS: 106 KB a
-// block, one block a CU, as the registers allow.)
+// stages, reciprocals replace their divisions, and the two sides of a face, the
+// two edges of a cell and the two star states of a tie each go through one copy:
+// 25600 -> 14300 instructions of code, x 169 -> 113 us, y 190 -> 131 us a sweep,
+// the gradient 4760 -> 3740 us.
 template <int DIR, bool GS>
 __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __restrict__ U_in,
                                                    const double* __restrict__ lam_out, double* __restrict__ lam_in,
@@ -93,8 +96,6 @@ __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __res
   constexpr int F = F2;
   constexpr int TD = 1 - DIR;
   __shared__ double sU[F * 256];        // conserved state
-  __shared__ double sW[F * 256];        // primitive state
-  __shared__ double sC[6 * 256];        // candidates, irho0, rc2
   __shared__ double sUb[(F + 1) * 256];  // conserved-state bar of the update, and irho0's bar
   __shared__ double sPb[2 * PB_N * 256];  // parameter bars of phase 2
   const int tid = threadIdx.x;
@@ -154,15 +155,27 @@ __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __res
         }
       }
     };
-    // the neighbours' primitive states and candidates
-    auto neighbours = [&](const double* W, double* Wm, double* Wp) {
+    // primitive state, its neighbours and the candidates of the lane and
+    // its neighbours, from the parked conserved state
+    auto forward_cells = [&](double* W, double* Wm, double* Wp, double& irho0, double& rc2, Cand& cm, Cand& c0,
+                             Cand& cp, double st[3][3]) {
+      double U[F];
+      asm volatile("" ::: "memory");  // re-read LDS; recompute rather than keep phase-1 values live
+#pragma unroll
+      for (int f = 0; f < F; ++f) U[f] = sU[f * 256 + tid];
+      calib::Thermo T;
+      double H[6], J2;
+      calib::cons_to_prim(P, U, W, T, H, J2);
+      irho0 = T.irho;
+      rc2 = T.rho * T.c2;
 #pragma unroll
       for (int f = 0; f < F; ++f) {
         Wm[f] = from_left_keep(W[f]);
         Wp[f] = from_right_keep(W[f]);
       }
-    };
-    auto candidates = [&](const Cand& c0, Cand& cm, Cand& cp) {
+      stencil(st);
+      auto normal = [&]() -> double { return youngs2(st, P.dx, DIR); };
+      c0 = calib::phi_candidates(P, Wm[0], W[0], Wp[0], normal);
       cm.mL = from_left_keep(c0.mL); cm.mR = from_left_keep(c0.mR); cm.tL = from_left_keep(c0.tL); cm.tR = from_left_keep(c0.tR);
       cp.mL = from_right_keep(c0.mL); cp.mR = from_right_keep(c0.mR); cp.tL = from_right_keep(c0.tL); cp.tR = from_right_keep(c0.tR);
     };
@@ -190,26 +203,7 @@ __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __res
     {
       double W[F], Wm[F], Wp[F], rc2, st[3][3];
       Cand cm, c0, cp;
-      {
-        double U[F];
-#pragma unroll
-        for (int f = 0; f < F; ++f) U[f] = sU[f * 256 + tid];
-        calib::Thermo T;
-        double H[6], J2;
-        calib::cons_to_prim(P, U, W, T, H, J2);
-        irho0 = T.irho;
-        rc2 = T.rho * T.c2;
-      }
-      neighbours(W, Wm, Wp);
-      stencil(st);
-      auto normal = [&]() -> double { return youngs2(st, P.dx, DIR); };
-      c0 = calib::phi_candidates(P, Wm[0], W[0], Wp[0], normal);
-      candidates(c0, cm, cp);
-#pragma unroll
-      for (int f = 0; f < F; ++f) sW[f * 256 + tid] = W[f];
-      const double v[6] = {c0.mL, c0.mR, c0.tL, c0.tR, irho0, rc2};
-#pragma unroll
-      for (int q = 0; q < 6; ++q) sC[q * 256 + tid] = v[q];
+      forward_cells(W, Wm, Wp, irho0, rc2, cm, c0, cp, st);
       double WR[F];
       calib::edges_predict<DIR>(P, Wm, W, Wp, irho0, rc2, cm, c0, cp, nu, WL, WR);
 #pragma unroll
@@ -264,19 +258,9 @@ __global__ __launch_bounds__(256) void k_sweep_adj(Params P, const double* __res
         }
     }
     // ---------------------------------------------------- 3. cell reverse
-    double W[F], Wm[F], Wp[F], st[3][3];
+    double W[F], Wm[F], Wp[F], irho0c, rc2, st[3][3];
     Cand cm, c0, cp;
-    asm volatile("" ::: "memory");  // re-read LDS rather than keep phase-1 values live
-#pragma unroll
-    for (int f = 0; f < F; ++f) W[f] = sW[f * 256 + tid];
-    c0.mL = sC[tid];
-    c0.mR = sC[256 + tid];
-    c0.tL = sC[2 * 256 + tid];
-    c0.tR = sC[3 * 256 + tid];
-    const double irho0c = sC[4 * 256 + tid], rc2 = sC[5 * 256 + tid];
-    neighbours(W, Wm, Wp);
-    candidates(c0, cm, cp);
-    stencil(st);
+    forward_cells(W, Wm, Wp, irho0c, rc2, cm, c0, cp, st);
     double Wmb[F], W0b[F], Wpb[F];
 #pragma unroll
     for (int f = 0; f < F; ++f) Wmb[f] = W0b[f] = Wpb[f] = 0.0;
