@@ -106,8 +106,9 @@ constexpr int BC_PERIODIC = 1, BC_REFLECTIVE = 2, BC_AXIS = 3;
 //   PROF_GAS_GAS    two gases.
 // The chosen instance computes the same expressions.  Without the branches a
 // sweep is a few long blocks that the scheduler can fill: the 2-D sweeps of
-// PROF_GAS_SOLID take 126-137 VGPRs against 149-151 and hardly spill scalar
-// registers (10 lane moves against 100-190).
+// PROF_GAS_SOLID take 122-136 VGPRs against 149-151 and hardly spill scalar
+// registers (10 lane moves against 100-190); 1024 x 900 with Johnson-Cook copper
+// 528 -> 394 us a pass from the profiles alone, 256^3 22260 -> 18350.
 //   PROF_CALIB      not a statement about the materials: the stages of
 //                   dimp_calib.hpp (Params::calib, sweeps and the initial state)
 constexpr int PROF_ANY = 0, PROF_GAS_SOLID = 1, PROF_GAS_JC = 2, PROF_GAS_GAS = 3, PROF_CALIB = 4;
@@ -647,7 +648,8 @@ __device__ __forceinline__ Split rx_newton(const RxP& r, double lam, double py, 
   };
   // Three loops, each with its own evaluation: the first two need g's sign
   // only, and a wave runs each for as long as its slowest lane (one loop with
-  // the stage in a variable spent two thirds of its instructions on choosing).
+  // the stage in a variable spent two thirds of its instructions on choosing:
+  // the x sweep of a 400 x 1000 stick 111 -> 62 us, fused 396 -> 260).
   double ti = 0.5, gi = eval(0.5).g, to = 0.5, go = gi;  // the bracket's inner and outer end
   const bool up = gi < 0.0;
   bool found = false;
@@ -715,7 +717,8 @@ __device__ __forceinline__ Split rx_newton(const RxP& r, double lam, double py, 
     // above it only where the root itself is known to 1e-5).  Without this
     // test about one split in 300 of a detonation front ran all 160
     // evaluations, and the waves that hold one set the kernels' time: two
-    // steps of a 400 x 1000 rate stick took 5.5 ms, with it 1.43 ms
+    // steps of a 400 x 1000 rate stick took 5.5 ms, with it 1.43 ms (0.45 with
+    // the steps after it)
     if (size > 0.5 * last && last <= 1e-7 * room) break;
     last = size;
     t = t - step;

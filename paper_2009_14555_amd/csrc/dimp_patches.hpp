@@ -30,7 +30,9 @@ namespace dimp {
 constexpr int PD = 2;
 // waves per SIMD of the patch sweeps: 2 with a JWL mixture (its split holds
 // more live state) or three materials, 4 where the state fits 128 VGPRs (a
-// material profile without a history slot), else 3
+// material profile without a history slot), else 3 (with the ghost positions in
+// LDS and the tiles in place: 2048 patches of 16..128 cells a side, two steps,
+// 1924 -> 1810 us)
 template <int N, int RX, int PROF>
 constexpr int patch_waves() {
   if (RX == 2 || N > 2) return 2;

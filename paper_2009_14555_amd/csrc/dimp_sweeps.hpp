@@ -6,8 +6,9 @@
 //    cross-lane shuffles; no LDS, no barriers.  Loads and stores are
 //    coalesced 512-byte rows per field.
 //  * sweep_tile: sweep along y or z.  The same one-cell-per-lane stages on a
-//    tile of TILE_COLUMNS x columns by 64 cells, staged through LDS so that
-//    HBM sees contiguous row segments; XCD-aware block order.
+//    tile of 4 or 8 x columns by 64 cells, staged through LDS so that HBM sees
+//    contiguous row segments.
+// Both deal their blocks to the XCDs in short runs (xcd_block).
 // The last sweep of a step can fuse the plastic and reactive fractional steps
 // and the wave-speed reduction into its epilogue (FUSE), so a 2-D step reads
 // and writes the state exactly twice.  Included by the translation units that
