@@ -29,10 +29,15 @@ namespace dimp {
 // eight waves, and with 16 columns, slower by a third and more: the LDS of 17
 // fields holds one such block a CU).  With the sources fused (z 3032, 3039) and
 // on 2-D grids (2048^2: y 232, 249; fused 257, 260) the second column costs what
-// the wider rows gain or more; eight columns by eight waves there take 216 us
-// at 2048^2 but 7% longer a step at 601 x 480 and at 96 x 75, half as many blocks.
+// the wider rows gain or more.
 constexpr int TILE_WAVES = 4;
 constexpr int tile_columns(int D, bool fuse) { return (D == 3 && !fuse) ? 8 : 4; }
+// Two-dimensional y sweeps that run four waves a SIMD take eight columns with
+// eight waves where the state read and the state written exceed the 256 MB
+// cache in front of the memory, which takes the short rows' partial lines:
+// y alone, four columns and eight: 777 x 1031 39 and 41 us, 1024^2 42 and 46,
+// 1448^2 113 and 106, 2048^2 220 and 199, 4096^2 860 and 742.
+constexpr int64_t WIDE_TILE_BYTES = int64_t(256) << 20;
 
 // waves per SIMD the sweep kernels are built for (launch bound): four where
 // the state fits 128 VGPRs, the 1-D and 2-D instances of a two-material profile
@@ -166,8 +171,9 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE, false>())) 
 // HBM sees rows of CW doubles, while each wave holds one column with one cell
 // per lane and runs the same stages as the row sweep.  The blocks
 // of a run (xcd_block) are neighbouring x chunks, which share L2 lines.
-template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false>
-__global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE, true>())) void sweep_tile(Params P, const double* __restrict__ in,
+template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false,
+          int NW = TILE_WAVES>
+__global__ __launch_bounds__(64 * NW, (sweep_waves<D, N, RX, PROF, FUSE, true>())) void sweep_tile(Params P, const double* __restrict__ in,
                                                        double* __restrict__ out, double dt_arg,
                                                        const double* __restrict__ dtp,
                                                        double* __restrict__ part,
@@ -198,7 +204,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE,
   const int tid = threadIdx.x;
 
   // load the tile: thread t -> row r (sweep axis), column c (x)
-  for (int t = tid; t < 64 * CW; t += 64 * TILE_WAVES) {
+  for (int t = tid; t < 64 * CW; t += 64 * NW) {
     const int r = t / CW, c = t % CW;
     const int64_t xx = bc_map(x0 + c, nx, P.bc[0]);
     const int64_t jj = WALL ? bc_map_wall(j0 + r, nm, P.bc[DIR]) : bc_map(j0 + r, nm, P.bc[DIR]);
@@ -218,7 +224,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE,
 #pragma unroll
   for (int k = 0; k < D; ++k) smax[k] = 0.0;
 #pragma unroll 1
-  for (int col = w; col < CW && x0 + col < nx; col += TILE_WAVES) {
+  for (int col = w; col < CW && x0 + col < nx; col += NW) {
     // every lane reads and writes its own slots of the wave's column only
     auto load_U = [&](double* U) {
       asm volatile("" ::: "memory");  // re-read LDS rather than keep U live in registers
@@ -260,7 +266,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE,
     for (int k = 0; k < D; ++k) smax[k] = (s[k] > smax[k] || s[k] != s[k]) ? s[k] : smax[k];
   }
   __syncthreads();
-  for (int t = tid; t < 64 * CW; t += 64 * TILE_WAVES) {
+  for (int t = tid; t < 64 * CW; t += 64 * NW) {
     const int r = t / CW, c = t % CW;
     const int64_t xx = x0 + c, jj = j0 + r;
     if (r >= 3 && r < 61 && xx < nx && jj < nm) {
@@ -286,7 +292,7 @@ __global__ __launch_bounds__(64 * TILE_WAVES, (sweep_waves<D, N, RX, PROF, FUSE,
     }
   }
   if (FUSE && MODE == M_SPLIT) {
-    const int64_t slot = lb * TILE_WAVES + w;
+    const int64_t slot = lb * NW + w;
 #pragma unroll
     for (int k = 0; k < D; ++k) wave_max_store(smax[k], part + slot * 3 + k);
   }
@@ -303,21 +309,24 @@ template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int MODE = M_SPLIT
 static void launch_tile(const Params& P, const double* in, double* out, double dt, const double* dtp,
                         double* part, hipStream_t st, const double* Rin = nullptr, const double* qn = nullptr,
                         int stage = 0) {
-  constexpr int CW = tile_columns(D, FUSE);
   using L = Lay<D, N, RX>;
   const int oa = (DIR == 1) ? 2 : 1;
   const int64_t no = (D == 3) ? P.n[oa] : 1;
-  const int64_t grid = ((P.n[0] + CW - 1) / CW) * no * ((P.n[DIR] + 57) / 58);
-  const size_t lds = sizeof(double) * L::F * 64 * CW;
+  const int64_t segs = no * ((P.n[DIR] + 57) / 58);
+  auto launch = [&](auto kernel, int cw, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(((P.n[0] + cw - 1) / cw) * segs)), dim3(64 * waves),
+                       sizeof(double) * L::F * 64 * cw, st, P, in, out, dt, dtp, part, Rin, qn, stage);
+  };
+  constexpr int CW = tile_columns(D, FUSE);
   if constexpr (PROF != PROF_CALIB) {  // (those grids have no walls)
-    if (P.bc[DIR] >= BC_REFLECTIVE) {
-      hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE, true>), dim3((unsigned)grid), dim3(64 * TILE_WAVES),
-                         lds, st, P, in, out, dt, dtp, part, Rin, qn, stage);
-      return;
-    }
+    if (P.bc[DIR] >= BC_REFLECTIVE)
+      return launch(sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE, true>, CW, TILE_WAVES);
   }
-  hipLaunchKernelGGL((sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE>), dim3((unsigned)grid), dim3(64 * TILE_WAVES), lds, st, P,
-                     in, out, dt, dtp, part, Rin, qn, stage);
+  if constexpr (D == 2 && !FUSE && sweep_waves<D, N, RX, PROF, FUSE, true>() == 4) {
+    if (2 * int64_t(sizeof(double)) * L::F * P.ncell > WIDE_TILE_BYTES)
+      return launch(sweep_tile<D, N, RX, PROF, DIR, FUSE, 8, MODE, false, 8>, 8, 8);
+  }
+  launch(sweep_tile<D, N, RX, PROF, DIR, FUSE, CW, MODE>, CW, TILE_WAVES);
 }
 
 static inline int row_grid(const Params& P) {

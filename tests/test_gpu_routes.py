@@ -104,6 +104,38 @@ def test_every_block_of_a_sweep_runs_once(S, blocks, d):
     assert bool((U[L.E] != before[L.E]).any(dim=1 - d).all())
 
 
+@pytest.mark.parametrize("integ", ["split", "rk3"])
+@pytest.mark.parametrize("copies", [192, 193])
+def test_wide_tiles_match_narrow(S, copies, integ):
+    """a y sweep of a grid past the cache (eight columns by eight waves) against
+    the same columns of a small one; 61 columns leave a part of a tile, and a
+    part of eight.  The same stages in another instance: a few roundings"""
+    import torch
+
+    def grid(nx):
+        pb = P.Problem(ndim=2, n=(nx, 130, 1), dx=(1 / 61, 1 / 130, 1), bc=(P.BC_PERIODIC,) * 3,
+                       materials=[P.water_sg(), P.solid_c2(yield_stress=0.05e9)], thinc=1)
+        return pb, S.Grid(pb)
+
+    pb, g = grid(61)
+    W = torch.as_tensor(P.random_smooth_state(pb, seed=4, solid_strain=1e-3), device="cuda")
+    g.set_primitive(W)
+    pb2, h = grid(61 * copies)
+    assert (2 * 8 * P.layout(pb).nfields * h.pb.ncell > 2**28) == (copies > 192)
+    h.set_primitive(W.reshape(-1, 130, 61).repeat(1, 1, copies))
+    dt = g.dt_cfl()
+    for a in (g, h):
+        if integ == "rk3":
+            a.set_integrator("rk3")
+            a.advance(dt)
+        else:
+            a.sweep(dt, 1)
+    ref = to_np(g.state).reshape(-1, 130, 61)
+    out = to_np(h.state).reshape(-1, 130, copies, 61)
+    for k in (0, 1, 7, copies // 2, copies - 1):
+        assert_parity(out[:, :, k], ref, 1e-13, f"copy {k}", P.layout(pb))
+
+
 @pytest.mark.parametrize("slots", [1, 63, 64, 65, 256, 257, 1024, 1025, 2048, 2049])
 def test_wave_speed_reduction_finds_its_slot(S, slots):
     """one row of 58 cells a slot after a fused x sweep; the fastest row is the
