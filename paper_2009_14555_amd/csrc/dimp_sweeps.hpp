@@ -36,7 +36,8 @@ constexpr int tile_columns(int D, bool fuse) { return (D == 3 && !fuse) ? 8 : 4;
 // eight waves where the state read and the state written exceed the 256 MB
 // cache in front of the memory, which takes the short rows' partial lines:
 // y alone, four columns and eight: 777 x 1031 39 and 41 us, 1024^2 42 and 46,
-// 1448^2 113 and 106, 2048^2 220 and 199, 4096^2 860 and 742.
+// 1448^2 113 and 106, 2048^2 220 and 199, 4096^2 860 and 742.  (With the sources
+// fused 2048^2 took 234 and 253.)
 constexpr int64_t WIDE_TILE_BYTES = int64_t(256) << 20;
 
 // waves per SIMD the sweep kernels are built for (launch bound): four where
