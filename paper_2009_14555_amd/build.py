@@ -88,20 +88,25 @@ def build(verbose: bool = False, resource_usage: bool = False, force: bool = Tru
 
 UNITS_SRC = os.path.join(ROOT, "tests", "adjoint_units.hip")
 UNITS_LIB = os.path.join(ROOT, "tests", "libdimp_adjunits.so")
+FLUX_UNITS_SRC = os.path.join(ROOT, "tests", "flux_units.hip")
+FLUX_UNITS_LIB = os.path.join(ROOT, "tests", "libdimp_fluxunits.so")
 
 
 def build_units(verbose: bool = False) -> str:
-    """test library: each reverse stage of the adjoint against central
-    differences of its forward stage"""
-    tmp = UNITS_LIB + ".tmp%d" % os.getpid()
-    cmd = [HIPCC, *FLAGS, "-I", CSRC, UNITS_SRC, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError("hipcc failed (adjoint unit library)")
-    os.replace(tmp, UNITS_LIB)
+    """test libraries: each reverse stage of the adjoint against central
+    differences of its forward stage, and the recorded boundary fluxes against
+    the sweep's (linked to the library, whose launchers it calls)"""
+    link = ["-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN/../" + os.path.basename(HERE)]
+    for src, lib, extra in ((UNITS_SRC, UNITS_LIB, []), (FLUX_UNITS_SRC, FLUX_UNITS_LIB, link)):
+        tmp = lib + ".tmp%d" % os.getpid()
+        cmd = [HIPCC, *FLAGS, "-I", CSRC, src, *extra, "-o", tmp]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode != 0:
+            sys.stderr.write(r.stdout + r.stderr)
+            raise RuntimeError("hipcc failed (%s)" % os.path.basename(src))
+        os.replace(tmp, lib)
     return UNITS_LIB
 
 

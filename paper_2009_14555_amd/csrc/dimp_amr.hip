@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "dimp_amr.hpp"
+#include "dimp_calib.hpp"
 #include "dimp_lane.hpp"
 
 namespace dimp {
@@ -150,6 +151,7 @@ __global__ __launch_bounds__(256) void k_amr_tag(TagLayout L, const double* __re
 // as the sweep computes it (the same stages, lane_face): the split sweep's
 // (MUSCL-Hancock edges, time step dt) or, with RK, the unsplit operator's
 // (edges without the predictor); times wgt, added to what is stored with acc.
+// PROF_CALIB: the calibrated step's stages (dimp_calib.hpp).
 constexpr int FLUX_SEG = 6, FLUX_PER_WAVE = 10;
 
 template <int N, int RX, int PROF, int DIR, bool RK>
@@ -180,7 +182,10 @@ __global__ __launch_bounds__(256) void k_amr_flux(Params P, FaceSet fs, const do
   auto phi_at = [&](int b, int) -> double { return in[at(a, tr + b - 1)]; };
   FaceV<D, N, RX> fa;
   double irho0;
-  lane_face<D, N, RX, DIR, RK, PROF>(P, load_U, phi_at, RK ? P.idx[DIR] : dt * P.idx[DIR], fa, irho0, false);
+  if constexpr (PROF == PROF_CALIB)  // (split sweeps only: the unsplit operator has the general stages on every grid)
+    calib::lane_face<DIR>(P, load_U, phi_at, dt / P.dx[DIR], fa, irho0, false);
+  else
+    lane_face<D, N, RX, DIR, RK, PROF>(P, load_U, phi_at, RK ? P.idx[DIR] : dt * P.idx[DIR], fa, irho0, false);
   (void)irho0;
   if (live && l == 3) {
 #pragma unroll
@@ -258,6 +263,18 @@ hipError_t launch_amr_flux(const Params& P, int rx, int dir, const FaceSet& fs, 
   const int64_t waves = (2 * fs.len + FLUX_PER_WAVE - 1) / FLUX_PER_WAVE;
   const int grid = (int)((waves + 3) / 4);
   const int a = acc ? 1 : 0;
+  // grids whose split sweeps take the calibrated step's arithmetic record its
+  // fluxes: those of the general stages differ from what the sweep applied by
+  // rounding, and by a whole edge state where a BVD choice turns on it
+  if (P.calib && !rk) {
+    if (dir == 0)
+      hipLaunchKernelGGL((k_amr_flux<2, 0, PROF_CALIB, 0, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,
+                         wgt, a);
+    else
+      hipLaunchKernelGGL((k_amr_flux<2, 0, PROF_CALIB, 1, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,
+                         wgt, a);
+    return hipGetLastError();
+  }
 #define DIMP_AMR_FLUX(NV, RXV, DIRV)                                                                            \
   (void)by_profile<NV, RXV>(P, [&](auto prof) {                                                                 \
     constexpr int PROF = decltype(prof)::value;                                                                 \
