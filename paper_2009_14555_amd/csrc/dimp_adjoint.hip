@@ -447,7 +447,7 @@ hipError_t launch_sweep_adjoint(const Params& P, int dir, const double* U_in, co
   const int64_t nblk = (nwaves + 3) / 4;
   const double nu = dt / P.dx[dir];
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)nblk), dim3(256), 0, st, P, U_in, lam_out, lam_in, tang, part, nu, nseg,
+    launch_params(kernel, dim3((unsigned)nblk), dim3(256), 0, st, P, U_in, lam_out, lam_in, tang, part, nu, nseg,
                        nwaves);
   };
   // other materials, or the solid first: the instance that reads their kinds

@@ -268,10 +268,10 @@ hipError_t launch_amr_flux(const Params& P, int rx, int dir, const FaceSet& fs, 
   // rounding, and by a whole edge state where a BVD choice turns on it
   if (P.calib && !rk) {
     if (dir == 0)
-      hipLaunchKernelGGL((k_amr_flux<2, 0, PROF_CALIB, 0, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,
+      launch_params((k_amr_flux<2, 0, PROF_CALIB, 0, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,
                          wgt, a);
     else
-      hipLaunchKernelGGL((k_amr_flux<2, 0, PROF_CALIB, 1, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,
+      launch_params((k_amr_flux<2, 0, PROF_CALIB, 1, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt, flux,
                          wgt, a);
     return hipGetLastError();
   }
@@ -279,10 +279,10 @@ hipError_t launch_amr_flux(const Params& P, int rx, int dir, const FaceSet& fs, 
   (void)by_profile<NV, RXV>(P, [&](auto prof) {                                                                 \
     constexpr int PROF = decltype(prof)::value;                                                                 \
     if (rk)                                                                                                     \
-      hipLaunchKernelGGL((k_amr_flux<NV, RXV, PROF, DIRV, true>), dim3(grid), dim3(256), 0, st, P, fs, in, dt,    \
+      launch_params((k_amr_flux<NV, RXV, PROF, DIRV, true>), dim3(grid), dim3(256), 0, st, P, fs, in, dt,    \
                          flux, wgt, a);                                                                         \
     else                                                                                                        \
-      hipLaunchKernelGGL((k_amr_flux<NV, RXV, PROF, DIRV, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt,   \
+      launch_params((k_amr_flux<NV, RXV, PROF, DIRV, false>), dim3(grid), dim3(256), 0, st, P, fs, in, dt,   \
                          flux, wgt, a);                                                                         \
     return hipSuccess;                                                                                          \
   })

@@ -149,8 +149,9 @@ __device__ __forceinline__ void assume_profile(const Params& P) {
   }
 }
 
-// The parameters, read anew from the kernel's arguments (P must be the kernel's
-// first; PROF < 0: P itself).  The compiler reads what a kernel uses of them
+// The parameters, read anew from the kernel's arguments (PROF < 0: P itself).
+// They must be the kernel's first: kernels whose stages call this are launched by
+// launch_params, which takes no others.  The compiler reads what a kernel uses of them
 // once, at its start, and parks what exceeds the 100 scalar registers in vector
 // lanes: a fused sweep of a JWL mixture had 1640-3100 lane reads among its 11800
 // instructions and a three-material one 1389-1761, and the parked values took
@@ -165,6 +166,14 @@ __device__ __forceinline__ const Params& fresh(const Params& P) {
   const Params& q = *(const Params*)p;
   assume_profile<N, RX, PROF>(q);
   return q;
+}
+
+// kernel(P, args...) for kernels whose first parameter is Params (see fresh)
+template <class... A, class... B>
+static inline void launch_params(void (*kernel)(Params, A...), dim3 grid, dim3 block, size_t lds, hipStream_t st,
+                                 const Params& P, B... args) {
+  static_assert(sizeof...(A) == sizeof...(B), "the kernel's other arguments");
+  hipLaunchKernelGGL(kernel, grid, block, lds, st, P, static_cast<A>(args)...);
 }
 
 // f(std::integral_constant<int, PROF>) for the profile that P states, among

@@ -218,10 +218,10 @@ hipError_t launch_patch_p(const Params& P, const PatchGeo* geo, WorkList wl, int
     const dim3 block(64 * row_wpb);
 #define DIMP_ROW(W)                                                                                              \
   if (fuse)                                                                                                     \
-    hipLaunchKernelGGL((psweep_row<N, RX, PROF, true, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp,  \
+    launch_params((psweep_row<N, RX, PROF, true, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp,  \
                        part);                                                                                   \
   else                                                                                                          \
-    hipLaunchKernelGGL((psweep_row<N, RX, PROF, false, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp, \
+    launch_params((psweep_row<N, RX, PROF, false, W>), grid, block, 0, st, P, geo, wl, w0, nwork, in, out, dt, dtp, \
                        part);
     if (row_wpb == 1) {
       DIMP_ROW(1)
@@ -237,18 +237,18 @@ hipError_t launch_patch_p(const Params& P, const PatchGeo* geo, WorkList wl, int
   if (cw == 8) {
     const size_t lds = tile_lds_bytes<N, RX, 8>();
     if (fuse)
-      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, true, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      launch_params((psweep_tile<N, RX, PROF, true, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
     else
-      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, false, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      launch_params((psweep_tile<N, RX, PROF, false, 8>), grid, dim3(512), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
   } else {
     const size_t lds = tile_lds_bytes<N, RX, 4>();
     if (fuse)
-      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, true, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      launch_params((psweep_tile<N, RX, PROF, true, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
     else
-      hipLaunchKernelGGL((psweep_tile<N, RX, PROF, false, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
+      launch_params((psweep_tile<N, RX, PROF, false, 4>), grid, dim3(256), lds, st, P, geo, wl, w0, nwork, in, out, dt,
                          dtp, part);
   }
   return hipGetLastError();

@@ -315,7 +315,7 @@ static void launch_tile(const Params& P, const double* in, double* out, double d
   const int64_t no = (D == 3) ? P.n[oa] : 1;
   const int64_t segs = no * ((P.n[DIR] + 57) / 58);
   auto launch = [&](auto kernel, int cw, int waves) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(((P.n[0] + cw - 1) / cw) * segs)), dim3(64 * waves),
+    launch_params(kernel, dim3((unsigned)(((P.n[0] + cw - 1) / cw) * segs)), dim3(64 * waves),
                        sizeof(double) * L::F * 64 * cw, st, P, in, out, dt, dtp, part, Rin, qn, stage);
   };
   constexpr int CW = tile_columns(D, FUSE);
@@ -344,18 +344,18 @@ static hipError_t launch_rk_p(const Params& P, int dir, int mode, int stage, boo
     if (mode != M_RK_LAST) return hipErrorInvalidValue;
     if (P.bc[0] >= BC_REFLECTIVE) {
       if (fuse)
-        hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P, in,
+        launch_params((sweep_row<D, N, RX, PROF, true, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P, in,
                            out, dt, dtp, part, Rin, qn, stage);
       else
-        hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P,
+        launch_params((sweep_row<D, N, RX, PROF, false, M_RK_LAST, true>), dim3(row_grid(P)), dim3(256), 0, st, P,
                            in, out, dt, dtp, part, Rin, qn, stage);
       return hipGetLastError();
     }
     if (fuse)
-      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out, dt,
+      launch_params((sweep_row<D, N, RX, PROF, true, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out, dt,
                          dtp, part, Rin, qn, stage);
     else
-      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out,
+      launch_params((sweep_row<D, N, RX, PROF, false, M_RK_LAST>), dim3(row_grid(P)), dim3(256), 0, st, P, in, out,
                          dt, dtp, part, Rin, qn, stage);
     return hipGetLastError();
   }
@@ -384,19 +384,19 @@ static hipError_t launch_sweep_p(const Params& P, const double* in, double* out,
     if constexpr (PROF != PROF_CALIB) {  // (those grids have no walls)
       if (P.bc[0] >= BC_REFLECTIVE) {
         if (fuse)
-          hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in,
+          launch_params((sweep_row<D, N, RX, PROF, true, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in,
                              out, dt, dtp, part, nullptr, nullptr, 0);
         else
-          hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in,
+          launch_params((sweep_row<D, N, RX, PROF, false, M_SPLIT, true>), dim3(grid), dim3(block), 0, st, P, in,
                              out, dt, dtp, part, nullptr, nullptr, 0);
         return hipGetLastError();
       }
     }
     if (fuse)
-      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, true>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
+      launch_params((sweep_row<D, N, RX, PROF, true>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
                          nullptr, nullptr, 0);
     else
-      hipLaunchKernelGGL((sweep_row<D, N, RX, PROF, false>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
+      launch_params((sweep_row<D, N, RX, PROF, false>), dim3(grid), dim3(block), 0, st, P, in, out, dt, dtp, part,
                          nullptr, nullptr, 0);
     return hipGetLastError();
   }
