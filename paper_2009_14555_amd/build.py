@@ -90,6 +90,8 @@ UNITS_SRC = os.path.join(ROOT, "tests", "adjoint_units.hip")
 UNITS_LIB = os.path.join(ROOT, "tests", "libdimp_adjunits.so")
 STAGES_SRC = os.path.join(ROOT, "tests", "adjoint_stages.hip")
 STAGES_LIB = os.path.join(ROOT, "tests", "libdimp_adjstages.so")
+SCALARS_SRC = os.path.join(ROOT, "tests", "scalar_units.hip")
+SCALARS_LIB = os.path.join(ROOT, "tests", "libdimp_scalars.so")
 FLUX_UNITS_SRC = os.path.join(ROOT, "tests", "flux_units.hip")
 FLUX_UNITS_LIB = os.path.join(ROOT, "tests", "libdimp_fluxunits.so")
 
@@ -97,10 +99,11 @@ FLUX_UNITS_LIB = os.path.join(ROOT, "tests", "libdimp_fluxunits.so")
 def build_units(verbose: bool = False) -> str:
     """test libraries: each reverse stage of the adjoint against central
     differences of its forward stage (general stages, and those of the calibrated
-    step), and the recorded boundary fluxes against the sweep's (linked to the
-    library, whose launchers it calls)"""
+    step), the scalar functions of the stages, and the recorded boundary fluxes
+    against the sweep's (linked to the library, whose launchers it calls)"""
     link = ["-L", HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN/../" + os.path.basename(HERE)]
-    for src, lib, extra in ((UNITS_SRC, UNITS_LIB, []), (STAGES_SRC, STAGES_LIB, []), (FLUX_UNITS_SRC, FLUX_UNITS_LIB, link)):
+    for src, lib, extra in ((UNITS_SRC, UNITS_LIB, []), (STAGES_SRC, STAGES_LIB, []), (SCALARS_SRC, SCALARS_LIB, []),
+                            (FLUX_UNITS_SRC, FLUX_UNITS_LIB, link)):
         tmp = lib + ".tmp%d" % os.getpid()
         cmd = [HIPCC, *FLAGS, "-I", CSRC, src, *extra, "-o", tmp]
         if verbose:

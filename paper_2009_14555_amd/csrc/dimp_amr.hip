@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void k_amr_flux(Params P, FaceSet fs, const do
   if constexpr (PROF == PROF_CALIB)  // (split sweeps only: the unsplit operator has the general stages on every grid)
     calib::lane_face<DIR>(P, load_U, phi_at, dt / P.dx[DIR], fa, irho0, false);
   else
-    lane_face<D, N, RX, DIR, RK, PROF>(P, load_U, phi_at, RK ? P.idx[DIR] : dt * P.idx[DIR], fa, irho0, false);
+    lane_face<D, N, RX, DIR, RK, PROF>(P, load_U, phi_at, RK ? P.idx[DIR] : over_dx(P, DIR, dt), fa, irho0, false);
   (void)irho0;
   if (live && l == 3) {
 #pragma unroll

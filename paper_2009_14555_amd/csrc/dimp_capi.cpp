@@ -234,13 +234,22 @@ int material_profile(const dimp::Params& P, int nmat, bool hist) {
   return dimp::PROF_ANY;
 }
 
+// 1/b in two parts: the rounded inverse and what it lacks (0 where it overflows)
+void inverse_of(double b, double out[2]) {
+  out[0] = 1.0 / b;
+  out[1] = std::isfinite(out[0]) ? std::fma(-out[0], b, 1.0) / b : 0.0;
+}
+
 void rebuild_params(dimp_ctx* h) {
   dimp::Params& P = h->P;
   std::memset(&P, 0, sizeof P);
   for (int d = 0; d < 3; ++d) {
     P.n[d] = h->n[d];
     P.dx[d] = h->dx[d];
-    P.idx[d] = 1.0 / h->dx[d];
+    double inv[2];
+    inverse_of(h->dx[d], inv);
+    P.idx[d] = inv[0];
+    P.idl[d] = inv[1];
     P.bc[d] = h->bc[d];
   }
   P.ncell = h->ncell();
@@ -315,8 +324,8 @@ void rebuild_params(dimp_ctx* h) {
     P.rx.igFig = g[12];
     P.rx.igFG1 = g[13];
     P.rx.igFG2 = g[14];
-    P.rx.ig_irho0 = 1.0 / g[15];
-    P.rx.ig_ipunit = 1.0 / g[16];
+    inverse_of(g[15], P.rx.ig_irho0);
+    inverse_of(g[16], P.rx.ig_ipunit);
     for (int k = 0; k < 8; ++k) {
       const double e = g[4 + k];  // b, c, d, e, g, x, y, z
       P.rx.ign[k] = (e == std::floor(e) && e >= 1.0 && e <= 8.0) ? (int)e : 0;

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64 * WPB, (patch_waves<N, RX, PROF>())) void psweep
   const int64_t wv = xcd_block(blockIdx.x, gridDim.x) * WPB + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (wv >= nwork) return;  // whole waves only: a work item is one wave
   const double dt = dtp ? dtp[0] : dt_arg;
-  const double nu = dt * P.idx[0];
+  const double nu = over_dx(P, 0, dt);
   const int64_t E = P.ncell;
   __shared__ double stash[F * 64 * WPB];
   const int sb = wl.beg[w0 + wv], se = wl.beg[w0 + wv + 1];
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * CW, (patch_waves<N, RX, PROF>())) void psweep_
   const int64_t t = xcd_block(blockIdx.x, gridDim.x);
   if (t >= nwork) return;  // whole block: a work item is one tile
   const double dt = dtp ? dtp[0] : dt_arg;
-  const double nu = dt * P.idx[1];
+  const double nu = over_dx(P, 1, dt);
   const int64_t E = P.ncell;
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;

@@ -257,7 +257,8 @@ __device__ __forceinline__ void star_flux(const Params& P, const double* W, cons
   using L = Lay<D, N, RX>;
   const double un = S.u[DIR];
   const double r = a * inv;
-  const double us_face = un + SK * (r - 1.0);
+  // S_K (r - 1) = S_K (S* - u_n) / (S_K - S*), without the cancellation of r - 1
+  const double us_face = un + SK * ((ust[DIR] - un) * inv);
   // F_K + S_K (U*_K - U_K) collected: a mass m moves with the face velocity
   // u* = u_n + S_K (r - 1), every other term with S_K / (S_K - S*) = SK inv of
   // its star correction; the normal row of Vbar is continuous and carries no
@@ -556,7 +557,7 @@ __device__ __forceinline__ void plastic_cell(const Params& P, double* U, double 
 __device__ __forceinline__ double ig_rate(const RxP& r, double lam, double rho, double p) {
   if (!(lam > 0.0)) return 0.0;
   const double F = 1.0 - lam;
-  const double mu = rho * r.ig_irho0 - 1.0 - r.ig_a;
+  const double mu = times_inverse(rho, r.ig_irho0[0], r.ig_irho0[1]) - 1.0 - r.ig_a;
   const bool ignite = r.igFig - F > 0.0 && mu > 0.0;
   const bool grow1 = F > 0.0 && r.igFG1 - F > 0.0, grow2 = F > 0.0 && F - r.igFG2 > 0.0;
   if (!(ignite || grow1 || grow2)) return 0.0;
@@ -565,7 +566,7 @@ __device__ __forceinline__ double ig_rate(const RxP& r, double lam, double rho, 
   const double lb = pow_of(lam, r.ig_b, r.ign[0]);
   const double lc = (r.ig_c == r.ig_b) ? lb : pow_of(lam, r.ig_c, r.ign[1]);
   const double le = (r.ig_e == r.ig_b) ? lb : pow_of(lam, r.ig_e, r.ign[3]);
-  const double ph = fmax(p, 0.0) * r.ig_ipunit;
+  const double ph = times_inverse(fmax(p, 0.0), r.ig_ipunit[0], r.ig_ipunit[1]);
   double out = 0.0;
   if (ignite) out = out + r.igI * lb * pow_of(mu, r.ig_x, r.ign[5]);
   if (grow1) out = out + r.igG1 * lc * pow_of(F, r.ig_d, r.ign[2]) * pow_of(ph, r.ig_y, r.ign[6]);
@@ -672,7 +673,7 @@ __device__ __forceinline__ void reaction_cell(const Params& P, double* U, double
     }
   // the four stages, and the split of the result for its wave speed, through
   // one evaluation site
-  const double l0 = fmin(fmax(U[L::LAM] * frcp(my), 0.0), 1.0);
+  const double l0 = fmin(fmax(quot(U[L::LAM], my), 0.0), 1.0);
   double lam = l0, l1 = l0, k = 0.0, sum = 0.0;
 #pragma unroll 1
   for (int st = 0; st < (WS ? 5 : 4); ++st) {

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE, false>())) 
   if constexpr (PROF == PROF_CALIB) {
     calib::lane_sweep<0, FUSE>(P, load_U, phi_at, dt / P.dx[0], dt, writer, Un, s, wall);
   } else if (MODE == M_SPLIT) {
-    lane_sweep<D, N, RX, 0, FUSE, false, PROF>(P, load_U, phi_at, dt * P.idx[0], dt, writer, Un, s, wall);
+    lane_sweep<D, N, RX, 0, FUSE, false, PROF>(P, load_U, phi_at, over_dx(P, 0, dt), dt, writer, Un, s, wall);
   } else {
     lane_sweep<D, N, RX, 0, false, true, PROF>(P, load_U, phi_at, P.idx[0], dt, writer, Un, s, wall);
     if (writer) {
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64 * NW, (sweep_waves<D, N, RX, PROF, FUSE, true>()
     if constexpr (PROF == PROF_CALIB)
       calib::lane_sweep<DIR, FUSE>(P, load_U, phi_at, dt / P.dx[DIR], dt, writer, Un, s, wall);
     else if (MODE == M_SPLIT)
-      lane_sweep<D, N, RX, DIR, FUSE, false, PROF>(P, load_U, phi_at, dt * P.idx[DIR], dt, writer, Un, s, wall);
+      lane_sweep<D, N, RX, DIR, FUSE, false, PROF>(P, load_U, phi_at, over_dx(P, DIR, dt), dt, writer, Un, s, wall);
     else
       lane_sweep<D, N, RX, DIR, false, true, PROF>(P, load_U, phi_at, P.idx[DIR], dt, writer, Un, s, wall);
     if (MODE == M_RK_FIRST && writer) {

@@ -58,6 +58,7 @@ int flux_unit(const dimp_material* mats, const dimp_options* o, const int64_t* n
     P.n[d] = d < 2 ? n[d] : 1;
     P.dx[d] = d < 2 ? dx[d] : 1.0;
     P.idx[d] = 1.0 / P.dx[d];
+    P.idl[d] = std::fma(-P.idx[d], P.dx[d], 1.0) / P.dx[d];
     P.bc[d] = BC_PERIODIC;
   }
   P.ncell = n[0] * n[1];
