@@ -872,8 +872,11 @@ __device__ __forceinline__ Split rx_solve_gas(const RxP& r, double lam, double A
   double sp = 0.0, t_end = 1.0;
   const bool picked = rx_pick(sr, nr, up, lam, sp, t_end);
   if (picked) {
-    const double qv = (Q2 * sp + Q1) * sp + Q0, dq = 2.0 * Q2 * sp + Q1;
-    if (dq != 0.0) sp = sp - qv * frcp(dq);  // one Newton polish of the root taken
+    // one Newton polish of the root taken, on Q's own factors: at a low pressure
+    // b0 + b1 s and 1 - s are small differences (1e-5 and 1e-7 in unreacted
+    // explosive at rest) that Q2 s^2 + Q1 s + Q0 loses to rounding
+    const double qv = ka * sp * fma(a1, sp, a0) - kb * (1.0 - sp) * fma(b1, sp, b0), dq = 2.0 * Q2 * sp + Q1;
+    if (dq != 0.0) sp = sp - qv * frcp(dq);
   }
   return rx_from_pick(r, picked, sp, t_end, lam);
 }

@@ -1,11 +1,15 @@
 """The stages' reciprocal, quotient, root and exponential against extended
 precision: rounded as the IEEE operations (and no further off than the library's
-exponential) that they stand in place of."""
+exponential) that they stand in place of; and the pressure of unreacted explosive at
+rest, which the two-gas split has to find between two nearly equal roots."""
 import ctypes as C
 import os
 
 import numpy as np
 import pytest
+
+from paper_2009_14555_amd import problems as P
+from tests.parity_util import to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +71,59 @@ def test_special_values(gpu):
         np.testing.assert_array_equal(r, np.sqrt(x))
     assert np.array_equal(gpu("exp_curve", np.array([0.0, -800.0, np.nan, 800.0]), np.ones(4)),
                           np.array([1.0, 0.0, np.nan, np.inf]), equal_nan=True)
+
+
+def pressure_of(E, py, rho, lam, solid, r, p0):
+    """p of the mixture cell from rho e in extended precision: the split at a
+    trial p is explicit (equal temperatures), rho e(p) is monotone"""
+    a, b = r.reactant, r.product
+    ga, gb = LD(a.gamma) - 1, LD(b.gamma) - 1
+    pa, pb = (-LD(m.gamma) * LD(m.pinf) for m in (a, b))
+    ps, x = 1 - py, rho[1] / LD(solid.rho0)
+    gs, pref = LD(solid.Gamma0), LD(solid.K0) * x * x * (x - 1)
+    es = rho[1] * LD(solid.K0) / (2 * LD(solid.rho0)) * (x - 1) ** 2
+
+    def f(p):
+        al, be = (p - pa) / (ga * LD(a.cv)), (p - pb) / (gb * LD(b.cv))
+        s = lam * be / (lam * be + (1 - lam) * al)
+        mix = s * (p - pa) / ga + (1 - s) * (p - pb) / gb - rho[0] * (1 - lam) * LD(r.Q)
+        return py * mix + ps * ((p - pref) / gs + es) - E
+
+    p = p0
+    for _ in range(60):
+        h = p * LD(1e-7)
+        p = p - f(p) * (2 * h) / (f(p + h) - f(p - h))
+    return p
+
+
+def test_pressure_between_two_nearly_equal_roots(gpu):
+    """progress 1 - 1e-11 at 1e5 Pa: the error allowed is twice what one rounding
+    of the progress and one of the energy move the pressure by"""
+    from paper_2009_14555_amd import solver as S
+
+    n = 4096
+    solid = P.solid_c2()
+    pb = P.Problem(ndim=1, n=(n, 1, 1), dx=(1.0 / n, 1, 1), materials=[P.placeholder_for_reactive(), solid],
+                   reactive=P.generic_explosive(0))
+    L = P.layout(pb)
+    rng = np.random.default_rng(4)
+    W = P.blank_prim(pb)
+    W[L.phi(0)] = 1.0 - P.PHI_PURE
+    W[L.rho(0)] = 1600.0 * (1 + 0.01 * rng.uniform(-1, 1, n))
+    W[L.rho(1)] = solid.rho0
+    W[L.lam] = 1.0 - 1e-11 * rng.uniform(1.0, 2.0, n)
+    W[L.p] = 1e5 * (1 + 0.1 * rng.uniform(-1, 1, n))
+    g = S.Grid(pb)
+    g.set_primitive(W)
+    U = to_np(g.state).astype(LD)
+    p = to_np(g.primitive())[L.p].astype(LD)
+    py, E = U[0], U[L.E]
+    m = [U[L.m(0)], U[L.m(1)]]
+    rho = [m[0] / py, m[1] / (1 - py)]
+    lam = U[L.lam] / m[0]
+    args = (py, rho, lam, solid, pb.reactive, W[L.p].astype(LD))
+    ref = pressure_of(E, *args)
+    du = LD(2.0) ** -53
+    dlam = np.abs(pressure_of(E, py, rho, lam - 8 * du, *args[3:]) - ref) / 8
+    dE = np.abs(pressure_of(E * (1 + 8 * du), *args) - ref) / 8
+    assert np.all(np.abs(p - ref) <= 2 * (dlam + dE)), float((np.abs(p - ref) / (dlam + dE)).max())
