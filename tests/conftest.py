@@ -18,3 +18,13 @@ def _oracle_threads():
     from oracle import pyoracle
     pyoracle.set_threads(min(16, os.cpu_count() or 1))
     yield
+
+
+@pytest.fixture(autouse=True)
+def _seeded_draws(request):
+    """GPU tests that draw without a generator of their own draw the same each run"""
+    if request.node.get_closest_marker("gpu"):
+        import torch
+
+        torch.manual_seed(0)
+    yield
