@@ -999,12 +999,11 @@ __device__ __forceinline__ void sound_sums(const Params& P, const Phases<N>& Q, 
   gnum = 0.0;
 #pragma unroll
   for (int l = 0; l < N; ++l) {
-    if (rx_mix<RX>(P) && l == P.rx.mat) {
-      cnum += Q.phi[l] * T.yrc;
-    } else {
-      cnum += T.w[l] * T.c[l].rc;
-      gnum += T.w[l] * T.c[l].G;
-    }
+    // (values, not sums, chosen by the material: with the additions under the
+    // branch the compiler chose between the sums' addresses, in scratch memory)
+    const bool mix = rx_mix<RX>(P) && l == P.rx.mat;
+    cnum += mix ? Q.phi[l] * T.yrc : T.w[l] * T.c[l].rc;
+    gnum += mix ? 0.0 : T.w[l] * T.c[l].G;
   }
 }
 
