@@ -97,25 +97,11 @@ __device__ __forceinline__ void strain(const double* V, double H[6], double& J2)
       B[hs(i, j)] = s;
     }
   double A[6];
-  if (D == 1) {
-    A[0] = B[3] * B[5];
-    A[3] = B[0] * B[5];
-    A[5] = B[0] * B[3];
-    A[1] = A[2] = A[4] = 0.0;
-  } else if (D == 2) {
-    A[0] = B[3] * B[5];
-    A[1] = -B[1] * B[5];
-    A[3] = B[0] * B[5];
-    A[5] = B[0] * B[3] - B[1] * B[1];
-    A[2] = A[4] = 0.0;
-  } else {
-    A[0] = B[3] * B[5] - B[4] * B[4];
-    A[1] = B[2] * B[4] - B[1] * B[5];
-    A[2] = B[1] * B[4] - B[2] * B[3];
-    A[3] = B[0] * B[5] - B[2] * B[2];
-    A[4] = B[2] * B[1] - B[0] * B[4];
-    A[5] = B[0] * B[3] - B[1] * B[1];
-  }
+  A[0] = B[3] * B[5];
+  A[1] = -B[1] * B[5];
+  A[3] = B[0] * B[5];
+  A[5] = B[0] * B[3] - B[1] * B[1];
+  A[2] = A[4] = 0.0;
   double K[6];
 #pragma unroll
   for (int s = 0; s < 6; ++s) K[s] = 0.25 * (B[s] - A[s]);
@@ -126,10 +112,8 @@ __device__ __forceinline__ void strain(const double* V, double H[6], double& J2)
   H[1] = K[1];
   H[2] = K[2];
   H[4] = K[4];
-  double j2 = H[0] * H[0] + H[3] * H[3] + H[5] * H[5];
-  if (D >= 2) j2 += 2.0 * (H[1] * H[1]);
-  if (D == 3) j2 += 2.0 * (H[2] * H[2] + H[4] * H[4]);
-  J2 = j2;
+  J2 = H[0] * H[0] + H[3] * H[3] + H[5] * H[5];
+  J2 += 2.0 * (H[1] * H[1]);
 }
 
 // phi_l, rho_l and 1/rho_l of every material.  For two materials one

@@ -429,7 +429,7 @@ dimp_status sweep_launch(dimp_ctx* h, double dt, const double* dtp, int dir, boo
   }
   if (!h->patches) {
     HIPCHECK(dimp::launch_sweep(h->P, h->ndim, h->rxk(), h->buf[h->cur], h->buf[h->cur ^ 1], dt, dtp, dir,
-                                fuse, h->dpart, dimp::COL_SEGMENT, h->stream),
+                                fuse, h->dpart, h->stream),
              "sweep");
   } else if (!h->per_patch) {
     const dimp_ctx::List& L = dir == 0 ? h->lx : h->ylist(false);
@@ -1271,12 +1271,11 @@ dimp_status dimp_adjoint_step_kept(dimp_handle h, double dt, int64_t step_index,
   // forward); a caller that kept the first sweep's output passes it
   if (!U1) {
     HIPCHECK(dimp::launch_sweep(h->P, 2, false, state_in, aw_state(h, 0), dt, nullptr, d1, false, h->dpart,
-                                dimp::COL_SEGMENT, h->stream),
+                                h->stream),
              "adjoint: recompute sweep");
     U1 = aw_state(h, 0);
   }
-  HIPCHECK(dimp::launch_sweep(h->P, 2, false, U1, U2, dt, nullptr, d2, false, h->dpart, dimp::COL_SEGMENT,
-                              h->stream),
+  HIPCHECK(dimp::launch_sweep(h->P, 2, false, U1, U2, dt, nullptr, d2, false, h->dpart, h->stream),
            "adjoint: recompute sweep");
   // reverse: plastic relaxation, second sweep, first sweep
   // the three parameter partial-sum sets side by side, totalled once

@@ -7,9 +7,6 @@
 
 namespace dimp {
 
-// march length of the column sweeps (unused by the tile kernels)
-constexpr int COL_SEGMENT = 16;
-
 // patch sets: ghost layers stored around every patch, and the patch table
 constexpr int PATCH_GHOST = 2;
 struct PatchGeo {
@@ -58,19 +55,19 @@ hipError_t launch_param_total(const double* part, int64_t nblk, double* dparams,
 // the 3-D sweeps (dimp_sweeps3.hip), called by launch_sweep and
 // launch_rk_sweep for D = 3
 hipError_t launch_sweep3(const Params& P, int rx, const double* in, double* out, double dt, const double* dtp,
-                         int dir, bool fuse, double* part, int S, hipStream_t st);
+                         int dir, bool fuse, double* part, hipStream_t st);
 hipError_t launch_rk_sweep3(const Params& P, int rx, int dir, int mode, int stage, bool fuse, const double* in,
                             double* out, const double* Rin, const double* qn, double dt, const double* dtp,
                             double* part, hipStream_t st);
 // three materials on 1-D and 2-D grids (dimp_sweeps_n3.hip), called by
 // launch_sweep and launch_rk_sweep when P.nmat is 3
 hipError_t launch_sweep_n3(const Params& P, int D, int rx, const double* in, double* out, double dt,
-                           const double* dtp, int dir, bool fuse, double* part, int S, hipStream_t st);
+                           const double* dtp, int dir, bool fuse, double* part, hipStream_t st);
 hipError_t launch_rk_sweep_n3(const Params& P, int D, int rx, int dir, int mode, int stage, bool fuse,
                               const double* in, double* out, const double* Rin, const double* qn, double dt,
                               const double* dtp, double* part, hipStream_t st);
 hipError_t launch_sweep(const Params& P, int D, int rx, const double* in, double* out, double dt,
-                        const double* dtp, int dir, bool fuse, double* part, int S, hipStream_t st);
+                        const double* dtp, int dir, bool fuse, double* part, hipStream_t st);
 // One directional pass of stage `stage` (1..3) of the unsplit SSP-RK3
 // (Sec. 3.1), the stage being a qn + b (in - dt D(in)) with qn the step's
 // initial state.  mode 1 (y, the first direction): out = a qn + b (in - dt

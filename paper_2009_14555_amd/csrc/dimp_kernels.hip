@@ -289,17 +289,17 @@ __global__ __launch_bounds__(T) void k_reduce_smax(const double* __restrict__ pa
 
 // ---------------------------------------------------------------- launch
 hipError_t launch_sweep(const Params& P, int D, int rx, const double* in, double* out, double dt,
-                        const double* dtp, int dir, bool fuse, double* part, int S, hipStream_t st) {
+                        const double* dtp, int dir, bool fuse, double* part, hipStream_t st) {
 #define DIMP_SWEEP_RX(DD)                                                                  \
-  return rx == 2 ? launch_sweep_t<DD, 2, 2>(P, in, out, dt, dtp, dir, fuse, part, S, st)   \
-         : rx    ? launch_sweep_t<DD, 2, 1>(P, in, out, dt, dtp, dir, fuse, part, S, st)   \
-                 : launch_sweep_t<DD, 2, 0>(P, in, out, dt, dtp, dir, fuse, part, S, st)
-  if (P.nmat == 3) return launch_sweep_n3(P, D, rx, in, out, dt, dtp, dir, fuse, part, S, st);
+  return rx == 2 ? launch_sweep_t<DD, 2, 2>(P, in, out, dt, dtp, dir, fuse, part, st)   \
+         : rx    ? launch_sweep_t<DD, 2, 1>(P, in, out, dt, dtp, dir, fuse, part, st)   \
+                 : launch_sweep_t<DD, 2, 0>(P, in, out, dt, dtp, dir, fuse, part, st)
+  if (P.nmat == 3) return launch_sweep_n3(P, D, rx, in, out, dt, dtp, dir, fuse, part, st);
   if (P.nmat != 2) return hipErrorInvalidValue;
-  if (P.calib) return launch_sweep_p<2, 2, 0, PROF_CALIB>(P, in, out, dt, dtp, dir, fuse, part, S, st);
+  if (P.calib) return launch_sweep_p<2, 2, 0, PROF_CALIB>(P, in, out, dt, dtp, dir, fuse, part, st);
   if (D == 1) DIMP_SWEEP_RX(1);
   if (D == 2) DIMP_SWEEP_RX(2);
-  return launch_sweep3(P, rx, in, out, dt, dtp, dir, fuse, part, S, st);
+  return launch_sweep3(P, rx, in, out, dt, dtp, dir, fuse, part, st);
 #undef DIMP_SWEEP_RX
 }
 

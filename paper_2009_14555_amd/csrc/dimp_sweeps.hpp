@@ -23,8 +23,8 @@
 
 namespace dimp {
 
-// A tile sweep's block has four waves and 4 or 8 columns (a wave takes its
-// columns one after the other).  Eight columns read and write 64 contiguous
+// A tile sweep's block has four waves (eight in the wide 2-D tile below) and 4 or
+// 8 columns (a wave takes its columns one after the other).  Eight columns read and write 64 contiguous
 // bytes of a row instead of 32: 256^3, y 1757 -> 1549 us, z 2419 -> 2241 (with
 // eight waves, and with 16 columns, slower by a third and more: the LDS of 17
 // fields holds one such block a CU).  With the sources fused (z 3032, 3039) and
@@ -167,11 +167,11 @@ __global__ __launch_bounds__(256, (sweep_waves<D, N, RX, PROF, FUSE, false>())) 
 }
 
 // ---------------------------------------------------------- tile sweep
-// Sweep along y or z.  A block of CW waves covers CW consecutive x columns
+// Sweep along y or z.  A block of NW waves covers CW consecutive x columns
 // and 64 cells along the sweep axis; the tile is staged through LDS so that
-// HBM sees rows of CW doubles, while each wave holds one column with one cell
-// per lane and runs the same stages as the row sweep.  The blocks
-// of a run (xcd_block) are neighbouring x chunks, which share L2 lines.
+// HBM sees rows of CW doubles, while each wave takes the columns w, w + NW, ...,
+// one at a time with one cell per lane, through the same stages as the row
+// sweep.  The blocks of a run (xcd_block) are neighbouring x chunks, which share L2 lines.
 template <int D, int N, int RX, int PROF, int DIR, bool FUSE, int CW, int MODE = M_SPLIT, bool WALL = false,
           int NW = TILE_WAVES>
 __global__ __launch_bounds__(64 * NW, (sweep_waves<D, N, RX, PROF, FUSE, true>())) void sweep_tile(Params P, const double* __restrict__ in,
@@ -376,8 +376,7 @@ static hipError_t launch_rk_p(const Params& P, int dir, int mode, int stage, boo
 
 template <int D, int N, int RX, int PROF>
 static hipError_t launch_sweep_p(const Params& P, const double* in, double* out, double dt, const double* dtp,
-                                 int dir, bool fuse, double* part, int S, hipStream_t st) {
-  (void)S;
+                                 int dir, bool fuse, double* part, hipStream_t st) {
   const int block = 256;
   if (dir == 0) {
     const int grid = row_grid(P);
@@ -418,9 +417,9 @@ static hipError_t launch_sweep_p(const Params& P, const double* in, double* out,
 // the instance of the materials' profile
 template <int D, int N, int RX>
 static hipError_t launch_sweep_t(const Params& P, const double* in, double* out, double dt, const double* dtp,
-                                 int dir, bool fuse, double* part, int S, hipStream_t st) {
+                                 int dir, bool fuse, double* part, hipStream_t st) {
   return by_profile<N, RX>(P, [&](auto prof) {
-    return launch_sweep_p<D, N, RX, decltype(prof)::value>(P, in, out, dt, dtp, dir, fuse, part, S, st);
+    return launch_sweep_p<D, N, RX, decltype(prof)::value>(P, in, out, dt, dtp, dir, fuse, part, st);
   });
 }
 

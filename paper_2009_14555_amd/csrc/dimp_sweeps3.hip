@@ -8,10 +8,10 @@
 namespace dimp {
 
 hipError_t launch_sweep3(const Params& P, int rx, const double* in, double* out, double dt, const double* dtp,
-                         int dir, bool fuse, double* part, int S, hipStream_t st) {
-  return rx == 2 ? launch_sweep_t<3, 2, 2>(P, in, out, dt, dtp, dir, fuse, part, S, st)
-         : rx    ? launch_sweep_t<3, 2, 1>(P, in, out, dt, dtp, dir, fuse, part, S, st)
-                 : launch_sweep_t<3, 2, 0>(P, in, out, dt, dtp, dir, fuse, part, S, st);
+                         int dir, bool fuse, double* part, hipStream_t st) {
+  return rx == 2 ? launch_sweep_t<3, 2, 2>(P, in, out, dt, dtp, dir, fuse, part, st)
+         : rx    ? launch_sweep_t<3, 2, 1>(P, in, out, dt, dtp, dir, fuse, part, st)
+                 : launch_sweep_t<3, 2, 0>(P, in, out, dt, dtp, dir, fuse, part, st);
 }
 
 hipError_t launch_rk_sweep3(const Params& P, int rx, int dir, int mode, int stage, bool fuse, const double* in,

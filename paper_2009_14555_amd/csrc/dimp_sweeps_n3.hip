@@ -8,11 +8,11 @@
 namespace dimp {
 
 hipError_t launch_sweep_n3(const Params& P, int D, int rx, const double* in, double* out, double dt,
-                           const double* dtp, int dir, bool fuse, double* part, int S, hipStream_t st) {
+                           const double* dtp, int dir, bool fuse, double* part, hipStream_t st) {
 #define DIMP_SWEEP3_RX(DD)                                                                 \
-  return rx == 2 ? launch_sweep_t<DD, 3, 2>(P, in, out, dt, dtp, dir, fuse, part, S, st)   \
-         : rx    ? launch_sweep_t<DD, 3, 1>(P, in, out, dt, dtp, dir, fuse, part, S, st)   \
-                 : launch_sweep_t<DD, 3, 0>(P, in, out, dt, dtp, dir, fuse, part, S, st)
+  return rx == 2 ? launch_sweep_t<DD, 3, 2>(P, in, out, dt, dtp, dir, fuse, part, st)   \
+         : rx    ? launch_sweep_t<DD, 3, 1>(P, in, out, dt, dtp, dir, fuse, part, st)   \
+                 : launch_sweep_t<DD, 3, 0>(P, in, out, dt, dtp, dir, fuse, part, st)
   if (D == 1) DIMP_SWEEP3_RX(1);
   if (D == 2) DIMP_SWEEP3_RX(2);
 #undef DIMP_SWEEP3_RX

@@ -76,7 +76,7 @@ int flux_unit(const dimp_material* mats, const dimp_options* o, const int64_t* n
   P.prof = PROF_GAS_SOLID;
   P.calib = calib;
   P.rx.mat = -1;
-  if (launch_sweep(P, 2, 0, U, Un, dt, nullptr, dir, false, nullptr, COL_SEGMENT, nullptr) != hipSuccess) return 1;
+  if (launch_sweep(P, 2, 0, U, Un, dt, nullptr, dir, false, nullptr, nullptr) != hipSuccess) return 1;
   const FaceSet fs{{pos, pos + 1}, t0, len};
   if (launch_amr_flux(P, 0, dir, fs, U, dt, flux, nullptr) != hipSuccess) return 2;
   return hipDeviceSynchronize() != hipSuccess;
