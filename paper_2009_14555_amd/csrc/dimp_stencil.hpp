@@ -249,16 +249,16 @@ __device__ __forceinline__ double m_lambda(const Params& P, const double* W) {
 // Flux of side K: the physical flux F_K plus S_K (U*_K - U_K), the HLLC-type
 // star state with velocity (S*, u*_t) and traction continuous across the
 // contact and Rankine-Hugoniot across S_K.  A supersonic face passes SK = 0
-// with a = inv = 1, which returns F_K exactly.
+// with a = inv = 1, which returns F_K exactly.  rm1 is a inv - 1, which the caller
+// has as (S* - u_n) inv, without the cancellation.
 template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void star_flux(const Params& P, const double* W, const Side<D, N, RX>& S, double SK,
                                           double a, double inv, const double ust[D], double mK,
-                                          FaceV<D, N, RX>& out) {
+                                          FaceV<D, N, RX>& out, double rm1) {
   using L = Lay<D, N, RX>;
   const double un = S.u[DIR];
   const double r = a * inv;
-  // S_K (r - 1) = S_K (S* - u_n) / (S_K - S*), without the cancellation of r - 1
-  const double us_face = un + SK * ((ust[DIR] - un) * inv);
+  const double us_face = un + SK * rm1;
   // F_K + S_K (U*_K - U_K) collected: a mass m moves with the face velocity
   // u* = u_n + S_K (r - 1), every other term with S_K / (S_K - S*) = SK inv of
   // its star correction; the normal row of Vbar is continuous and carries no
@@ -306,6 +306,14 @@ __device__ __forceinline__ void star_flux(const Params& P, const double* W, cons
   for (int j = 0; j < D; ++j) out.Vn[j] = vget<D, N, RX>(W + L::V0, DIR, j);
 }
 
+// the same for any a and inv
+template <int D, int N, int RX, int DIR>
+__device__ __forceinline__ void star_flux(const Params& P, const double* W, const Side<D, N, RX>& S, double SK,
+                                          double a, double inv, const double ust[D], double mK,
+                                          FaceV<D, N, RX>& out) {
+  star_flux<D, N, RX, DIR>(P, W, S, SK, a, inv, ust, mK, out, a * inv - 1.0);
+}
+
 template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void face_flux(const Params& P, const double* WL, const double* WR,
                                           FaceV<D, N, RX>& out, bool wall = false) {
@@ -349,14 +357,14 @@ __device__ __forceinline__ void face_flux(const Params& P, const double* WL, con
   const double m_K = left ? mL : mR;
   const double a = sup ? 1.0 : S_K - SK.u[DIR];
   const double inv = sup ? 1.0 : frcp(S_K - Sst);
-  star_flux<D, N, RX, DIR>(P, WK, SK, sup ? 0.0 : S_K, a, inv, ust, m_K, out);
+  star_flux<D, N, RX, DIR>(P, WK, SK, sup ? 0.0 : S_K, a, inv, ust, m_K, out, (Sst - SK.u[DIR]) * inv);
   if (tie) {
     // S* exactly zero: the average of both star fluxes.  A tie is never
     // 'left', so out already holds the right one; only the left one is
     // added.  (Every face between cells of a fluid at rest is a tie.)
     FaceV<D, N, RX> o1;
-    const double a1 = SL - A.u[DIR];
-    star_flux<D, N, RX, DIR>(P, WL, A, SL, a1, frcp(SL), ust, mL, o1);
+    const double a1 = SL - A.u[DIR], inv1 = frcp(SL);
+    star_flux<D, N, RX, DIR>(P, WL, A, SL, a1, inv1, ust, mL, o1, -A.u[DIR] * inv1);
 #pragma unroll
     for (int f = 0; f < F; ++f) out.F[f] = 0.5 * (o1.F[f] + out.F[f]);
     out.ustar = 0.5 * (o1.ustar + out.ustar);
