@@ -11,6 +11,15 @@
 // from one version of the library to the next: the forms below (1/rho closures,
 // IEEE quotients where they stand) are not the cheaper ones of
 // dimp_device.hpp and dimp_stencil.hpp, which every other run takes.
+//
+// On the grids that the adjoint takes (Params::calib, whether or not gradients are
+// taken) these kernels follow it: the split sweeps with their fused plastic step
+// and wave speed, the initial state from primitive fields, the boundary fluxes of
+// a refined patch, and the adjoint's recomputation.  The general forms stay in the
+// wave speed of a given state (the first dt of device CFL steps), the source step
+// called by itself, the conversion to primitive fields, the state check, and the
+// unsplit integrator's passes.  A run forward only pays for it: four steps of
+// 2048^2, van Albada, 2820 us against 2265 with the general stages (700^2: 420, 350).
 #pragma once
 #include "dimp_stencil.hpp"
 

@@ -11,8 +11,12 @@ namespace dimp {
 // all of them.  One run for each XCD left a 400 x 1000 detonating stick at 691 us
 // for two steps, where runs of 16 blocks take 445 (4: 458, 64: 538); 256^3, with
 // 10 times the blocks, 13310 us, where runs of 64 take 12070 (16: 12140, 4:
-// 12480); 2048^2 1935, 1852 (16: 1885, 4: 1978).  So a run is as long as leaves
-// each XCD eight runs or more, up to 64 blocks.
+// 12480); 2048^2 1935, 1852 (16: 1885, 4: 1978).  So runs of 4 and 16 start where
+// they leave each XCD eight runs, and runs of 64 at 32 each: with 4096 to 16384
+// blocks they would leave eight to 32, and the reaction zone of a 500 x 2000 stick
+// (4500 blocks) takes 775 us for two steps against 640 in runs of 16, of an 800 x
+// 2000 one (7000) 1005 against 855, while discs of 1000^2 to 1900^2, three materials
+// at 1000^2 and slabs of 110^3 and 150^3 take the same in both.
 __device__ __forceinline__ int64_t xcd_block(uint32_t b, uint32_t nb) {
   const int sh = nb >= 16384 ? 6 : nb >= 1024 ? 4 : nb >= 256 ? 2 : 0;  // log2 of the run
   const uint32_t group = 8u << sh;

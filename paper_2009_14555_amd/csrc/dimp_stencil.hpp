@@ -81,6 +81,7 @@ __device__ __forceinline__ void shear_col(const Params& P, const double* W, doub
   for (int k = 0; k < 3; ++k) sig[k] = hnz<D>(k, DIR) ? G2 * H[hs(k, DIR)] : 0.0;
 }
 
+// (the half step calls shear_col; with the pressure for the tests of the stages)
 template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void stress_col(const Params& P, const double* W, double sig[3]) {
   MixY my{}, mw{};
@@ -183,6 +184,7 @@ __device__ __forceinline__ void edges_half_step(const Params& P, const double* W
   }
 }
 
+// (the sweeps call the three parts; together for the tests of the stages)
 template <int D, int N, int RX, int DIR, class C>
 __device__ __forceinline__ void edges_predict(const Params& P, const double* Wm, const double* W0, const double* Wp,
                                               double irho0, double rc2, const C& cm, const C& c0, const C& cp,
@@ -306,7 +308,7 @@ __device__ __forceinline__ void star_flux(const Params& P, const double* W, cons
   for (int j = 0; j < D; ++j) out.Vn[j] = vget<D, N, RX>(W + L::V0, DIR, j);
 }
 
-// the same for any a and inv
+// the same for any a and inv (the tests of the stages)
 template <int D, int N, int RX, int DIR>
 __device__ __forceinline__ void star_flux(const Params& P, const double* W, const Side<D, N, RX>& S, double SK,
                                           double a, double inv, const double ust[D], double mK,

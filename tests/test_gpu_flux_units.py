@@ -65,3 +65,47 @@ def test_recorded_fluxes_are_the_sweeps(limiter, d):
         bound = 2.0**-53 * (4 * np.abs(inc) + np.maximum(np.abs(u0), np.abs(u1)))
         off = np.abs(u1 - (u0 - inc)) - bound
         assert np.all(off[cons] <= 0), (pos, d, [(f, float((np.abs(u1 - (u0 - inc)) / bound)[f].max())) for f in cons])
+
+
+@pytest.mark.parametrize("integrator", ["split", "rk3"])
+def test_refined_interface_conserves_with_van_albada(integrator):
+    """a solid disc moving in water, THINC on, its interface crossing the patch's
+    boundary: the composite grid keeps partial masses, momentum and energy to
+    round-off (the bound of the other refinement tests)"""
+    from oracle import amr as A
+    from paper_2009_14555_amd import solver as S
+    from tests.test_oracle_amr import prolong_prim
+
+    n, box = (40, 36), (8, 7, 24, 27)
+    pbc = P.Problem(ndim=2, n=(n[0], n[1], 1), dx=(1 / n[0], 1 / n[1], 1), bc=(P.BC_PERIODIC,) * 3,
+                    materials=[P.water_sg(), P.solid_c2()], thinc=1, limiter=P.LIM_VANALBADA, cfl=0.4)
+    L = P.layout(pbc)
+    x, y = P.cell_centres(pbc)
+    W = P.blank_prim(pbc)
+    W[L.phi(0)] = np.clip(0.5 + (np.hypot(x - 0.5, y - 0.5) - 0.22) * n[0], 1e-6, 1 - 1e-6)
+    W[L.rho(0)] = 1000.0 * (1 + 0.01 * np.sin(2 * np.pi * (x + y)))
+    W[L.rho(1)] = 2700.0
+    W[L.u(0)], W[L.u(1)] = 60.0, 20.0 * np.cos(2 * np.pi * x)
+    W[L.p] = 1e8 * (1 + 0.5 * np.exp(-60.0 * ((x - 0.4) ** 2 + (y - 0.5) ** 2)))
+    pbf = A.fine_problem(pbc, box)
+    gc, gf = S.Grid(pbc), S.Grid(pbf)
+    gc.set_primitive(W)
+    gf.set_primitive(prolong_prim(pbc, W, pbf, box)[0])
+    gc.set_integrator(integrator)
+    gf.set_integrator(integrator)
+    h = S.Hierarchy(gc, gf, box)
+    cons = list(range(L.nphi, L.V(0)))
+    inner = A.interior_mask(box)
+    i0, j0, i1, j1 = box
+
+    def totals():
+        Uc, Uf = to_np(gc.state), to_np(gf.state)
+        out = Uc[cons].sum(axis=(1, 2)) - Uc[cons, j0:j1, i0:i1].sum(axis=(1, 2))
+        return out + Uf[cons][:, inner].sum(axis=1) / 4
+
+    m0 = totals()
+    for _ in range(12):
+        h.advance(h.dt(pbc.cfl))
+    drift = np.abs(totals() - m0) / np.maximum(np.abs(m0), 1.0)
+    h.close()
+    assert np.all(np.isfinite(drift)) and np.all(drift < 1e-12), drift
